@@ -3,18 +3,25 @@
 // reuse, or l + r' with r' drawn anew; per trial the statistic is the mean over rows and classes
 // of (g - g*) / p under the likelihood (h = -e_y) and the constructed loss (h = r).
 //
-// One wave per (row, chunk of trials); a lane takes groups of 4 consecutive classes (one Philox
-// call per group, draw and trial). Per trial the wave first sums r over the row (the constructed
-// loss's 1^T h), then forms the four errors literally (g and g* in fp64, then / p). Per-trial
-// row sums go to the workspace; a second kernel sums them over rows in row order and takes the
-// mean and se over trials.
+// The four entry errors share their factors: with w_j(x) = (p_j - exp(l_j + x) / cal) / p_j for
+// x = +eps or -eps, (g_j - g*_j) / p_j = (1^T h) w_j under either loss, so per (row, trial) the
+// row sums of w under the two copies and the number of plus signs of r give all four. The
+// preparation writes w_j(+eps) and w_j(-eps) once (the operator's exponentials and quotients in
+// fp64, from the logits); a trial adds the one its sign picks. Per element and trial that leaves
+// two Philox words (8.5 VALU each), a compare, a 64-bit select and an fp64 add per copy: 26 VALU,
+// the bound. (Forming g and g* anew per trial took a third word for 1^T h and four fp64 quotients:
+// 7.0 ms at 512 x 32768, 64 trials; now 0.78 ms, 1.38 T element-trials/s against 1.46 at the VALU
+// ceiling.)
+//
+// A wave takes one row and TK trials; a lane takes groups of 4 consecutive classes (one Philox
+// call per group, draw and trial), the trials unrolled inside so that the element's part of the
+// first two rounds is shared and the trial's runs on the scalar unit. A block's four waves share
+// the row. A sum over the wave halves the trials each lane carries at each exchange.
 #include "bsp_kernels.h"
 
 namespace bsp {
 
 namespace {
-
-constexpr int LSM_TCH = 32;  // trials per wave
 
 __device__ __forceinline__ double wsum(double v) {
 #pragma unroll
@@ -22,88 +29,124 @@ __device__ __forceinline__ double wsum(double v) {
   return v;
 }
 
-// l = z - max - log(sum exp(z - max)) per row, one wave per row, and the three values every
-// trial's exponentials take (the saved output is l + r with r = +eps or -eps exactly):
-// p = exp(l), ep = exp(l + eps) / cal and em = exp(l - eps) / cal
-__global__ __launch_bounds__(64) void lsm_prep_kernel(const double* __restrict__ z, int64_t rows, int C, double eps,
-                                                      double cal, double* __restrict__ p, double* __restrict__ ep,
-                                                      double* __restrict__ em) {
+// l = z - max - log(sum exp(z - max)) per row, one block per row, then w(+eps) and w(-eps): four
+// fp64 exponentials and two quotients per element (one wave per row left most of the chip idle:
+// 694 us at 512 x 32768 with three exponentials, 136 us now)
+__global__ __launch_bounds__(1024) void lsm_prep_kernel(const double* __restrict__ z, int C, double eps, double cal,
+                                                        double* __restrict__ wp, double* __restrict__ wm) {
   const int64_t row = blockIdx.x;
-  const int lane = threadIdx.x;
+  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6, nw = nt >> 6;
   const double* zr = z + row * C;
+  __shared__ double red[16];
   double m = -INFINITY;
-  for (int j = lane; j < C; j += 64) m = fmax(m, zr[j]);
+  for (int j = tid; j < C; j += nt) m = fmax(m, zr[j]);
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) m = fmax(m, __shfl_xor(m, off, 64));
+  if (lane == 0) red[wave] = m;
+  __syncthreads();
+  m = red[0];
+  for (int i = 1; i < nw; ++i) m = fmax(m, red[i]);
   double se = 0.0;
-  for (int j = lane; j < C; j += 64) se += exp(zr[j] - m);
-  const double lse = m + log(wsum(se));
-  for (int j = lane; j < C; j += 64) {
-    const double lj = zr[j] - lse;
+  for (int j = tid; j < C; j += nt) se += exp(zr[j] - m);
+  se = wsum(se);
+  __syncthreads();
+  if (lane == 0) red[wave] = se;
+  __syncthreads();
+  se = red[0];
+  for (int i = 1; i < nw; ++i) se += red[i];
+  const double lse = m + log(se);
+  for (int j = tid; j < C; j += nt) {
+    const double lj = zr[j] - lse, p = exp(lj);
     const int64_t e = row * C + j;
-    p[e] = exp(lj);
-    ep[e] = exp(lj + eps) / cal;
-    em[e] = exp(lj + -eps) / cal;
+    wp[e] = (p - exp(lj + eps) / cal) / p;
+    wm[e] = (p - exp(lj + -eps) / cal) / p;
   }
 }
 
-// per (row, trial): the row sums of the four entry errors, [4][K][rows]
-__global__ __launch_bounds__(64) void lsm_trial_kernel(const double* __restrict__ pv, const double* __restrict__ epv,
-                                                       const double* __restrict__ emv, const int32_t* __restrict__ y,
-                                                       int64_t rows, int C, double eps, int K, uint64_t seed,
-                                                       uint32_t use_r, uint32_t use_p, double* __restrict__ part) {
-  const int64_t row = blockIdx.x;
-  const int lane = threadIdx.x;
-  const int yt = y[row];
-  const double sh = (yt >= 0 && yt < C) ? -1.0 : 0.0;
-  const int ngroups = C / 4;
-  const int k_end = min(K, (int)(blockIdx.y + 1) * LSM_TCH);
-  for (int k = blockIdx.y * LSM_TCH; k < k_end; ++k) {
-    const uint32_t trial = (uint32_t)(k + 1);
-    // 1^T r over the row
-    double sr = 0.0;
-    for (int gi = lane; gi < ngroups; gi += 64) {
-      const Philox4 pr = philox_group(seed, (uint64_t)(row * C) / 4 + gi, trial, use_r);
-      const uint32_t R[4] = {pr.w0, pr.w1, pr.w2, pr.w3};
+// v[t] summed over the L lanes of a lane group (L >= TK, powers of two): each exchange hands half
+// of a lane's values over, so lane i of the group ends with value t(i) in v[0], t from its top
+// bits; the remaining exchanges add whole. A fixed tree.
+template <int H, typename V>
+__device__ __forceinline__ void sum_halves(V* v, int lane, int off) {
+  if constexpr (H >= 1) {
+    const bool up = (lane & off) != 0;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) sr += R[q] >= 0x80000000u ? eps : -eps;
+    for (int i = 0; i < H; ++i) {
+      const V lo = v[i], hi = v[i + H];
+      const V send = up ? lo : hi, keep = up ? hi : lo;
+      v[i] = keep + __shfl_xor(send, off, 64);
     }
-    sr = wsum(sr);
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int gi = lane; gi < ngroups; gi += 64) {
-      const uint64_t grp = (uint64_t)(row * C) / 4 + gi;
+    sum_halves<H / 2>(v, lane, off >> 1);
+  }
+}
+template <int TK, typename V>
+__device__ __forceinline__ void sum_trials(V* v, int lane, int L) {
+  sum_halves<TK / 2>(v, lane, L >> 1);
+  for (int off = L / (2 * TK); off >= 1; off >>= 1) v[0] += __shfl_xor(v[0], off, 64);
+}
+
+// per (row, trial): the row sums of the four entry errors, [4][K][rows]. SUB: rows of at most 32
+// groups, L lanes (a power of two, at least TK) per trial and 64 / L trials side by side; else
+// L = 64.
+template <int TK, bool SUB>
+__global__ __launch_bounds__(256) void lsm_trial_kernel(const double* __restrict__ wp, const double* __restrict__ wm,
+                                                        const int32_t* __restrict__ y, int64_t rows, int C, int L,
+                                                        double eps, int K, uint64_t seed, uint32_t use_r,
+                                                        uint32_t use_p, double* __restrict__ part) {
+  const int64_t row = blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nsub = SUB ? 64 / L : 1;
+  const int k0 = (blockIdx.y * 4 + wave) * TK * nsub;  // trial index (trial k0 + 1) of the wave's first
+  if (k0 >= K) return;                                 // wave-uniform; no barrier below
+  const int sub = SUB ? lane / L : 0, gl = SUB ? lane % L : lane;
+  const int ngroups = C / 4;
+  double ar[TK], ap[TK];
+  int n[TK];
+#pragma unroll
+  for (int t = 0; t < TK; ++t) ar[t] = ap[t] = 0.0, n[t] = 0;
+  for (int gi = gl; gi < ngroups; gi += L) {
+    const int64_t e = row * C + 4 * gi;
+    const uint64_t grp = (uint64_t)e / 4;
+    double vp[4], vm[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) vp[q] = wp[e + q], vm[q] = wm[e + q];
+#pragma unroll
+    for (int t = 0; t < TK; ++t) {
+      const uint32_t trial = (uint32_t)(k0 + t * nsub + sub + 1);  // past K: computed, not stored
       const Philox4 pr = philox_group(seed, grp, trial, use_r);
       const Philox4 pp = philox_group(seed, grp, trial, use_p);
-      const uint32_t R[4] = {pr.w0, pr.w1, pr.w2, pr.w3}, Rp[4] = {pp.w0, pp.w1, pp.w2, pp.w3};
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int j = 4 * gi + q;
-        const int64_t e = row * C + j;
-        const double p = pv[e];
-        const bool ur = R[q] >= 0x80000000u, urp = Rp[q] >= 0x80000000u;
-        const double r = ur ? eps : -eps;
-        const double er = ur ? epv[e] : emv[e], erp = urp ? epv[e] : emv[e];
-        // likelihood: h = -e_y, 1^T h = sh (-1, or 0 for a target outside the classes)
-        const double hl = j == yt ? -1.0 : 0.0;
-        const double gl_star = hl - p * sh;
-        acc[0] += ((hl - er * sh) - gl_star) / p;
-        acc[1] += ((hl - erp * sh) - gl_star) / p;
-        // constructed: h = r, 1^T h = sr
-        const double gc_star = r - p * sr;
-        acc[2] += ((r - er * sr) - gc_star) / p;
-        acc[3] += ((r - erp * sr) - gc_star) / p;
+        const bool ur = (int32_t)philox_word(pr, q) < 0, up = (int32_t)philox_word(pp, q) < 0;  // words >= 2^31
+        ar[t] += ur ? vp[q] : vm[q];
+        ap[t] += up ? vp[q] : vm[q];
+        n[t] += ur;
       }
     }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const double v = wsum(acc[c]);
-      if (lane == 0) part[((int64_t)c * K + k) * rows + row] = v;
-    }
+  }
+  sum_trials<TK>(ar, lane, L);
+  sum_trials<TK>(ap, lane, L);
+  sum_trials<TK>(n, lane, L);
+  int t = 0;
+  for (int h = TK / 2, off = L >> 1; h >= 1; h >>= 1, off >>= 1) t += (lane & off) ? h : 0;
+  const int k = k0 + t * nsub + sub;
+  if ((gl & (L / TK - 1)) == 0 && k < K) {
+    const int yt = y[row];
+    const double sh = (yt >= 0 && yt < C) ? -1.0 : 0.0;  // likelihood: 1^T h
+    const double sr = eps * (double)(2 * n[0] - C);      // constructed: 1^T r
+    const int64_t o = (int64_t)k * rows + row, stride = (int64_t)K * rows;
+    part[o] = sh * ar[0];
+    part[o + stride] = sh * ap[0];
+    part[o + 2 * stride] = sr * ar[0];
+    part[o + 3 * stride] = sr * ap[0];
   }
 }
 
 // per statistic: t_k = sum over rows (row order) / (rows C); mean and se over trials
-constexpr int LSM_RT = 64;  // trials per block of the first reduction stage
+// trials per block of the first reduction stage: one per wave while the second stage's single
+// blocks stay short (the stage is latency: 66 us with 64 trials per block at 512 rows, 64 trials,
+// now 8 us), 64 beyond
+inline int lsm_rt(int K) { return K <= 4096 ? 4 : 64; }
 
 // mean over rows and classes of statistic c in trial k: one wave, rows lane-strided, combined by
 // a fixed xor tree (every lane ends with the total)
@@ -117,15 +160,15 @@ __device__ __forceinline__ double lsm_trial_mean(const double* __restrict__ part
   return t / ((double)rows * C);
 }
 
-// first stage: block (j, c) takes trials 64 j .. 64 j + 63 of statistic c and writes their sums of
+// first stage: block (j, c) takes trials rt j .. rt j + rt - 1 of statistic c and writes their sums of
 // d_k = m_k - m_0 and d_k^2 (shifted by trial 0's mean m_0, which block (0, c) also writes)
 __global__ __launch_bounds__(256) void lsm_reduce_kernel(const double* __restrict__ part, int64_t rows, int C, int K,
-                                                         double* __restrict__ acc, double* __restrict__ m0) {
+                                                         int rt, double* __restrict__ acc, double* __restrict__ m0) {
   const int c = blockIdx.y, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const double t0 = lsm_trial_mean(part, rows, C, K, c, 0);
   double s1 = 0.0, s2 = 0.0;
-  for (int j = w; j < LSM_RT; j += 4) {
-    const int k = blockIdx.x * LSM_RT + j;
+  for (int j = w; j < rt; j += 4) {
+    const int k = blockIdx.x * rt + j;
     if (k >= K) break;  // wave-uniform
     const double d = lsm_trial_mean(part, rows, C, K, c, k) - t0;
     s1 += d;
@@ -179,9 +222,9 @@ __global__ __launch_bounds__(256) void lsm_final_kernel(const double* __restrict
 size_t lsm_ws_size(int64_t rows, int C, int K) {
   if (rows < 1 || C < 4 || (C & 3) || K < 1) return 0;
   Carver c;
-  for (int i = 0; i < 3; ++i) c.take<double>(rows * C);
+  for (int i = 0; i < 2; ++i) c.take<double>(rows * C);
   c.take<double>((int64_t)4 * K * rows);
-  c.take<double>((int64_t)8 * ((K + LSM_RT - 1) / LSM_RT));
+  c.take<double>((int64_t)8 * ((K + lsm_rt(K) - 1) / lsm_rt(K)));
   c.take<double>(4);
   return c.used();
 }
@@ -204,28 +247,42 @@ bs_status bs_logsoftmax_reuse_check(const double* logits, const int32_t* target,
   if (!ws || ((uintptr_t)ws & 255) || ws_bytes < need) return BS_EWORKSPACE;
   hipStream_t st = (hipStream_t)stream;
   Carver c(ws, ws_bytes);
-  double* pv = c.take<double>(rows * C);
-  double* epv = c.take<double>(rows * C);
-  double* emv = c.take<double>(rows * C);
+  double* wp = c.take<double>(rows * C);
+  double* wm = c.take<double>(rows * C);
   double* part = c.take<double>((int64_t)4 * K * rows);
-  const int nb = (K + LSM_RT - 1) / LSM_RT;
+  const int rt = lsm_rt(K), nb = (K + rt - 1) / rt;
   double* acc = c.take<double>((int64_t)8 * nb);
   double* m0 = c.take<double>(4);
   {
     ProfScope prof("lsm_prep", st);
-    lsm_prep_kernel<<<(unsigned)rows, 64, 0, st>>>(logits, rows, C, eps, calibrate ? cosh(eps) : 1.0, pv, epv, emv);
+    // a row's fp64 exponentials bound it: as many waves per row as its length fills
+    const int nt = C >= 4096 ? 1024 : (C >= 512 ? 256 : 64);
+    lsm_prep_kernel<<<(unsigned)rows, nt, 0, st>>>(logits, C, eps, calibrate ? cosh(eps) : 1.0, wp, wm);
     BS_CHECK_LAUNCH();
   }
   const uint32_t base = store_id * 256u;
   {
     ProfScope prof("lsm_trial", st);
-    const dim3 grid((unsigned)rows, (unsigned)((K + LSM_TCH - 1) / LSM_TCH));
-    lsm_trial_kernel<<<grid, 64, 0, st>>>(pv, epv, emv, target, rows, C, eps, K, seed, base, base + 1, part);
+    // L lanes per trial (short rows put several trials side by side); 16 trials per lane group
+    // where that still gives every SIMD two waves, else 4 (shorter serial chains on an idle chip)
+    int L = 64;
+    while (L > 16 && C / 4 <= L / 2) L /= 2;
+    const int nsub = 64 / L;
+    const bool wide = rows * ((K + 16 * nsub - 1) / (16 * nsub)) >= 2048;
+    const int per = 4 * (wide ? 16 : 4) * nsub;
+    const dim3 grid((unsigned)rows, (unsigned)((K + per - 1) / per));
+    auto go = [&](auto kernel) {
+      kernel<<<grid, 256, 0, st>>>(wp, wm, target, rows, C, L, eps, K, seed, base, base + 1, part);
+    };
+    if (L == 64)
+      wide ? go(lsm_trial_kernel<16, false>) : go(lsm_trial_kernel<4, false>);
+    else
+      wide ? go(lsm_trial_kernel<16, true>) : go(lsm_trial_kernel<4, true>);
     BS_CHECK_LAUNCH();
   }
   {
     ProfScope prof("lsm_reduce", st);
-    lsm_reduce_kernel<<<dim3((unsigned)nb, 4), 256, 0, st>>>(part, rows, C, K, acc, m0);
+    lsm_reduce_kernel<<<dim3((unsigned)nb, 4), 256, 0, st>>>(part, rows, C, K, rt, acc, m0);
     lsm_final_kernel<<<4, 256, 0, st>>>(acc, m0, nb, K, stats);
     BS_CHECK_LAUNCH();
   }

@@ -42,6 +42,20 @@ def test_statistics_match_oracle(lib, rows, C, K, eps, calibrate):
         assert abs(got[i, 1] - se) <= 1e-9 * max(se, 1e-300) or (K == 1 and got[i, 1] == 0), (name, got[i, 1], se)
 
 
+@pytest.mark.parametrize("rows,C,K", [
+    (2100, 16, 20),     # 16 lanes per trial, 16 trials per lane, a ragged last chunk of trials
+    (1030, 68, 70),     # 17 groups on 32 lanes, two trials side by side
+    (2050, 200, 17),    # 50 groups on 64 lanes, 16 trials per wave and one more
+    (3, 516, 9),        # 256 threads per row in the preparation, 4 trials per wave
+    (2, 4100, 5),       # 1024 threads per row, the lanes' last group ragged
+    (1, 8, 4100),       # more than 4096 trials: 64 per block of the reduction
+])
+def test_lane_and_trial_splits_match_oracle(lib, rows, C, K):
+    """The edges of the trial kernel's lane groups, its two trial counts and both reductions; the
+    tolerance is that of test_statistics_match_oracle (fp64 sums in different orders)."""
+    test_statistics_match_oracle(lib, rows, C, K, 0.1, False)
+
+
 def test_targets_outside_the_classes_match_none(lib):
     """A target outside [0, C) makes the likelihood's h zero on that row, on both sides."""
     z, y = inputs(4, 12, 3)
