@@ -220,26 +220,117 @@ __global__ __launch_bounds__(256) void quantize_kernel(const T* __restrict__ x, 
   if ((threadIdx.x & 63) == 0 && nsat) atomicAdd(&diag->n_saturated, nsat);
 }
 
-// K-trial counter of new roundings of a [T, d] store y = fl32(x / s) (d % 4 == 0).
-// counts[t, j] = number of trials k in 1..K whose rounding of element t*d + j goes up.
-// Block: 256 threads = 64 column groups (4 columns each) x 4 row lanes, 8 rows per thread,
-// so one block covers 32 rows x 256 columns. The row lane is the wave, except for FC_COLSUM,
-// where a wave holds 16 column groups x 4 row lanes so that the column sums reduce inside the
-// wave (cross-lane adds in a fixed order, no barrier). With c = sign(y) step (t, j) w(t, j):
-//   FC_COLSUM: colsum[k-1][rt][j] = sum over the block's 32 rows of up_k c (w = w1), fp32
-//   FC_BLOCKSUM: partial[k-1][i][b] = sum over the block's elements of up_k c_i (w1, w2), fp64
+// K-trial counters of new roundings of a [T, d] store y = fl32(x / s) (d % 4 == 0):
+// counts[t, j] = number of trials k whose rounding of element t*d + j goes up. With c = sign(y)
+// step (t, j) w(t, j) the variants with weights also give
+//   FC_COLSUM: colsum[k-1][rt][j] = sum over 32 rows (row tile rt) of up_k c (w = w1), fp32
+//   FC_BLOCKSUM: partial[k-1][i][b] = sum over block b's elements of up_k c_i (w1, w2), fp64
+// Bound by the Philox rounds (8.5 VALU per word beside the shared first rounds) and the decision.
+//
+// The trials of one element are independent, so a tensor with too few elements to fill the chip
+// splits its trials over the TS waves of a block (wave p takes trials p, p + TS, ...); the counts
+// of the parts meet in LDS (integers: any order gives the same sum). At 256 x 64 with 64 trials the
+// counts take 4.9 us (56 with every trial in one wave) and the column sums 20 us (64); at 1111 x
+// 520 with 24 trials 9.6 (27) and 19 us (32).
+
+// Counts alone: the tensor as flat groups of 4 elements (one Philox call each); block of NT
+// threads, G groups per thread. A block's groups are an aligned power-of-two range, so the high
+// counter word is uniform (scalar). 16384 x 8192 x 64 trials: 2.80 ms, 3.07 T element-trials/s
+// (2.91 ms with rows and columns per thread and a vector high word).
+template <typename X, int G, int TS>
+__global__ __launch_bounds__(TS > 4 ? 64 * TS : 256) void fresh_count_kernel(FreshArgs<X> a) {
+  constexpr int NT = TS > 4 ? 64 * TS : 256, LN = NT / TS, TB = 4;  // LN lanes (x G groups) per block
+  const int tid = threadIdx.x;
+  const int part = TS > 1 ? __builtin_amdgcn_readfirstlane(tid / LN) : 0, ln = TS > 1 ? tid % LN : tid;
+  const uint64_t ngroups = (uint64_t)(a.T * a.d) >> 2, base = (uint64_t)blockIdx.x * (LN * G);
+  const uint32_t g_hi = (uint32_t)(base >> 32);
+  const double rs = 1.0 / (double)*a.scale;
+  uint32_t F[G][4], cnt[G][4];
+#pragma unroll
+  for (int r = 0; r < G; ++r) {
+    const uint64_t g = base + r * LN + ln;
+    const bool ok = g < ngroups;
+    float xv[4] = {0.f, 0.f, 0.f, 0.f};
+    if (ok) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) xv[q] = load_f32(a.x, 4 * g + q);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const Bracket b = f8_bracket(fminf(fabsf(div_scale(xv[q], rs)), a.f.fmax), a.f);
+      F[r][q] = b.F;  // 0 past the end
+      cnt[r][q] = 0;
+      asm volatile("" : "+v"(F[r][q]));  // opaque: keeps the validity test out of the trial loop
+    }
+  }
+  for (int k0 = part; k0 < a.K; k0 += TB * TS) {
+#pragma unroll
+    for (int i = 0; i < TB; ++i) {
+      const int k = k0 + i * TS;
+      if (k >= a.K) break;
+#pragma unroll
+      for (int r = 0; r < G; ++r) {
+        const Philox4 p = philox4x32_10((uint32_t)base + r * LN + ln, g_hi, (uint32_t)(k + a.trial0), a.use,
+                                        (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) cnt[r][q] += sr_up(F[r][q], philox_word(p, q));
+      }
+    }
+  }
+  uint2 out[G];
+#pragma unroll
+  for (int r = 0; r < G; ++r) out[r] = make_uint2(cnt[r][0] | (cnt[r][1] << 16), cnt[r][2] | (cnt[r][3] << 16));
+  if constexpr (TS > 1) {  // K <= 4096: the packed 16-bit sums do not carry into each other
+    __shared__ uint32_t red[2][LN * G];
+    for (int i = tid; i < 2 * LN * G; i += NT) (&red[0][0])[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < G; ++r) {
+      atomicAdd(&red[0][r * LN + ln], out[r].x);
+      atomicAdd(&red[1][r * LN + ln], out[r].y);
+    }
+    __syncthreads();
+    if (part != 0) return;
+#pragma unroll
+    for (int r = 0; r < G; ++r) out[r] = make_uint2(red[0][r * LN + ln], red[1][r * LN + ln]);
+  }
+#pragma unroll
+  for (int r = 0; r < G; ++r) {
+    const uint64_t g = base + r * LN + ln;
+    if (g < ngroups) *(uint2*)(a.counts + 4 * g) = out[r];
+  }
+}
+
+// With weights. Block: 256 threads = 64 column groups (4 columns each) x 4 row lanes, 8 rows per
+// thread, so one block covers 32 rows x 256 columns. The row lane is the wave, except for
+// FC_COLSUM, where a wave holds 16 column groups x 4 row lanes so that the column sums reduce
+// inside the wave (cross-lane adds in a fixed order, no barrier) and, with TS > 1 trial parts, the
+// block's TS waves share the 16 column groups (64 columns).
 // FC_BLOCKSUM reduces through LDS four trials at a time, in a fixed order. The column sums feed only a
 // sample variance over trials: they hold no trial-independent term (an element whose
 // rounding never goes up adds nothing), so fp32 rounding of a 32-row sum perturbs each trial
 // by a few ulps of values of the size of the trial-to-trial spread, far below the 1e-5 of the
 // statistic, and the sums over row blocks are taken in fp64.
-template <typename X, int MODE>
-__device__ __forceinline__ void fresh_count_body(const FreshArgs<X>& a) {
+// With B = 32 (16): lanes with lane bit B clear return a(l) + a(l + B), the others b(l - B) + b(l).
+template <int B>
+__device__ __forceinline__ float swap_add(float a, float b) {
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  const uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
+  // the halves (odd 16-lane rows) of x trade places with the other halves (even rows) of y
+  const u32x2 r = B == 32 ? __builtin_amdgcn_permlane32_swap(x, y, false, false)
+                          : __builtin_amdgcn_permlane16_swap(x, y, false, false);
+  return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+
+template <typename X, int MODE, int TS>
+__device__ __forceinline__ void fresh_weighted_body(const FreshArgs<X>& a) {
+  static_assert(TS == 1 || MODE == FC_COLSUM, "trial parts: the column sums only");
   constexpr int RT = 32, RPT = 8, TB = MODE == FC_COLSUM ? 1 : 4;
-  const int lane = threadIdx.x & 63;
-  const int tx = MODE == FC_COLSUM ? (threadIdx.x >> 6) * 16 + (lane & 15) : lane;
-  const int ty = MODE == FC_COLSUM ? lane >> 4 : threadIdx.x >> 6;
-  const int64_t j0 = (int64_t)blockIdx.x * 256 + 4 * tx;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int part = TS > 1 ? wave : 0;
+  const int tx = MODE == FC_COLSUM ? (TS > 1 ? 0 : wave * 16) + (lane & 15) : lane;
+  const int ty = MODE == FC_COLSUM ? lane >> 4 : wave;
+  const int64_t j0 = (int64_t)blockIdx.x * (TS > 1 ? 64 : 256) + 4 * tx;
   const int64_t t0 = (int64_t)blockIdx.y * RT;
   const bool colok = j0 < a.d;
   const double rs = 1.0 / (double)*a.scale;
@@ -254,10 +345,8 @@ __device__ __forceinline__ void fresh_count_body(const FreshArgs<X>& a) {
       const int64_t e = t * a.d + j0;
 #pragma unroll
       for (int q = 0; q < 4; ++q) xv[q] = load_f32(a.x, e + q);
-      if (MODE != FC_COUNT) {
-        const float4 v = *(const float4*)(a.w1 + e);
-        w1v[0] = v.x; w1v[1] = v.y; w1v[2] = v.z; w1v[3] = v.w;
-      }
+      const float4 v = *(const float4*)(a.w1 + e);
+      w1v[0] = v.x; w1v[1] = v.y; w1v[2] = v.z; w1v[3] = v.w;
       if (MODE == FC_BLOCKSUM && a.w2) {
         const float4 v = *(const float4*)(a.w2 + e);
         w2v[0] = v.x; w2v[1] = v.y; w2v[2] = v.z; w2v[3] = v.w;
@@ -280,7 +369,7 @@ __device__ __forceinline__ void fresh_count_body(const FreshArgs<X>& a) {
   __shared__ double red[MODE == FC_BLOCKSUM ? TB : 1][2 * 4];
   const int64_t nrt = gridDim.y;
   const int64_t nblk = (int64_t)gridDim.x * gridDim.y, bid = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-  for (int k0 = 1; k0 <= a.K; k0 += TB) {
+  for (int k0 = 1 + part; k0 <= a.K; k0 += TB * TS) {
     Acc acc[TB][4];
 #pragma unroll
     for (int i = 0; i < TB; ++i)
@@ -288,7 +377,7 @@ __device__ __forceinline__ void fresh_count_body(const FreshArgs<X>& a) {
       for (int q = 0; q < 4; ++q) acc[i][q] = 0;
 #pragma unroll
     for (int i = 0; i < TB; ++i) {
-      const int k = k0 + i;
+      const int k = k0 + i * TS;
       if (k > a.K) break;
 #pragma unroll
       for (int r = 0; r < RPT; ++r) {
@@ -300,7 +389,12 @@ __device__ __forceinline__ void fresh_count_body(const FreshArgs<X>& a) {
         for (int q = 0; q < 4; ++q) {
           const uint32_t up = sr_up(F[r][q], R[q]);
           cnt[r][q] += up;
-          if (MODE == FC_COLSUM) acc[i][q] += up ? c1[r][q] : 0.0f;
+          if (MODE == FC_COLSUM) {
+            acc[i][q] += up ? c1[r][q] : 0.0f;
+            // opaque: the count stays beside its carry (one add with carry; sunk to the loop's end it
+            // becomes a select and an add on a saved mask)
+            asm volatile("" : "+v"(cnt[r][q]));
+          }
           if (MODE == FC_BLOCKSUM) {
             acc[i][0] += up ? (double)c1[r][q] : 0.0;
             acc[i][1] += up ? (double)c2[r][q] : 0.0;
@@ -310,21 +404,11 @@ __device__ __forceinline__ void fresh_count_body(const FreshArgs<X>& a) {
         if (MODE == FC_COLSUM && (r & 3) == 3) __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (MODE == FC_COLSUM) {
-      // sum over the 4 row lanes (lane bits 4 and 5): (l + l^16) + (l^32 + l^48)
-#pragma unroll
-      for (int i = 0; i < TB; ++i) {
-        float v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          v[q] = (float)acc[i][q];
-          v[q] += __shfl_xor(v[q], 16, 64);
-          v[q] += __shfl_xor(v[q], 32, 64);
-        }
-        const int k = k0 + i;
-        if (ty == 0 && colok && k <= a.K)
-          *(float4*)(a.colsum + ((int64_t)(k - 1) * nrt + blockIdx.y) * a.d + j0) = make_float4(v[0], v[1], v[2], v[3]);
-      }
+    if constexpr (MODE == FC_COLSUM) {
+      // Sum over the 4 row lanes (lane bits 4 and 5), (l + l^32) + (l^16 + l^48): each exchange hands
+      // half of a lane's columns over, so row lane ty ends with column ty of its group.
+      const float v = swap_add<16>(swap_add<32>(acc[0][0], acc[0][2]), swap_add<32>(acc[0][1], acc[0][3]));
+      if (colok) a.colsum[((int64_t)(k0 - 1) * nrt + blockIdx.y) * a.d + j0 + ty] = v;
     }
     if (MODE == FC_BLOCKSUM) {
       const int wv = threadIdx.x >> 6;
@@ -348,13 +432,29 @@ __device__ __forceinline__ void fresh_count_body(const FreshArgs<X>& a) {
     }
   }
   if (a.counts) {
+    constexpr int LG = TS > 1 ? 64 * RPT : 1;
+    __shared__ uint32_t cred[2][LG];
+    if constexpr (TS > 1) {
+      for (int i = threadIdx.x; i < 2 * LG; i += 64 * TS) (&cred[0][0])[i] = 0;
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < RPT; ++r) {
+        atomicAdd(&cred[0][r * 64 + lane], cnt[r][0] | (cnt[r][1] << 16));
+        atomicAdd(&cred[1][r * 64 + lane], cnt[r][2] | (cnt[r][3] << 16));
+      }
+      __syncthreads();
+      if (part != 0) return;
+    }
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
       const int64_t t = t0 + ty + 4 * r;
       if (colok && t < a.T) {
-        const uint32_t lo = cnt[r][0] | (cnt[r][1] << 16);
-        const uint32_t hi = cnt[r][2] | (cnt[r][3] << 16);
-        *(uint2*)(a.counts + t * a.d + j0) = make_uint2(lo, hi);
+        uint2 v;
+        if constexpr (TS > 1)
+          v = make_uint2(cred[0][r * 64 + lane], cred[1][r * 64 + lane]);
+        else
+          v = make_uint2(cnt[r][0] | (cnt[r][1] << 16), cnt[r][2] | (cnt[r][3] << 16));
+        *(uint2*)(a.counts + t * a.d + j0) = v;
       }
     }
   }
@@ -362,13 +462,13 @@ __device__ __forceinline__ void fresh_count_body(const FreshArgs<X>& a) {
 
 // The column-sum variant holds the per-element weights too; it is held to 168 registers so that
 // three waves share each SIMD (the Philox latency needs them).
-template <typename X, int MODE>
-__global__ __launch_bounds__(256) void fresh_count_kernel(FreshArgs<X> a) {
-  fresh_count_body<X, MODE>(a);
-}
 template <typename X>
-__global__ __launch_bounds__(256) void fresh_colsum_kernel(FreshArgs<X> a) {
-  fresh_count_body<X, FC_COLSUM>(a);
+__global__ __launch_bounds__(256) void fresh_blocksum_kernel(FreshArgs<X> a) {
+  fresh_weighted_body<X, FC_BLOCKSUM, 1>(a);
+}
+template <typename X, int TS>
+__global__ __launch_bounds__(TS > 4 ? 64 * TS : 256) void fresh_colsum_kernel(FreshArgs<X> a) {
+  fresh_weighted_body<X, FC_COLSUM, TS>(a);
 }
 
 // ------------------------------------------------------------------------------------
@@ -420,17 +520,47 @@ bs_status launch_store(const void* x, bs_dtype xt, int64_t n, int fmt, int mode,
   return BS_OK;
 }
 
+template <typename X, int G, int TS>
+static bs_status launch_fresh_flat(const FreshArgs<X>& a, hipStream_t st) {
+  constexpr int NT = TS > 4 ? 64 * TS : 256;
+  const int64_t per = (int64_t)NT / TS * G, blocks = ((a.T * a.d) / 4 + per - 1) / per;
+  if (blocks > 0x7FFFFFFF) return BS_ESHAPE;
+  fresh_count_kernel<X, G, TS><<<(unsigned)blocks, NT, 0, st>>>(a);
+  return BS_OK;
+}
+
 template <typename X>
 bs_status launch_fresh_count_t(const FreshArgs<X>& a, int mode, hipStream_t st) {
   if (a.T == 0) return BS_OK;
-  dim3 grid((unsigned)((a.d + 255) / 256), (unsigned)((a.T + 31) / 32));
   ProfScope prof(mode == FC_COUNT ? "fresh_count" : (mode == FC_COLSUM ? "fresh_count_se" : "fresh_count_kappa"), st);
-  if (mode == FC_COUNT)
-    fresh_count_kernel<X, FC_COUNT><<<grid, 256, 0, st>>>(a);
-  else if (mode == FC_COLSUM)
-    fresh_colsum_kernel<X><<<grid, 256, 0, st>>>(a);
-  else
-    fresh_count_kernel<X, FC_BLOCKSUM><<<grid, 256, 0, st>>>(a);
+  bs_status rc = BS_OK;
+  if (mode == FC_COUNT) {
+    // waves of the chip's 1024 SIMDs: 8 groups per thread (the set-up paid once for all of them)
+    // while that gives two waves each; fewer groups per thread, then 4 and 16 trial parts, below
+    const int64_t waves = (a.T * a.d) / 4 / 64;  // of one group per thread
+    if (waves >= 8 * 2048)
+      rc = launch_fresh_flat<X, 8, 1>(a, st);
+    else if (waves >= 2 * 2048 || a.K < 4)
+      rc = launch_fresh_flat<X, 2, 1>(a, st);
+    else if (waves >= 512 || a.K < 16)
+      rc = launch_fresh_flat<X, 2, 4>(a, st);
+    else
+      rc = launch_fresh_flat<X, 1, 16>(a, st);
+  } else if (mode == FC_COLSUM) {
+    // 64-column blocks with 4 or 8 trial parts where 256-column blocks leave SIMDs idle
+    const unsigned rt = (unsigned)((a.T + 31) / 32);
+    const int64_t waves = ((a.d + 63) / 64) * rt;
+    const dim3 g64((unsigned)((a.d + 63) / 64), rt);
+    if (waves >= 1024 || a.K < 4)
+      fresh_colsum_kernel<X, 1><<<dim3((unsigned)((a.d + 255) / 256), rt), 256, 0, st>>>(a);
+    else if (waves >= 256 || a.K < 8)
+      fresh_colsum_kernel<X, 4><<<g64, 256, 0, st>>>(a);
+    else
+      fresh_colsum_kernel<X, 8><<<g64, 512, 0, st>>>(a);
+  } else {
+    fresh_blocksum_kernel<X><<<dim3((unsigned)((a.d + 255) / 256), (unsigned)((a.T + 31) / 32)), 256, 0, st>>>(a);
+  }
+  if (rc != BS_OK) return rc;
   BS_CHECK_LAUNCH();
   return BS_OK;
 }

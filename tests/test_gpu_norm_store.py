@@ -72,6 +72,26 @@ def test_ragged_all_policies(lib, dtype, fwd_mode):
     compare(out, ref, ALL, d=d, n=n)
 
 
+@pytest.mark.parametrize("T,d,K", [
+    (33, 72, 3),       # fewer trials than parts
+    (70, 64, 20),      # 16 trial parts (counts), 8 (column sums), uneven
+    (600, 264, 17),    # 4 parts (counts), a ragged last 64-column block
+    (1100, 1024, 5),   # one part (counts), 4 (column sums), uneven
+    (4200, 1024, 5),   # 8 groups per thread, 256-column blocks
+])
+def test_trial_parts_of_the_new_rounding_counters(lib, T, d, K):
+    """Every split of the trials over a block's waves: counts through the N biases, column sums
+    through the gain use's se (sampled outputs)."""
+    n, pols = 64, ("N/N", "U/N")
+    rng = np.random.default_rng(T)
+    rows = np.sort(rng.choice(d, 6, replace=False))
+    cols = np.sort(rng.choice(d, 8, replace=False))
+    xrows = np.sort(rng.choice(T, 5, replace=False))
+    out, ref = run_both(lib, T, d, n, torch.bfloat16, K, pols, seed=60 + K,
+                        oracle_kw=dict(dw_rows=rows, gain_cols=cols, dx_rows=xrows))
+    compare(out, ref, pols, rows=rows, cols=cols, xrows=xrows, d=d, n=n)
+
+
 def test_shared_new_rounding_and_norm_input_R(lib):
     T, d, n = 130, 64, 72
     pols = ("N/N", "U/N", "R/R")
