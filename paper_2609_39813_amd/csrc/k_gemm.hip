@@ -6,7 +6,7 @@
 // are summed in one pass: that is how fp32-valued operands enter as a sum of exact bf16
 // terms. Products of bf16 values are exact in the fp32 accumulator.
 //
-// Two kernels. The pipelined kernel (K a multiple of 64) moves operand tiles straight from
+// Three kernels. The pipelined kernel moves operand tiles straight from
 // global memory into LDS (buffer_load_dwordx4 ... lds, no register staging) in 64-deep
 // chunks, so that every operand row of a chunk is one full 128-byte line; two LDS stages
 // (128 KB for a 256 x 256 tile) hold the chunk being computed and the next one. A 256 x 256
@@ -19,15 +19,18 @@
 // of the next k-step and the global loads of the chunk after next are spread between the
 // MFMAs, one barrier per chunk. Shapes with fewer tiles than CUs split K over blocks into
 // fp32 partials that one more kernel sums in a fixed order (the result does not depend on
-// timing). The register-staged kernel below serves the other shapes.
+// timing). The small-output kernel (32 x 32 tiles, K split over a block's waves) serves outputs that
+// even 128 x 128 tiles leave on a few CUs; plan_gemm chooses. The register-staged kernel below
+// serves operands that are not 16-byte aligned or whose rows are too long for buffer offsets.
 //
-// Register-staged kernel: tile 128 x 128 x 64 or 256 x 256 x 64, 256 threads (4 wave64s in
+// Register-staged kernel: tile 128 x 128 x 64, 256 threads (4 wave64s in
 // 2 x 2), double-buffered LDS with a 16-byte row pad (row stride 144 B keeps the 16 rows read
 // by one ds_read_b128 on distinct banks).
 //
-// Both renumber workgroups so that the tiles of one XCD are contiguous in row-major tile order
+// All renumber workgroups so that the tiles of one XCD are contiguous in row-major tile order
 // (shared A panels in that XCD's L2).
 #include <algorithm>
+#include <cmath>
 
 #include "bsp_kernels.h"
 
@@ -173,7 +176,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds_kernel(GemmArgs g, in
   const int group = tile / (GM * tiles_n), in_group = tile - group * GM * tiles_n;
   const int first_m = group * GM, gsz = min(tiles_m - first_m, GM);
   const int bm = (first_m + in_group % gsz) * BM, bn = (in_group / gsz) * BN;
-  const int nch = g.K / LBK, total = nch * g.nseg;
+  const int nch = (g.K + LBK - 1) / LBK, total = nch * g.nseg;
   const int c0 = split * cps;
   const int n = min(total, c0 + cps) - c0;
 
@@ -197,26 +200,37 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds_kernel(GemmArgs g, in
   int iss_seg = c0 / nch, iss_k = (c0 - iss_seg * nch) * LBK;
   __amdgpu_buffer_rsrc_t ra = rsrc(g.A[iss_seg] + oA, bm, rows_a, g.lda);
   __amdgpu_buffer_rsrc_t rb = rsrc(g.B[iss_seg] + oB, bn, rows_b, g.ldb);
+  // A segment's last chunk may be ragged (K any multiple of 8): lanes whose unit lies past K take
+  // an offset past every resource (< 2^31 bytes) and read zero.
+  const int unit_k = ((lane & 7) ^ swz_of(lane >> 3)) << 3;
+  uint32_t va = 0, vb = 0;
+  auto place = [&]() {
+    const bool in = iss_k + unit_k < g.K;
+    va = in ? lane_a : 0x7FFFFFF0u;
+    vb = in ? lane_b : 0x7FFFFFF0u;
+  };
+  place();
   auto issue_one = [&](int st, int i) {
     char* base = smem + st * STAGE;
     if (i < AI)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (void __attribute__((address_space(3)))*)(base + (wave * AI + i) * 1024),
-                                               16, lane_a, (uint32_t)iss_k * 2 + i * step_a, 0, 0);
+                                               16, va, (uint32_t)iss_k * 2 + i * step_a, 0, 0);
     else
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          rb, (void __attribute__((address_space(3)))*)(base + BM * 128 + (wave * BI + i - AI) * 1024), 16, lane_b,
+          rb, (void __attribute__((address_space(3)))*)(base + BM * 128 + (wave * BI + i - AI) * 1024), 16, vb,
           (uint32_t)iss_k * 2 + (i - AI) * step_b, 0, 0);
   };
   // Kept out of the MFMA regions: the rare segment switch is a branch with scalar loads.
   auto advance = [&]() {
     iss_k += LBK;
-    if (iss_k == g.K) {
+    if (iss_k >= g.K) {
       iss_k = 0;
       if (++iss_seg < g.nseg) {
         ra = rsrc(g.A[iss_seg] + oA, bm, rows_a, g.lda);
         rb = rsrc(g.B[iss_seg] + oB, bn, rows_b, g.ldb);
       }
     }
+    place();
   };
 
   floatx4 acc[FM][FN];
@@ -358,29 +372,10 @@ __global__ __launch_bounds__(256) void gemm_split_sum_kernel(GemmArgs g, int spl
 }
 
 template <int BM, int BN, int WGM, int WGN, bool F16>
-static bs_status launch_gemm_lds(const GemmArgs& g0, hipStream_t st) {
+static bs_status launch_gemm_lds(const GemmArgs& g0, int splits, hipStream_t st) {
   GemmArgs g = g0;
   const int64_t tiles = (int64_t)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
-  const int total = (g.K / LBK) * g.nseg;
-  // split K while the tiles leave CUs idle, keeping at least 16 chunks (1024 of K) per block. One
-  // block fits a CU (its LDS), so blocks beyond the 256 CUs run in a second round: the split count
-  // minimizes the makespan ceil(tiles * splits / 256) / splits (e.g. 48 tiles: 5 splits in one round
-  // of 240 blocks, not 6 in two rounds of 288)
-  int splits = 1;
-  if (g.batch > 1) g.part = nullptr;  // batch members fill the CUs
-  if (g.part && tiles < 256) {
-    const int64_t by_k = total / 16;
-    const int64_t by_ws = g.part_cap / ((int64_t)g.M * g.N);
-    const int64_t top = std::max<int64_t>(1, std::min((256 + tiles - 1) / tiles, std::min(by_k, by_ws)));
-    double best = 2.0;
-    for (int64_t sp = 1; sp <= top; ++sp) {
-      const double span = (double)((tiles * sp + 255) / 256) / (double)sp;
-      if (span < best - 1e-12) {
-        best = span;
-        splits = (int)sp;
-      }
-    }
-  }
+  const int total = (g.K + LBK - 1) / LBK * g.nseg;
   const int cps = (total + splits - 1) / splits;
   splits = (total + cps - 1) / cps;
   if (splits == 1) g.part = nullptr;
@@ -411,6 +406,170 @@ static bs_status launch_gemm_cfg(const GemmArgs& g, hipStream_t st) {
   return BS_OK;
 }
 
+// ------------------------------------------------------------------------------------
+// small-output kernel
+// ------------------------------------------------------------------------------------
+// A block computes one (16 FM) x (16 FN) tile; its NW waves split the 64-deep k steps of all the
+// segments (wave w takes steps w, w + NW, ...), read their fragments straight from global memory
+// (a lane's eight k values are 16 contiguous bytes; no LDS staging, no barrier in the loop, the
+// next step's loads in flight during a step's MFMAs) and meet once in LDS, where the partial tiles
+// are added in wave order. Outputs too small to fill the chip with staged tiles are bound by the
+// serial chain of a tile's k steps: this takes the chain apart inside the block, without
+// partials in global memory and without a second launch. K any multiple of 8 (the tail reads zero).
+template <int FM, int FN, int NW, bool F16>
+__global__ __launch_bounds__(64 * NW) void gemm_wave_kernel(GemmArgs g) {
+  constexpr int NF = FM * FN;
+  __shared__ floatx4 red[NW][NF][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tiles_n = (g.N + 16 * FN - 1) / (16 * FN), ntile = (g.M + 16 * FM - 1) / (16 * FM) * tiles_n;
+  const int nblk = gridDim.x;
+  int bid = blockIdx.x;
+  if ((nblk & 7) == 0) bid = (bid & 7) * (nblk >> 3) + (bid >> 3);  // XCD-contiguous tiles
+  const int zb = bid / ntile, tile = bid - zb * ntile;
+  const int bm = tile / tiles_n * (16 * FM), bn = tile % tiles_n * (16 * FN);
+  const int ks = (g.K + 63) / 64, total = ks * g.nseg;
+  const int fr = lane & 15, fk = (lane >> 4) * 8;
+  // rows past the edge read the last row (their products are not stored)
+  int64_t ra[FM], rb[FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i) ra[i] = (int64_t)zb * g.sA + (int64_t)min(bm + i * 16 + fr, g.M - 1) * g.lda;
+#pragma unroll
+  for (int j = 0; j < FN; ++j) rb[j] = (int64_t)zb * g.sB + (int64_t)min(bn + j * 16 + fr, g.N - 1) * g.ldb;
+
+  floatx4 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 fa[2][2][FM], fb[2][2][FN];  // [stage][32-deep half][fragment]
+  auto load = [&](int st, int s) {
+    const int seg = s / ks;
+    const u16 *A = g.A[seg], *B = g.B[seg];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = (s - seg * ks) * 64 + 32 * h + fk;
+      const bool ok = k < g.K;
+#pragma unroll
+      for (int i = 0; i < FM; ++i) fa[st][h][i] = ok ? *(const bf16x8*)(A + ra[i] + k) : bf16x8{};
+#pragma unroll
+      for (int j = 0; j < FN; ++j) fb[st][h][j] = ok ? *(const bf16x8*)(B + rb[j] + k) : bf16x8{};
+    }
+  };
+  auto mma = [&](int st) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          if constexpr (F16)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(halfx8, fa[st][h][i]),
+                                                               __builtin_bit_cast(halfx8, fb[st][h][j]), acc[i][j], 0, 0, 0);
+          else
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[st][h][i], fb[st][h][j], acc[i][j], 0, 0, 0);
+        }
+  };
+  if (wave < total) load(0, wave);
+  for (int s = wave; s < total; s += 2 * NW) {
+    if (s + NW < total) load(1, s + NW);
+    mma(0);
+    if (s + NW < total) {
+      if (s + 2 * NW < total) load(0, s + 2 * NW);
+      mma(1);
+    }
+  }
+  if (wave < total) {
+#pragma unroll
+    for (int f = 0; f < NF; ++f) red[wave][f][lane] = acc[f / FN][f % FN];
+  }
+  __syncthreads();
+  // wave w finishes fragments w, w + NW, ...; D[i][j] of a 16 x 16 tile sits in lane
+  // (j + 16 (i / 4)), register i % 4
+  const int np = min(NW, total);
+  const int oc = lane & 15, orow = (lane >> 4) * 4;
+  const float alpha = gemm_alpha(g, zb);
+  float* out = g.C + (int64_t)zb * g.sC;
+  float mx = 0.0f;
+#pragma unroll
+  for (int f0 = 0; f0 < NF; f0 += NW) {
+    const int f = f0 + wave;
+    if (f >= NF) break;
+    floatx4 v = red[0][f][lane];
+    for (int w = 1; w < np; ++w) v += red[w][f][lane];
+    const int n = bn + f % FN * 16 + oc;
+    if (n >= g.N) continue;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = bm + f / FN * 16 + orow + r;
+      if (m < g.M) {
+        float* p = out + (int64_t)m * g.ldc + n;
+        const float o = alpha * v[r];
+        *p = g.accumulate ? *p + o : o;
+        mx = fmaxf(mx, fabsf(o));
+      }
+    }
+  }
+  if (g.amax) wave_amax_to_slot(mx, g.amax);
+}
+
+template <int FM, int FN, int NW, bool F16>
+static bs_status launch_gemm_wave(const GemmArgs& g, hipStream_t st) {
+  const int64_t blocks = (int64_t)((g.M + 16 * FM - 1) / (16 * FM)) * ((g.N + 16 * FN - 1) / (16 * FN)) * g.batch;
+  if (blocks > 0x7FFFFFFF) return BS_ESHAPE;
+  ProfScope prof("gemm", st, gemm_flops(g), gemm_exec_flops(g));
+  gemm_wave_kernel<FM, FN, NW, F16><<<(unsigned)blocks, 64 * NW, 0, st>>>(g);
+  BS_CHECK_LAUNCH();
+  return BS_OK;
+}
+
+// Which kernel, and how many splits of K: the least estimated time of the pipelined kernel's 256 x 256
+// and 128 x 128 tiles (one and two blocks per CU) and the small-output kernel's 32 x 32 tiles.
+// The times (us) are fitted to launches of 44 shapes from 64 x 64 x 64 to 16384 x 1024 x 4096: a
+// fixed part, and per 64-deep chunk of a block a part that grows as more blocks load and multiply at
+// once (n chunks per block, f the launch's share of the blocks the CUs hold, r rounds of them):
+//   256 x 256   13 + n (0.95 + 0.6 f) r     4096^2 x 1024: 38 measured, 38 estimated
+//   128 x 128   6.5 + n (0.42 + 0.6 f) r    2048 x 4096 x 1024: 24 and 23; 640^2 x 2816: 25 and 26
+//   32 x 32     2.4 + 1.9 n/8 r             512^2 x 1536: 8.7 and 8.1 (its 8 waves share the chunks)
+//   split sum   4 + s M N 1e-6 (the partials out and in, and the launch)
+// (By output size alone, 256 x 256 from M N = 2^20, these took 33.3, 19.3 with 128 x 128, at 4160 x
+// 776 x 1152; 28.6, now 14.4, at 4096 x 512 x 1024; 16.3, now 8.7, at 512^2 x 1536.)
+struct GemmPlan {
+  int kind = 0;  // 0: 256 x 256, 1: 128 x 128, 2: 32 x 32
+  int splits = 1;
+};
+static GemmPlan plan_gemm(const GemmArgs& g) {
+  const double mn = (double)g.M * g.N;
+  const int total = (int)std::min<int64_t>((int64_t)((g.K + LBK - 1) / LBK) * g.nseg, 1 << 30);
+  const int top = g.part && g.batch == 1 ? (int)std::min<int64_t>(16, std::min<int64_t>(total / 2, g.part_cap / ((int64_t)g.M * g.N))) : 1;
+  GemmPlan best;
+  double tb = 1e300;
+  for (int kind = 0; kind < 3; ++kind) {
+    const int bt = kind == 0 ? 256 : (kind == 1 ? 128 : 32), cap = kind == 0 ? 256 : (kind == 1 ? 512 : 256);
+    const double tiles = (double)((g.M + bt - 1) / bt) * ((g.N + bt - 1) / bt) * g.batch;
+    for (int s = 1; s <= (kind == 2 ? 1 : std::max(1, top)); ++s) {
+      const double blocks = tiles * s, f = std::min(1.0, blocks / cap);
+      // whole rounds where a block fills its CU; the smaller blocks' rounds overlap
+      const double r = kind == 0 ? std::ceil(blocks / cap) : std::max(1.0, blocks / cap);
+      double t;
+      if (kind == 2)
+        t = 2.4 + 1.9 * ((total + 7) / 8) * r;
+      else
+        t = (kind == 0 ? 13.0 : 6.5) + (double)((total + s - 1) / s) * ((kind == 0 ? 0.95 : 0.42) + 0.6 * f) * r;
+      if (s > 1) t += 4.0 + s * mn * 1e-6;
+      if (t < tb) tb = t, best.kind = kind, best.splits = s;
+    }
+  }
+  return best;
+}
+
+template <bool F16>
+static bs_status launch_gemm_planned(const GemmArgs& g, hipStream_t st) {
+  const GemmPlan p = plan_gemm(g);
+  if (p.kind == 2) return launch_gemm_wave<2, 2, 8, F16>(g, st);
+  return p.kind == 0 ? launch_gemm_lds<256, 256, 2, 4, F16>(g, p.splits, st)
+                     : launch_gemm_lds<128, 128, 2, 2, F16>(g, p.splits, st);
+}
+
 bs_status launch_gemm(const GemmArgs& g, hipStream_t st) {
   if (g.M <= 0 || g.N <= 0) return BS_OK;
   if (g.nseg < 1 || g.nseg > GEMM_MAX_SEG) return BS_EINVAL;
@@ -418,19 +577,11 @@ bs_status launch_gemm(const GemmArgs& g, hipStream_t st) {
   if (g.amax && g.accumulate) return BS_EINVAL;
   if (g.batch < 1 || (g.batch > 1 && (g.sA < 0 || g.sB < 0 || g.sC < 0 || g.s_alpha2 < 0))) return BS_EINVAL;
   if (g.K == 0) return g.accumulate ? BS_OK : launch_fill2d(g.C, g.M, g.N, g.ldc, 0.0f, st);
-  // pipelined kernel for 64-aligned K and 16-byte aligned operands
-  // (buffer offsets of one 256-row tile fit in 31 bits)
-  bool lds_ok = (g.K % LBK) == 0 && g.M >= 1 && g.N >= 1 && g.lda < (1 << 21) && g.ldb < (1 << 21);
+  // buffer offsets of one 256-row tile fit in 31 bits
+  bool lds_ok = g.lda < (1 << 21) && g.ldb < (1 << 21);
   for (int i = 0; i < g.nseg; ++i) lds_ok = lds_ok && ((uintptr_t)g.A[i] & 15) == 0 && ((uintptr_t)g.B[i] & 15) == 0;
-  const bool big_tiles = (int64_t)g.M * g.N >= (int64_t)256 * 256 * 16;
-  if (lds_ok && g.f16)
-    return big_tiles ? launch_gemm_lds<256, 256, 2, 4, true>(g, st) : launch_gemm_lds<128, 128, 2, 2, true>(g, st);
-  if (g.f16 || g.amax || g.batch > 1) return BS_EINVAL;  // fp16 operands, maxima, batches: the pipelined kernel only
-  if (lds_ok)
-    return big_tiles ? launch_gemm_lds<256, 256, 2, 4, false>(g, st) : launch_gemm_lds<128, 128, 2, 2, false>(g, st);
-  // 256 x 256 tiles once they still give every CU a tile; 128 x 128 below that
-  const int64_t big = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256);
-  if (big >= 256) return launch_gemm_cfg<256, 256, 2, 2>(g, st);
+  if (lds_ok) return g.f16 ? launch_gemm_planned<true>(g, st) : launch_gemm_planned<false>(g, st);
+  if (g.f16 || g.amax || g.batch > 1) return BS_EINVAL;  // fp16 operands, maxima, batches: aligned operands only
   return launch_gemm_cfg<128, 128, 2, 2>(g, st);
 }
 
