@@ -1,4 +1,6 @@
 // C-ABI entry point of the Linear backward whose incoming gradient is rounded to FP8.
+#include <algorithm>
+
 #include "bsp_kernels.h"
 #include "k_combine.h"
 #include "k_linear.h"
@@ -14,13 +16,16 @@ using namespace bsp;
 
 namespace {
 struct LinWs {
-  u16 *xT, *dyT, *e1r[3], *e1c[3], *e2c[3], *wT[3], *pa[3], *pbT[3], *tc[3];
+  u16 *xT, *dyT, *e1r[2], *e1c[2], *e2c[2], *x16T, *w16, *wT[3], *pa[3], *pbT[3], *tc[2];
   float *tdx, *tdw, *d1x, *d1w[2];
   double *S1x, *S2x, *S1w[2], *S2w[2];
   u16 *cnt1, *cnt2;
   float *AW, *XB, *bx[2], *bw[2];
   double *part1, *part2, *fixpart, *fixed;
-  float* scale_tmp;
+  uint32_t* am[2];  // maxima of X and W (slot arrays)
+  float* inv;       // multipliers 2^-e: X, W, the residuals
+  float* gpart;     // split-K partials of the contractions
+  int64_t gpart_cap;
 };
 LinWs carve_lin(Carver& c, int64_t M, int64_t k, int64_t n, bool any_shared, bool any_per_use, bool coupling,
                 bool want_se) {
@@ -28,13 +33,20 @@ LinWs carve_lin(Carver& c, int64_t M, int64_t k, int64_t n, bool any_shared, boo
   const int64_t Mp = round_up(M > 0 ? M : 1, 64);
   w.xT = c.take<u16>(k * Mp);
   w.dyT = c.take<u16>(n * Mp);
-  for (int i = 0; i < 3; ++i) w.e1r[i] = c.take<u16>(M * n);
+  w.x16T = c.take<u16>(k * Mp);
+  w.w16 = c.take<u16>(k * n);
+  uint32_t* a = c.take<uint32_t>(2 * AMAX_SLOTS * AMAX_STRIDE);
+  for (int i = 0; i < 2; ++i) w.am[i] = a ? a + i * AMAX_SLOTS * AMAX_STRIDE : nullptr;
+  w.inv = c.take<float>(3);
+  for (int i = 0; i < 2; ++i) w.e1r[i] = c.take<u16>(M * n);
   if (any_shared)
-    for (int i = 0; i < 3; ++i) w.e1c[i] = c.take<u16>(n * Mp);
+    for (int i = 0; i < 2; ++i) w.e1c[i] = c.take<u16>(n * Mp);
   if (any_per_use)
-    for (int i = 0; i < 3; ++i) w.e2c[i] = c.take<u16>(n * Mp);
-  w.cnt1 = c.take<u16>(M * n);
-  if (any_per_use) w.cnt2 = c.take<u16>(M * n);
+    for (int i = 0; i < 2; ++i) w.e2c[i] = c.take<u16>(n * Mp);
+  if (coupling) {
+    w.cnt1 = c.take<u16>(M * n);
+    if (any_per_use) w.cnt2 = c.take<u16>(M * n);
+  }
   for (int i = 0; i < 2; ++i) {
     w.bx[i] = c.take<float>(M * k);
     w.bw[i] = c.take<float>(k * n);
@@ -47,7 +59,7 @@ LinWs carve_lin(Carver& c, int64_t M, int64_t k, int64_t n, bool any_shared, boo
     w.XB = c.take<float>(M * n);
   }
   if (want_se) {  // the per-trial path: one trial's residual planes, moves and shifted sums
-    for (int i = 0; i < 3; ++i) w.tc[i] = c.take<u16>(n * Mp);
+    for (int i = 0; i < 2; ++i) w.tc[i] = c.take<u16>(n * Mp);
     w.tdx = c.take<float>(M * k);
     w.tdw = c.take<float>(k * n);
     w.d1x = c.take<float>(M * k);
@@ -59,6 +71,9 @@ LinWs carve_lin(Carver& c, int64_t M, int64_t k, int64_t n, bool any_shared, boo
       w.S2w[i] = c.take<double>(k * n);
     }
   }
+  // outputs that need splits have at most 256 tiles of 128 x 128
+  w.gpart_cap = 4 * std::min<int64_t>(std::max(M, n) * k, (int64_t)256 * 128 * 128);
+  w.gpart = c.take<float>(w.gpart_cap);
   return w;
 }
 }  // namespace
@@ -122,7 +137,7 @@ bs_status bs_linear_bwd_policy(const void* X, const void* W, const void* dY, bs_
   BS_TRY(launch_store(dY, BS_BF16, M * n, fmt, BS_RNE, seed, 0, base, nullptr, nullptr, dY_scale, diag, st, false));
 
   auto gemm = [&](int Mg, int Ng, int Kg, int64_t lda, int64_t ldb, u16* const* A, int nA, u16* const* B, int nB,
-                  float* C, float alpha) -> bs_status {
+                  float* C, float alpha, const float* inv_a = nullptr, const float* inv_b = nullptr) -> bs_status {
     GemmArgs g{};
     g.M = Mg;
     g.N = Ng;
@@ -132,6 +147,11 @@ bs_status bs_linear_bwd_policy(const void* X, const void* W, const void* dY, bs_
     g.ldc = Ng;
     g.alpha = alpha;
     g.C = C;
+    g.part = w.gpart;
+    g.part_cap = w.gpart_cap;
+    g.f16 = inv_a != nullptr;  // scaled fp16 operands and their multipliers, else bf16
+    g.alpha_dev = inv_a;
+    g.alpha_dev2 = inv_b;
     if (!gemm_add_products(g, A, nA, B, nB)) return BS_EINVAL;
     return launch_gemm(g, st);
   };
@@ -154,38 +174,43 @@ bs_status bs_linear_bwd_policy(const void* X, const void* W, const void* dY, bs_
     BS_TRY(launch_kappa_fixed((const u16*)dY, dY_scale, fmt, M, n, w.AW, w.XB, w.fixpart, w.fixed, st));
   }
 
-  // new roundings of dY: use +1 (dX, and dW when shared), use +2 (dW per use)
-  FreshArgs<u16> fa{(const u16*)dY, M, n, f, dY_scale, seed, base + 1, K, w.cnt1, nullptr, nullptr, nullptr};
+  // the residuals' fp16 partners: X^T and W scaled (by their finite maxima; exact for all but the
+  // smallest values, see launch_scale_f16)
+  BS_TRY(launch_fill2d((float*)w.am[0], 2 * AMAX_SLOTS, 1, AMAX_STRIDE, 0.0f, st));
+  BS_TRY(launch_amax_bf16(Xp, M * k, w.am[0], st, true));
+  BS_TRY(launch_amax_bf16(Wp, k * n, w.am[1], st, true));
+  BS_TRY(launch_scale_f16(w.xT, k * Mp, w.am[0], w.x16T, w.inv + 0, st));
+  BS_TRY(launch_scale_f16(Wp, k * n, w.am[1], w.w16, w.inv + 1, st));
+
+  // new roundings of dY: use +1 (dX, and dW when shared), use +2 (dW per use); the coupling
+  // statistic draws them with its weights and leaves their counts
   if (coupling_on) {
-    fa.w1 = w.AW;
-    fa.w2 = w.XB;
-    fa.partial = w.part1;
+    FreshArgs<u16> fa{(const u16*)dY, M, n, f, dY_scale, seed, base + 1, K, w.cnt1, w.AW, w.XB, w.part1};
     BS_TRY(launch_fresh_count_t(fa, FC_BLOCKSUM, st));
-  } else {
-    BS_TRY(launch_fresh_count_t(fa, FC_COUNT, st));
-  }
-  if (any_per_use) {
-    FreshArgs<u16> fb{(const u16*)dY, M, n, f, dY_scale, seed, base + 2, K, w.cnt2, nullptr, nullptr, nullptr};
-    if (coupling_on) {
-      fb.w1 = w.XB;
-      fb.partial = w.part2;
+    if (any_per_use) {
+      FreshArgs<u16> fb{(const u16*)dY, M, n, f, dY_scale, seed, base + 2, K, w.cnt2, w.XB, nullptr, w.part2};
       BS_TRY(launch_fresh_count_t(fb, FC_BLOCKSUM, st));
-    } else {
-      BS_TRY(launch_fresh_count_t(fb, FC_COUNT, st));
     }
   }
 
   // residual planes E_u = mean of use u's roundings - dY, and the bias contractions
-  ResidArgs ra{(const u16*)dY, w.cnt1, dY_scale, K, f, M, n, {w.e1r[0], w.e1r[1], w.e1r[2]},
-               {any_shared ? w.e1c[0] : nullptr, w.e1c[1], w.e1c[2]}, Mp};
-  BS_TRY(launch_resid_planes(ra, st));
-  BS_TRY(gemm((int)M, (int)k, (int)n, n, n, w.e1r, 3, &Wp, 1, w.bx[0], 1.0f));
-  if (any_shared) BS_TRY(gemm((int)k, (int)n, (int)Mp, Mp, Mp, &w.xT, 1, w.e1c, 3, w.bw[0], 1.0f));
+  auto resid = [&](int u, int Kt, int trial0, const u16* counts, u16* const* rows, u16* const* cols) {
+    ResidArgs ra{(const u16*)dY, dY_scale, Kt, f, M, n, {rows ? rows[0] : nullptr, rows ? rows[1] : nullptr},
+                 {cols ? cols[0] : nullptr, cols ? cols[1] : nullptr}, Mp, w.inv + 2, counts, seed, base + 1 + u, trial0};
+    return launch_resid_planes(ra, st);
+  };
+  auto move_dx = [&](u16* const* rows, float* out) {
+    return gemm((int)M, (int)k, (int)n, n, n, rows, 2, &w.w16, 1, out, 1.0f, w.inv + 2, w.inv + 1);
+  };
+  auto move_dw = [&](u16* const* cols, float* out) {
+    return gemm((int)k, (int)n, (int)Mp, Mp, Mp, &w.x16T, 1, cols, 2, out, 1.0f, w.inv + 2, w.inv + 0);
+  };
+  BS_TRY(resid(0, K, 1, w.cnt1, w.e1r, any_shared ? w.e1c : nullptr));
+  BS_TRY(move_dx(w.e1r, w.bx[0]));
+  if (any_shared) BS_TRY(move_dw(w.e1c, w.bw[0]));
   if (any_per_use) {
-    ResidArgs rb{(const u16*)dY, w.cnt2, dY_scale, K, f, M, n, {nullptr, nullptr, nullptr},
-                 {w.e2c[0], w.e2c[1], w.e2c[2]}, Mp};
-    BS_TRY(launch_resid_planes(rb, st));
-    BS_TRY(gemm((int)k, (int)n, (int)Mp, Mp, Mp, &w.xT, 1, w.e2c, 3, w.bw[1], 1.0f));
+    BS_TRY(resid(1, K, 1, w.cnt2, nullptr, w.e2c));
+    BS_TRY(move_dw(w.e2c, w.bw[1]));
   }
 
   // per-policy estimates and coupling
@@ -213,21 +238,14 @@ bs_status bs_linear_bwd_policy(const void* X, const void* W, const void* dY, bs_
     for (int kk = 1; kk <= K; ++kk) {
       for (int u = 0; u < 2; ++u) {
         if (u == 1 && !any_per_use) continue;
-        FreshArgs<u16> ft{(const u16*)dY, M, n, f, dY_scale, seed, base + 1 + u, 1, u == 0 ? w.cnt1 : w.cnt2,
-                          nullptr, nullptr, nullptr};
-        ft.trial0 = kk;
-        BS_TRY(launch_fresh_count_t(ft, FC_COUNT, st));
         const bool need_w = u == 1 || any_shared;
-        ResidArgs rt{(const u16*)dY, u == 0 ? w.cnt1 : w.cnt2, dY_scale, 1, f, M, n,
-                     {u == 0 ? w.e1r[0] : nullptr, w.e1r[1], w.e1r[2]},
-                     {need_w ? w.tc[0] : nullptr, w.tc[1], w.tc[2]}, Mp};
-        BS_TRY(launch_resid_planes(rt, st));
+        BS_TRY(resid(u, 1, kk, nullptr, u == 0 ? w.e1r : nullptr, need_w ? w.tc : nullptr));
         if (u == 0 && dX.se) {
-          BS_TRY(gemm((int)M, (int)k, (int)n, n, n, w.e1r, 3, &Wp, 1, w.tdx, 1.0f));
+          BS_TRY(move_dx(w.e1r, w.tdx));
           BS_TRY(launch_trial_accum(w.tdx, 1, kk, mk, w.d1x, w.S1x, w.S2x, st));
         }
         if (need_w && dW.se) {
-          BS_TRY(gemm((int)k, (int)n, (int)Mp, Mp, Mp, &w.xT, 1, w.tc, 3, w.tdw, 1.0f));
+          BS_TRY(move_dw(w.tc, w.tdw));
           BS_TRY(launch_trial_accum(w.tdw, 1, kk, kn, w.d1w[u], w.S1w[u], w.S2w[u], st));
         }
       }

@@ -116,7 +116,8 @@ bs_status launch_fill_f64(double* p, int64_t n, double v, hipStream_t st);
 // *out (the float bits of a maximum, zeroed by the caller) raised to max |x[i]| over n floats;
 // with the other AMAX_SLOTS - 1 slots zeroed, out is a slot array
 bs_status launch_amax_f32(const float* x, int64_t n, uint32_t* out, hipStream_t st);
-bs_status launch_amax_bf16(const u16* x, int64_t n, uint32_t* out, hipStream_t st);
+// finite: over the finite values only
+bs_status launch_amax_bf16(const u16* x, int64_t n, uint32_t* out, hipStream_t st, bool finite = false);
 bs_status launch_init_diag(bs_diag* diag, hipStream_t st);
 
 // bf16 operand planes. Row-major: out_p[r*ldo + c], c < C (ldo >= C). Transposed:

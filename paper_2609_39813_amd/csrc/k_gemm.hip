@@ -40,7 +40,7 @@ constexpr int GBK = 64, GPAD = 72;
 
 // Block tile BM x BN, 256 threads as a WGM x WGN grid of wave64s; each wave owns a
 // (BM / WGM) x (BN / WGN) tile of 16 x 16 MFMA results.
-template <int BM, int BN, int WGM, int WGN>
+template <int BM, int BN, int WGM, int WGN, bool F16>
 __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs g) {
   static_assert(WGM * WGN == 4, "four waves");
   constexpr int TM = BM / WGM, TN = BN / WGN, FM = TM / 16, FN = TN / 16;
@@ -110,7 +110,13 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs g) {
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < FN; ++j) {
+          if constexpr (F16)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(halfx8, af[i]),
+                                                               __builtin_bit_cast(halfx8, bfr[j]), acc[i][j], 0, 0, 0);
+          else
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
+        }
     }
     if (c + 1 < total) sstore(buf ^ 1);
     __syncthreads();
@@ -396,12 +402,12 @@ static bs_status launch_gemm_lds(const GemmArgs& g0, int splits, hipStream_t st)
   return BS_OK;
 }
 
-template <int BM, int BN, int WGM, int WGN>
+template <int BM, int BN, int WGM, int WGN, bool F16>
 static bs_status launch_gemm_cfg(const GemmArgs& g, hipStream_t st) {
   const int64_t tiles = (int64_t)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   if (tiles > 0x7FFFFFFF) return BS_ESHAPE;
   ProfScope prof("gemm", st, gemm_flops(g), gemm_exec_flops(g));
-  gemm_nt_kernel<BM, BN, WGM, WGN><<<(unsigned)tiles, 256, 0, st>>>(g);
+  gemm_nt_kernel<BM, BN, WGM, WGN, F16><<<(unsigned)tiles, 256, 0, st>>>(g);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }
@@ -581,8 +587,8 @@ bs_status launch_gemm(const GemmArgs& g, hipStream_t st) {
   bool lds_ok = g.lda < (1 << 21) && g.ldb < (1 << 21);
   for (int i = 0; i < g.nseg; ++i) lds_ok = lds_ok && ((uintptr_t)g.A[i] & 15) == 0 && ((uintptr_t)g.B[i] & 15) == 0;
   if (lds_ok) return g.f16 ? launch_gemm_planned<true>(g, st) : launch_gemm_planned<false>(g, st);
-  if (g.f16 || g.amax || g.batch > 1) return BS_EINVAL;  // fp16 operands, maxima, batches: aligned operands only
-  return launch_gemm_cfg<128, 128, 2, 2>(g, st);
+  if (g.amax || g.batch > 1) return BS_EINVAL;  // maxima, batches: aligned operands only
+  return g.f16 ? launch_gemm_cfg<128, 128, 2, 2, true>(g, st) : launch_gemm_cfg<128, 128, 2, 2, false>(g, st);
 }
 
 }  // namespace bsp

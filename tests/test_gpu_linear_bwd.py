@@ -57,6 +57,43 @@ def test_ragged_shared_and_per_use_with_coupling(lib, M, k, n):
     compare(out, ref, ("shared", "per_use"), M, k, n)
 
 
+@pytest.mark.parametrize("M,k,n,K,fmt,shift", [
+    (129, 40, 72, 5, "e5m2", 0),    # one row past two 64-row tiles, a ragged column tile, uneven trial blocks
+    (64, 8, 200, 7, "e4m3", 0),     # E4M3's bound of the residual split
+    (70, 24, 136, 4, "e5m2", 1),    # dY 2-byte aligned only
+])
+def test_residuals_drawn_with_their_planes(lib, M, k, n, K, fmt, shift):
+    """Without probes each use's new roundings are drawn in the pass that writes its residual planes."""
+    X, W, dY, _, _ = synth.linear_bwd_inputs(M, k, n, torch.bfloat16, 44)
+    dYd = torch.cat((torch.zeros(shift, dtype=torch.bfloat16), dY.reshape(-1))).cuda()[shift:].view(M, n)
+    print(f"[linear_bwd] drawn M={M} k={k} n={n} K={K} fmt={fmt} shift={shift}", flush=True)
+    out = lib.linear_bwd_policy(X.cuda(), W.cuda(), dYd, fmt=fmt, K=K, seed=M, store_id=2, want_se=True)
+    torch.cuda.synchronize()
+    ref = linear_bwd.check(X.float().numpy(), W.float().numpy(), dY.float().numpy(),
+                           fmt=fp8.E5M2 if fmt == "e5m2" else fp8.E4M3, K=K, seed=M, store_id=2)
+    compare(out, ref, ("shared", "per_use"), M, k, n, coupling=False)
+
+
+def test_an_infinity_in_x_stays_in_its_row(lib):
+    """The scaled fp16 copy of X takes its scale from the finite values: an infinite X[t, i] makes row i of
+    dW infinite or NaN and leaves the other rows (and dX) within tolerance."""
+    M, k, n, K = 96, 16, 64, 6
+    X, W, dY, _, _ = synth.linear_bwd_inputs(M, k, n, torch.bfloat16, 45)
+    X = X * 1000.0                  # beyond fp16's range unscaled
+    Xi = X.clone()
+    Xi[5, 3] = float("inf")
+    out = lib.linear_bwd_policy(Xi.cuda(), W.cuda(), dY.cuda(), K=K, seed=3, store_id=2)
+    torch.cuda.synchronize()
+    ref = linear_bwd.check(X.float().numpy(), W.float().numpy(), dY.float().numpy(), fmt=fp8.E5M2, K=K, seed=3,
+                           store_id=2)
+    rows = [i for i in range(k) if i != 3]
+    for i, sh in enumerate(("shared", "per_use")):
+        b = to_np(out["dW"]["bias"][i]).reshape(k, n)
+        assert not np.any(np.isfinite(b[3]))
+        assert_rel(b[rows], ref[sh]["dW"][1][rows], TOL, f"{sh} dW bias")
+        assert_rel(to_np(out["dX"]["bias"][i]).reshape(M, k), ref[sh]["dX"][1], TOL, f"{sh} dX bias")
+
+
 def test_se_over_trials_per_use_only_and_one_trial(lib):
     """The per-trial path: se of dX and dW for a per-use policy alone (its dW series is use +2),
     and K = 1 (se 0)."""
