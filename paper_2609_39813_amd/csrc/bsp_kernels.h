@@ -113,8 +113,8 @@ bs_status launch_combine(const float* ref, const float* bias, const float* se, i
 
 bs_status launch_fill2d(float* p, int64_t rows, int64_t cols, int64_t ld, float v, hipStream_t st);
 bs_status launch_fill_f64(double* p, int64_t n, double v, hipStream_t st);
-// *out (the float bits of a maximum, zeroed by the caller) raised to max |x[i]| over n floats;
-// with the other AMAX_SLOTS - 1 slots zeroed, out is a slot array
+// the slot array out (AMAX_SLOTS words AMAX_STRIDE apart, float bits, zeroed by the caller) raised
+// to max |x[i]| over n values
 bs_status launch_amax_f32(const float* x, int64_t n, uint32_t* out, hipStream_t st);
 // finite: over the finite values only
 bs_status launch_amax_bf16(const u16* x, int64_t n, uint32_t* out, hipStream_t st, bool finite = false);
@@ -154,6 +154,9 @@ bs_status launch_split_move(const MoveSrc& m, const float* base, int64_t ldb, in
 // AMAX_SLOTS array), 2^-e to inv_out (nullable). Exact where |in| 2^e >= 2^-17 (fp16 subnormal
 // spacing); below, the error is at most 2^-25 2^-e.
 bs_status launch_scale_f16(const u16* in, int64_t n, const uint32_t* slots, u16* out, float* inv_out, hipStream_t st);
+// its transpose: out[c*ldo + r] for r < ldo (zero for r >= R) of a bf16 [R][C]
+bs_status launch_transpose_f16(const u16* in, int64_t R, int64_t C, int64_t ldi, const uint32_t* slots, u16* out,
+                               int64_t ldo, float* inv_out, hipStream_t st);
 
 // Trial statistics over per-trial rows (App. C.4, App. D.4).
 bs_status launch_policy_bias(const float* delta, int K, int64_t m, const float* g_ref, float* mean_err, float* se,

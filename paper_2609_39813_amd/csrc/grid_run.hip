@@ -5,11 +5,12 @@
 // Per token t: s_t = fl32(max_j |u_tj| / M), M = 2^(b-1) - 1; y = fl32(u / s_t); a = min(|y|, M)
 // (clamps counted); lo = floor(a), F = floor((a - lo) 2^32); the code rounds up iff R + F >= 2^32;
 // u_q = fl32(q s_t). Every bias is a contraction (weight use) or an fp64 column sum (gain use) of
-// a residual: e_U = u - u_q, e_N = mean_k u_f,k - u_q, e_e = mean_k u_f,k - u, where the mean
+// a residual: e_U = u - u_q, e_e = mean_k u_f,k - u, e_N = mean_k u_f,k - u_q = e_U + e_e, where the mean
 // over trials of the grid values is ((K - n) v_lo + n v_hi) / K from the element's up-count n.
 #include <algorithm>
 
 #include "bsp_kernels.h"
+#include "k_fresh.h"
 #include "k_norm.h"
 
 #define BS_TRY(x)               \
@@ -89,78 +90,142 @@ __global__ __launch_bounds__(256) void grid_store_kernel(const float* __restrict
   if (lane == 0 && nsat) atomicAdd(&diag->n_saturated, nsat);
 }
 
-// one thread per 4 elements: up-counts of the new rounding over K trials, then e_N and e_e
-__global__ __launch_bounds__(256) void grid_fresh_kernel(const float* __restrict__ u, const float* __restrict__ uq,
-                                                         const float* __restrict__ step, int64_t T, int64_t d,
-                                                         int bits, uint64_t seed, uint32_t use, int K,
-                                                         float* __restrict__ eN, float* __restrict__ eE) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g * 4 >= T * d) return;
-  const int64_t e0 = g * 4, t = e0 / d;
+// up-counts of the new rounding over K trials (flat groups of 4 elements, k_fresh.h), then e_e =
+// mean_k u_f,k - u (e_N = e_e + e_U, so the N bias is the sum of the R+e and U biases). 8192 x 1024,
+// 256 trials: 740 us; one group per thread with every trial in its thread, 786 us.
+template <int G, int TS>
+__global__ __launch_bounds__(fresh_nt(TS)) void grid_fresh_kernel(const float* __restrict__ u,
+                                                                  const float* __restrict__ step, int64_t T, int64_t d,
+                                                                  int bits, uint64_t seed, uint32_t use, int K,
+                                                                  float* __restrict__ eE) {
+  const FreshBlock<G, TS> blk;
+  const uint64_t ngroups = (uint64_t)(T * d) >> 2;
   const float M = (float)((1 << (bits - 1)) - 1);
-  const float s = step[t];
-  const float4 v = *(const float4*)(u + e0);
-  const float4 q4 = *(const float4*)(uq + e0);
-  const float uv[4] = {v.x, v.y, v.z, v.w}, qv[4] = {q4.x, q4.y, q4.z, q4.w};
-  GridBracket b[4];
+  uint32_t F[G][4], cnt[G][4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) b[r] = grid_bracket(uv[r], s, M);
-  uint32_t n[4] = {0u, 0u, 0u, 0u};
-  for (int k = 1; k <= K; ++k) {
-    const Philox4 p = philox_group(seed, (uint64_t)g, (uint32_t)k, use);
-    n[0] += sr_up(b[0].F, p.w0);
-    n[1] += sr_up(b[1].F, p.w1);
-    n[2] += sr_up(b[2].F, p.w2);
-    n[3] += sr_up(b[3].F, p.w3);
-  }
-  float oN[4], oE[4];
+  for (int r = 0; r < G; ++r) {
+    const uint64_t g = blk.group(r);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const double vlo = grid_value(b[r].lo, b[r].neg, s), vhi = grid_value(b[r].lo + 1.0f, b[r].neg, s);
-    const double mf = ((double)(K - (int)n[r]) * vlo + (double)n[r] * vhi) / (double)K;
-    oN[r] = (float)(mf - (double)qv[r]);
-    oE[r] = (float)(mf - (double)uv[r]);
+    for (int q = 0; q < 4; ++q) F[r][q] = 0;
+    if (g < ngroups) {
+      const float s = step[4 * g / d];
+      const float4 v = *(const float4*)(u + 4 * g);
+      const float uv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) F[r][q] = grid_bracket(uv[q], s, M).F;
+    }
   }
-  *(float4*)(eN + e0) = make_float4(oN[0], oN[1], oN[2], oN[3]);
-  *(float4*)(eE + e0) = make_float4(oE[0], oE[1], oE[2], oE[3]);
+  blk.count(F, cnt, K, 1, use, seed);
+  uint2 n2[G];
+  if (!blk.merge(cnt, n2)) return;
+#pragma unroll
+  for (int r = 0; r < G; ++r) {
+    const uint64_t g = blk.group(r);
+    if (g >= ngroups) continue;
+    const float s = step[4 * g / d];
+    const float4 v = *(const float4*)(u + 4 * g);
+    const float uv[4] = {v.x, v.y, v.z, v.w};
+    float o[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t w = q < 2 ? n2[r].x : n2[r].y;
+      const int n = (int)(q & 1 ? w >> 16 : w & 0xFFFFu);
+      const GridBracket b = grid_bracket(uv[q], s, M);
+      const double vlo = grid_value(b.lo, b.neg, s), vhi = grid_value(b.lo + 1.0f, b.neg, s);
+      o[q] = (float)(((double)(K - n) * vlo + (double)n * vhi) / (double)K - (double)uv[q]);
+    }
+    *(float4*)(eE + 4 * g) = make_float4(o[0], o[1], o[2], o[3]);
+  }
+}
+
+// The bounds of the scaled fp16 splits as slot arrays: |u_q| <= max |u| (slots 0) and |e| <= the
+// largest step, max |u| / M (slots 1), each up to rounding.
+__global__ __launch_bounds__(64) void grid_bounds_kernel(const bs_diag* __restrict__ diag, int bits,
+                                                         uint32_t* __restrict__ su, uint32_t* __restrict__ se) {
+  const int i = threadIdx.x;
+  if (i >= AMAX_SLOTS) return;
+  const float a = diag->amax, m = (float)((1 << (bits - 1)) - 1);
+  su[i * AMAX_STRIDE] = i == 0 ? __float_as_uint(a) : 0u;
+  se[i * AMAX_STRIDE] = i == 0 ? __float_as_uint(a / m) : 0u;
 }
 
 // gain use, fp64 column partials over token chunks of 256: [3][nchunk][d]
 //   ref  sum z du;  R  sum (u/gain - z - eU/gain) du;  N  sum (u/gain - z + eE/gain) du
-// rows per chunk of the gain use's column partial sums: T / 32 chunks (grid x) x d / 64 one-wave
-// blocks (grid y)
+// rows per chunk of the gain use's column partial sums: T / 32 chunks (grid x) x d / 256 blocks
+// (grid y); a lane takes 4 columns of its wave's 8 rows (16-byte loads, four rows in flight), the
+// four waves' sums meet in LDS in wave order. 8192 x 1024: 35 us; one column and 32 rows per lane
+// 61 us (few bytes in flight).
 constexpr int GRID_GAIN_RT = 32;
 
+__device__ __forceinline__ float4 load4(const float* p) { return *(const float4*)p; }
+__device__ __forceinline__ float4 load4(const u16* p) {
+  const uint2 v = *(const uint2*)p;
+  return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xFFFF0000u), __uint_as_float(v.y << 16),
+                     __uint_as_float(v.y & 0xFFFF0000u));
+}
+
 template <typename XT>
-__global__ __launch_bounds__(64) void grid_gain_kernel(const XT* __restrict__ X, const float* __restrict__ rstd,
-                                                       const float* __restrict__ gain, const float* __restrict__ u,
-                                                       const float* __restrict__ du, const float* __restrict__ eU,
-                                                       const float* __restrict__ eE, int64_t T, int64_t d,
-                                                       double* __restrict__ part) {
+__global__ __launch_bounds__(256) void grid_gain_kernel(const XT* __restrict__ X, const float* __restrict__ rstd,
+                                                        const float* __restrict__ gain, const float* __restrict__ u,
+                                                        const float* __restrict__ du, const float* __restrict__ eU,
+                                                        const float* __restrict__ eE, int64_t T, int64_t d,
+                                                        double* __restrict__ part) {
 #pragma clang fp contract(off)
-  const int64_t j = (int64_t)blockIdx.y * 64 + threadIdx.x;
+  __shared__ double red[4][3][64][5];  // a lane's 4 columns and a pad word pair
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t j = (int64_t)blockIdx.y * 256 + 4 * lane;
   const int64_t c = blockIdx.x, nch = gridDim.x;
-  if (j >= d) return;
-  const double g = gain[j];
-  double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-  const int64_t t1 = min(T, (c + 1) * GRID_GAIN_RT);
-  for (int64_t t = c * GRID_GAIN_RT; t < t1; ++t) {
-    const int64_t e = t * d + j;
-    const double z = (double)(load_f32(X, e) * rstd[t]);
-    const double dd = du[e];
-    const double base = (double)u[e] / g - z;
-    a0 += z * dd;
-    if (eU) a1 += (base - (double)eU[e] / g) * dd;
-    if (eE) a2 += (base + (double)eE[e] / g) * dd;
+  const bool ok = j < d;  // d % 8 == 0
+  const bool va = ((uintptr_t)X & (4 * sizeof(XT) - 1)) == 0 && ((uintptr_t)gain & 15) == 0;
+  double acc[3][4] = {}, ig[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) ig[q] = ok ? 1.0 / (double)gain[j + q] : 0.0;
+  const int64_t t0 = c * GRID_GAIN_RT + 8 * wave;
+  if (ok) {
+#pragma unroll 4
+    for (int i = 0; i < 8; ++i) {
+      const int64_t t = t0 + i;
+      if (t >= T) break;
+      const int64_t e = t * d + j;
+      float4 xv;
+      if (va)
+        xv = load4(X + e);
+      else
+        xv = make_float4(load_f32(X, e), load_f32(X, e + 1), load_f32(X, e + 2), load_f32(X, e + 3));
+      const float4 uv = load4(u + e), dv = load4(du + e), a = load4(eU + e), b = load4(eE + e);
+      const float x4[4] = {xv.x, xv.y, xv.z, xv.w}, u4[4] = {uv.x, uv.y, uv.z, uv.w}, d4[4] = {dv.x, dv.y, dv.z, dv.w};
+      const float a4[4] = {a.x, a.y, a.z, a.w}, b4[4] = {b.x, b.y, b.z, b.w};
+      const float r = rstd[t];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double z = (double)(x4[q] * r), dd = d4[q], base = (double)u4[q] * ig[q] - z;
+        acc[0][q] += z * dd;
+        acc[1][q] += (base - (double)a4[q] * ig[q]) * dd;
+        acc[2][q] += (base + (double)b4[q] * ig[q]) * dd;
+      }
+    }
   }
-  part[(0 * nch + c) * d + j] = a0;
-  part[(1 * nch + c) * d + j] = a1;
-  part[(2 * nch + c) * d + j] = a2;
+#pragma unroll
+  for (int p = 0; p < 3; ++p)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) red[wave][p][lane][q] = acc[p][q];
+  __syncthreads();
+  // thread (column of the 256, each of the three sums)
+  const int l = threadIdx.x >> 2, q = threadIdx.x & 3;
+  const int64_t jo = (int64_t)blockIdx.y * 256 + threadIdx.x;
+  if (jo >= d) return;
+#pragma unroll
+  for (int p = 0; p < 3; ++p)
+    part[((int64_t)p * nch + c) * d + jo] = ((red[0][p][l][q] + red[1][p][l][q]) + red[2][p][l][q]) + red[3][p][l][q];
 }
 
 struct GridWs {
-  float *u, *rstd, *du, *uq, *eU, *eN, *eE, *bias_rg, *bias_ng, *bias_w[3];  // weight biases: U, N, R+e
+  float *u, *rstd, *du, *uq, *eU, *eE, *bias_rg, *bias_ng, *bias_w[2];  // weight biases: U, R+e
   u16 *dyT[3], *aT[3], *uq_rows[3], *wT[3], *dy_rows[3], *w_rows[3];
+  // fp16 operands (bf16 inputs): the maxima of dY, W, u_q and the residuals (slot arrays) and their
+  // multipliers 2^-e (u_q, U, R+e; W; dY)
+  uint32_t* am[4];
+  float* inv;
   double* gpart;
   float* gemm_part;
   int64_t gemm_part_cap;
@@ -170,7 +235,7 @@ GridWs carve_grid(Carver& c, int64_t T, int64_t d, int64_t n, bs_dtype wt, bs_dt
   GridWs w{};
   const int64_t Tp = round_up(T > 0 ? T : 1, 64);
   const int nt = gt == BS_F32 ? 3 : 1, ntw = wt == BS_F32 ? 3 : 1;
-  for (float** p : {&w.u, &w.du, &w.uq, &w.eU, &w.eN, &w.eE}) *p = c.take<float>(T * d);
+  for (float** p : {&w.u, &w.du, &w.uq, &w.eU, &w.eE}) *p = c.take<float>(T * d);
   w.rstd = c.take<float>(T > 0 ? T : 1);
   for (int i = 0; i < nt; ++i) w.dyT[i] = c.take<u16>(n * Tp);
   for (int i = 0; i < 3; ++i) w.aT[i] = c.take<u16>(d * Tp);
@@ -184,7 +249,10 @@ GridWs carve_grid(Carver& c, int64_t T, int64_t d, int64_t n, bs_dtype wt, bs_dt
   }
   w.bias_rg = c.take<float>(d);
   w.bias_ng = c.take<float>(d);
-  for (int i = 0; i < 3; ++i) w.bias_w[i] = c.take<float>(d * n);
+  for (int i = 0; i < 2; ++i) w.bias_w[i] = c.take<float>(d * n);
+  uint32_t* a = c.take<uint32_t>(4 * AMAX_SLOTS * AMAX_STRIDE);
+  for (int i = 0; i < 4; ++i) w.am[i] = a ? a + i * AMAX_SLOTS * AMAX_STRIDE : nullptr;
+  w.inv = c.take<float>(5);
   w.gpart = c.take<double>(3 * ((T + GRID_GAIN_RT - 1) / GRID_GAIN_RT + 1) * d);
   w.gemm_part_cap = 4 * d * std::max<int64_t>(std::max<int64_t>(T, n), 64);
   w.gemm_part = c.take<float>(w.gemm_part_cap);
@@ -253,10 +321,32 @@ bs_status grid_run(const GridIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
                                                                w.uq, w.eU, io.diag);
     BS_CHECK_LAUNCH();
   }
-  // Y = u_q W (three bf16 terms of u_q)
+  // bf16 inputs: u_q and the residuals enter the contractions as scaled two-term fp16 splits against
+  // scaled fp16 W and dY (9 term products in all; three bf16 terms each made it 16), their planes
+  // of one read each; fp32 inputs as three bf16 terms
+  const bool h16 = io.dt == BS_BF16;
+  if (h16) {
+    BS_TRY(launch_fill2d((float*)w.am[0], 2 * AMAX_SLOTS, 1, AMAX_STRIDE, 0.0f, st));
+    BS_TRY(launch_amax_bf16((const u16*)io.dY, T * n, w.am[0], st, true));
+    if (io.Y) BS_TRY(launch_amax_bf16((const u16*)io.W, d * n, w.am[1], st, true));
+    grid_bounds_kernel<<<1, 64, 0, st>>>(io.diag, io.bits, w.am[2], w.am[3]);
+    BS_CHECK_LAUNCH();
+  }
+  auto split16 = [&](const float* src, const uint32_t* am, float* inv, u16* const* rows) {
+    MoveSrc ms{};
+    ms.rows = src;
+    ms.ldi = d;
+    return launch_split_move(ms, nullptr, 0, T, d, F16Scale{am, nullptr, inv}, w.aT, nullptr, Tp, rows, d, st);
+  };
+  if (h16) BS_TRY(split16(w.uq, w.am[2], w.inv + 0, io.Y ? w.uq_rows : nullptr));
+  // Y = u_q W
   if (io.Y) {
-    BS_TRY(launch_planes(w.uq, BS_F32, T, d, d, false, w.uq_rows, 3, d, 1.0f, st));
-    BS_TRY(launch_planes(io.W, wt, d, n, n, true, w.wT, ntw, d, 1.0f, st));
+    if (h16) {
+      BS_TRY(launch_transpose_f16((const u16*)io.W, d, n, n, w.am[1], w.wT[0], d, w.inv + 3, st));
+    } else {
+      BS_TRY(launch_planes(w.uq, BS_F32, T, d, d, false, w.uq_rows, 3, d, 1.0f, st));
+      BS_TRY(launch_planes(io.W, wt, d, n, n, true, w.wT, ntw, d, 1.0f, st));
+    }
     GemmArgs g{};
     g.M = (int)T;
     g.N = (int)n;
@@ -266,7 +356,12 @@ bs_status grid_run(const GridIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
     g.ldc = n;
     g.alpha = 1.0f;
     g.C = io.Y;
-    gemm_add_products(g, w.uq_rows, 3, w.wT, ntw);
+    if (h16) {
+      g.f16 = 1;
+      g.alpha_dev = w.inv + 0;
+      g.alpha_dev2 = w.inv + 3;
+    }
+    gemm_add_products(g, w.uq_rows, h16 ? 2 : 3, w.wT, ntw);
     BS_TRY(launch_gemm(g, st));
   }
   // du = dY W^T
@@ -297,20 +392,28 @@ bs_status grid_run(const GridIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
     gemm_add_products(g, Aops, nt, Bops, ntw);
     BS_TRY(launch_gemm(g, st));
   }
-  // the new rounding's residuals over K trials
+  // the new rounding's residual over K trials
   {
     ProfScope prof("grid_fresh", st);
-    const int64_t groups = T * d / 4;
-    grid_fresh_kernel<<<(unsigned)((groups + 255) / 256), 256, 0, st>>>(w.u, w.uq, io.step, T, d, io.bits, io.seed,
-                                                                       base + 1, io.K, w.eN, w.eE);
+    BS_TRY(launch_fresh_flat(T * d, io.K, [&](auto g, auto ts, unsigned blocks, int nt) {
+      grid_fresh_kernel<decltype(g)::value, decltype(ts)::value><<<blocks, nt, 0, st>>>(
+          w.u, io.step, T, d, io.bits, io.seed, base + 1, io.K, w.eE);
+    }));
     BS_CHECK_LAUNCH();
   }
-  // weight use: reference and the U, N and R+e biases, contractions of [d][Tp] planes with dY^T
-  BS_TRY(launch_planes(io.dY, gt, T, n, n, true, w.dyT, nt, Tp, 1.0f, st));
-  const float* srcs[4] = {w.uq, w.eU, w.eN, w.eE};
-  float* dsts[4] = {io.dW_ref, w.bias_w[0], w.bias_w[1], w.bias_w[2]};
-  for (int i = 0; i < 4; ++i) {
-    BS_TRY(launch_planes(srcs[i], BS_F32, T, d, d, true, w.aT, 3, Tp, 1.0f, st));
+  // weight use: reference and the U and R+e biases, contractions of [d][Tp] planes with dY^T (the N
+  // bias is their sum)
+  if (h16)
+    BS_TRY(launch_transpose_f16((const u16*)io.dY, T, n, n, w.am[0], w.dyT[0], Tp, w.inv + 4, st));
+  else
+    BS_TRY(launch_planes(io.dY, gt, T, n, n, true, w.dyT, nt, Tp, 1.0f, st));
+  const float* srcs[3] = {w.uq, w.eU, w.eE};
+  float* dsts[3] = {io.dW_ref, w.bias_w[0], w.bias_w[1]};
+  for (int i = 0; i < 3; ++i) {
+    if (!h16)
+      BS_TRY(launch_planes(srcs[i], BS_F32, T, d, d, true, w.aT, 3, Tp, 1.0f, st));
+    else if (i > 0)
+      BS_TRY(split16(srcs[i], w.am[3], w.inv + i, nullptr));
     GemmArgs g{};
     g.M = (int)d;
     g.N = (int)n;
@@ -322,18 +425,23 @@ bs_status grid_run(const GridIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
     g.C = dsts[i];
     g.part = w.gemm_part;
     g.part_cap = w.gemm_part_cap;
-    if (!gemm_add_products(g, w.aT, 3, w.dyT, nt)) return BS_EINVAL;
+    if (h16) {
+      g.f16 = 1;
+      g.alpha_dev = w.inv + i;
+      g.alpha_dev2 = w.inv + 4;
+    }
+    if (!gemm_add_products(g, w.aT, h16 ? 2 : 3, w.dyT, nt)) return BS_EINVAL;
     BS_TRY(launch_gemm(g, st));
   }
   // gain use: fp64 column sums
   {
     const int64_t nch = (T + GRID_GAIN_RT - 1) / GRID_GAIN_RT;
-    const dim3 grid((unsigned)nch, (unsigned)((d + 63) / 64));
+    const dim3 grid((unsigned)nch, (unsigned)((d + 255) / 256));
     if (xt == BS_F32)
-      grid_gain_kernel<float><<<grid, 64, 0, st>>>((const float*)io.X, w.rstd, io.gain, w.u, w.du, w.eU, w.eE, T, d,
+      grid_gain_kernel<float><<<grid, 256, 0, st>>>((const float*)io.X, w.rstd, io.gain, w.u, w.du, w.eU, w.eE, T, d,
                                                    w.gpart);
     else
-      grid_gain_kernel<u16><<<grid, 64, 0, st>>>((const u16*)io.X, w.rstd, io.gain, w.u, w.du, w.eU, w.eE, T, d,
+      grid_gain_kernel<u16><<<grid, 256, 0, st>>>((const u16*)io.X, w.rstd, io.gain, w.u, w.du, w.eU, w.eE, T, d,
                                                  w.gpart);
     BS_CHECK_LAUNCH();
     BS_TRY(launch_gain_final(w.gpart, nch, d, io.dgain_ref, w.bias_rg, w.bias_ng, st));
@@ -360,9 +468,10 @@ bs_status grid_run(const GridIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
     const bs_grid_policy& q = io.pol[i];
     cg.bias[i] = q.gain_use == BS_READ_R ? w.bias_rg : (q.gain_use == BS_READ_N ? w.bias_ng : nullptr);
     cw.bias[i] = q.weight_use == BS_WREAD_U       ? w.bias_w[0]
-                 : q.weight_use == BS_WREAD_N     ? w.bias_w[1]
-                 : q.weight_use == BS_WREAD_R_EPS ? w.bias_w[2]
+                 : q.weight_use == BS_WREAD_N     ? w.bias_w[0]
+                 : q.weight_use == BS_WREAD_R_EPS ? w.bias_w[1]
                                                   : nullptr;
+    if (q.weight_use == BS_WREAD_N) cw.bias2[i] = w.bias_w[1];
   }
   BS_TRY(launch_combine_multi(cg, d, st));
   BS_TRY(launch_combine_multi(cw, d * n, st));

@@ -6,12 +6,14 @@ namespace bsp {
 
 // Every policy's estimate of one gradient in one pass over its reference: policy p writes
 // mean_p = ref + bias_p (or alt_p, with bias_p = alt_p - ref, when alt_p is set), bias_p and se_p
-// at offset p n of the nullable output bases (inputs bias_p / se_p nullable = 0).
+// at offset p n of the nullable output bases (inputs bias_p / se_p nullable = 0; bias2_p, with
+// bias_p set, is added to it).
 constexpr int COMBINE_MAX_POL = 16;
 struct CombineMulti {
   const float* ref;
   int n_pol, vec;
   const float* bias[COMBINE_MAX_POL];
+  const float* bias2[COMBINE_MAX_POL];
   const float* se[COMBINE_MAX_POL];
   const float* alt[COMBINE_MAX_POL];
   float *mean, *bias_out, *se_out;  // bases of [n_pol][n] outputs (nullable)

@@ -836,6 +836,10 @@ __global__ __launch_bounds__(256) void combine_multi_kernel(CombineMulti c, int6
         b = make_float4(m.x - r.x, m.y - r.y, m.z - r.z, m.w - r.w);
       } else {
         b = c.bias[p] ? ((const float4*)c.bias[p])[i] : z;
+        if (c.bias2[p]) {
+          const float4 b2 = ((const float4*)c.bias2[p])[i];
+          b = make_float4(b.x + b2.x, b.y + b2.y, b.z + b2.z, b.w + b2.w);
+        }
         m = c.bias[p] ? make_float4(r.x + b.x, r.y + b.y, r.z + b.z, r.w + b.w) : r;
       }
       // streaming outputs: non-temporal stores keep them from displacing the inputs in the caches
@@ -848,8 +852,9 @@ __global__ __launch_bounds__(256) void combine_multi_kernel(CombineMulti c, int6
     const float r = c.ref[i];
     for (int p = 0; p < c.n_pol; ++p) {
       const int64_t o = (int64_t)p * n + i;
-      const float m = c.alt[p] ? c.alt[p][i] : (c.bias[p] ? r + c.bias[p][i] : r);
-      const float b = c.alt[p] ? m - r : (c.bias[p] ? c.bias[p][i] : 0.0f);
+      const float bi = c.bias[p] ? c.bias[p][i] + (c.bias2[p] ? c.bias2[p][i] : 0.0f) : 0.0f;
+      const float m = c.alt[p] ? c.alt[p][i] : (c.bias[p] ? r + bi : r);
+      const float b = c.alt[p] ? m - r : bi;
       if (c.mean) c.mean[o] = m;
       if (c.bias_out) c.bias_out[o] = b;
       if (c.se_out) c.se_out[o] = c.se[p] ? c.se[p][i] : 0.0f;
@@ -873,7 +878,7 @@ bs_status launch_combine_multi(CombineMulti c, int64_t n, hipStream_t st) {
   for (const void* q : {(const void*)c.ref, (const void*)c.mean, (const void*)c.bias_out, (const void*)c.se_out})
     vec = vec && ((uintptr_t)q & 15) == 0;
   for (int p = 0; p < c.n_pol; ++p)
-    for (const void* q : {(const void*)c.bias[p], (const void*)c.se[p], (const void*)c.alt[p]})
+    for (const void* q : {(const void*)c.bias[p], (const void*)c.bias2[p], (const void*)c.se[p], (const void*)c.alt[p]})
       vec = vec && ((uintptr_t)q & 15) == 0;
   c.vec = vec ? 1 : 0;
   combine_multi_kernel<<<grid1d((n + 3) / 4, 4096), 256, 0, st>>>(c, n);

@@ -1,8 +1,10 @@
 // FP8 store kernels: amax, scale, quantize (RNE / stochastic), and the K-trial
 // stochastic-rounding counter of a store's new roundings.
+#include <algorithm>
 #include <type_traits>
 
 #include "bsp_kernels.h"
+#include "k_fresh.h"
 
 namespace bsp {
 
@@ -47,7 +49,7 @@ __device__ __forceinline__ uint32_t vec_absmax<u16, true>(uint4 v) { return bf16
 
 template <typename T, bool FIN = false>
 __global__ __launch_bounds__(256) void amax_kernel(const T* __restrict__ x, int64_t n,
-                                                   uint32_t* __restrict__ amax_bits) {
+                                                   uint32_t* __restrict__ amax_bits, int nslots) {
   constexpr int PER = 16 / sizeof(T);
   uint32_t m = 0;
   const int64_t nvec = ((uintptr_t)x & 15) ? 0 : n / PER;
@@ -97,8 +99,15 @@ __global__ __launch_bounds__(256) void amax_kernel(const T* __restrict__ x, int6
   if (threadIdx.x == 0) {
     uint32_t b = red[0];
     for (int k = 1; k < (int)(blockDim.x >> 6); ++k) b = b > red[k] ? b : red[k];
-    if (b) atomicMax(amax_bits, b);
+    if (b) atomicMax(amax_bits + (blockIdx.x % nslots) * AMAX_STRIDE, b);
   }
+}
+
+// Blocks of amax_kernel for nvec 16-byte vectors: at most four per CU, and no more than leave every
+// thread its batch of eight loads in flight (with 1024 blocks on 4 M floats each thread had one
+// load: 18.6 us, now 10.4); small tensors one load per thread on up to 64 blocks.
+inline int amax_blocks(int64_t nvec) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(1024, std::max<int64_t>(nvec / 2048, std::min<int64_t>(64, (nvec + 255) / 256))));
 }
 
 __global__ void finalize_scale_kernel(bs_diag* diag, const float* scale_in, float* scale_out, float fmax) {
@@ -235,79 +244,31 @@ __global__ __launch_bounds__(256) void quantize_kernel(const T* __restrict__ x, 
 //   FC_COLSUM: colsum[k-1][rt][j] = sum over 32 rows (row tile rt) of up_k c (w = w1), fp32
 //   FC_BLOCKSUM: partial[k-1][i][b] = sum over block b's elements of up_k c_i (w1, w2), fp64
 // Bound by the Philox rounds (8.5 VALU per word beside the shared first rounds) and the decision.
-//
-// The trials of one element are independent, so a tensor with too few elements to fill the chip
-// splits its trials over the TS waves of a block (wave p takes trials p, p + TS, ...); the counts
-// of the parts meet in LDS (integers: any order gives the same sum). At 256 x 64 with 64 trials the
-// counts take 4.9 us (56 with every trial in one wave) and the column sums 20 us (64); at 1111 x
-// 520 with 24 trials 9.6 (27) and 19 us (32).
-
-// Counts alone: the tensor as flat groups of 4 elements (one Philox call each); block of NT
-// threads, G groups per thread. A block's groups are an aligned power-of-two range, so the high
-// counter word is uniform (scalar). 16384 x 8192 x 64 trials: 2.80 ms, 3.07 T element-trials/s
-// (2.91 ms with rows and columns per thread and a vector high word).
+// Counts alone: the tensor as flat groups (k_fresh.h). 16384 x 8192 x 64 trials: 2.80 ms, 3.07 T
+// element-trials/s (2.91 ms with rows and columns per thread and a vector high word).
 template <typename X, int G, int TS>
-__global__ __launch_bounds__(TS > 4 ? 64 * TS : 256) void fresh_count_kernel(FreshArgs<X> a) {
-  constexpr int NT = TS > 4 ? 64 * TS : 256, LN = NT / TS, TB = 4;  // LN lanes (x G groups) per block
-  const int tid = threadIdx.x;
-  const int part = TS > 1 ? __builtin_amdgcn_readfirstlane(tid / LN) : 0, ln = TS > 1 ? tid % LN : tid;
-  const uint64_t ngroups = (uint64_t)(a.T * a.d) >> 2, base = (uint64_t)blockIdx.x * (LN * G);
-  const uint32_t g_hi = (uint32_t)(base >> 32);
+__global__ __launch_bounds__(fresh_nt(TS)) void fresh_count_kernel(FreshArgs<X> a) {
+  const FreshBlock<G, TS> blk;
+  const uint64_t ngroups = (uint64_t)(a.T * a.d) >> 2;
   const double rs = 1.0 / (double)*a.scale;
   uint32_t F[G][4], cnt[G][4];
 #pragma unroll
   for (int r = 0; r < G; ++r) {
-    const uint64_t g = base + r * LN + ln;
-    const bool ok = g < ngroups;
-    float xv[4] = {0.f, 0.f, 0.f, 0.f};
-    if (ok) {
+    const uint64_t g = blk.group(r);
+    float xv[4] = {0.f, 0.f, 0.f, 0.f};  // past the end: F = 0
+    if (g < ngroups) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) xv[q] = load_f32(a.x, 4 * g + q);
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const Bracket b = f8_bracket(fminf(fabsf(div_scale(xv[q], rs)), a.f.fmax), a.f);
-      F[r][q] = b.F;  // 0 past the end
-      cnt[r][q] = 0;
-      asm volatile("" : "+v"(F[r][q]));  // opaque: keeps the validity test out of the trial loop
-    }
+    for (int q = 0; q < 4; ++q) F[r][q] = f8_bracket(fminf(fabsf(div_scale(xv[q], rs)), a.f.fmax), a.f).F;
   }
-  for (int k0 = part; k0 < a.K; k0 += TB * TS) {
-#pragma unroll
-    for (int i = 0; i < TB; ++i) {
-      const int k = k0 + i * TS;
-      if (k >= a.K) break;
-#pragma unroll
-      for (int r = 0; r < G; ++r) {
-        const Philox4 p = philox4x32_10((uint32_t)base + r * LN + ln, g_hi, (uint32_t)(k + a.trial0), a.use,
-                                        (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
-#pragma unroll
-        for (int q = 0; q < 4; ++q) cnt[r][q] += sr_up(F[r][q], philox_word(p, q));
-      }
-    }
-  }
+  blk.count(F, cnt, a.K, a.trial0, a.use, a.seed);
   uint2 out[G];
+  if (!blk.merge(cnt, out)) return;
 #pragma unroll
-  for (int r = 0; r < G; ++r) out[r] = make_uint2(cnt[r][0] | (cnt[r][1] << 16), cnt[r][2] | (cnt[r][3] << 16));
-  if constexpr (TS > 1) {  // K <= 4096: the packed 16-bit sums do not carry into each other
-    __shared__ uint32_t red[2][LN * G];
-    for (int i = tid; i < 2 * LN * G; i += NT) (&red[0][0])[i] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < G; ++r) {
-      atomicAdd(&red[0][r * LN + ln], out[r].x);
-      atomicAdd(&red[1][r * LN + ln], out[r].y);
-    }
-    __syncthreads();
-    if (part != 0) return;
-#pragma unroll
-    for (int r = 0; r < G; ++r) out[r] = make_uint2(red[0][r * LN + ln], red[1][r * LN + ln]);
-  }
-#pragma unroll
-  for (int r = 0; r < G; ++r) {
-    const uint64_t g = base + r * LN + ln;
-    if (g < ngroups) *(uint2*)(a.counts + 4 * g) = out[r];
-  }
+  for (int r = 0; r < G; ++r)
+    if (blk.group(r) < ngroups) *(uint2*)(a.counts + 4 * blk.group(r)) = out[r];
 }
 
 // With weights. Block: 256 threads = 64 column groups (4 columns each) x 4 row lanes, 8 rows per
@@ -492,15 +453,12 @@ bs_status launch_store(const void* x, bs_dtype xt, int64_t n, int fmt, int mode,
     // amax runs with a caller's scale too: it flags NaN / infinity (no codes then) and reports the
     // tensor's amax to a delayed-scaling caller's history; the caller's scale replaces only s
     if (n > 0) {
-      // four blocks per CU, each streaming a contiguous range with eight 16-byte loads in flight
-      // per thread; the per-block atomics stay few (same-address atomics serialize)
-      const int64_t want = (n / (16 / (xt == BS_F32 ? 4 : 2)) + 255) / 256 + 1;
-      const int blocks = (int)(want < 1024 ? want : 1024);
+      const int blocks = amax_blocks(n / (16 / (xt == BS_F32 ? 4 : 2)));
       ProfScope prof("amax", st);
       if (xt == BS_F32)
-        amax_kernel<float><<<blocks, 256, 0, st>>>((const float*)x, n, (uint32_t*)&diag->amax);
+        amax_kernel<float><<<blocks, 256, 0, st>>>((const float*)x, n, (uint32_t*)&diag->amax, 1);
       else
-        amax_kernel<u16><<<blocks, 256, 0, st>>>((const u16*)x, n, (uint32_t*)&diag->amax);
+        amax_kernel<u16><<<blocks, 256, 0, st>>>((const u16*)x, n, (uint32_t*)&diag->amax, 1);
     }
   }
   finalize_scale_kernel<<<1, 64, 0, st>>>(diag, scale_in, scale_out, f.fmax);
@@ -529,32 +487,15 @@ bs_status launch_store(const void* x, bs_dtype xt, int64_t n, int fmt, int mode,
   return BS_OK;
 }
 
-template <typename X, int G, int TS>
-static bs_status launch_fresh_flat(const FreshArgs<X>& a, hipStream_t st) {
-  constexpr int NT = TS > 4 ? 64 * TS : 256;
-  const int64_t per = (int64_t)NT / TS * G, blocks = ((a.T * a.d) / 4 + per - 1) / per;
-  if (blocks > 0x7FFFFFFF) return BS_ESHAPE;
-  fresh_count_kernel<X, G, TS><<<(unsigned)blocks, NT, 0, st>>>(a);
-  return BS_OK;
-}
-
 template <typename X>
 bs_status launch_fresh_count_t(const FreshArgs<X>& a, int mode, hipStream_t st) {
   if (a.T == 0) return BS_OK;
   ProfScope prof(mode == FC_COUNT ? "fresh_count" : (mode == FC_COLSUM ? "fresh_count_se" : "fresh_count_kappa"), st);
   bs_status rc = BS_OK;
   if (mode == FC_COUNT) {
-    // waves of the chip's 1024 SIMDs: 8 groups per thread (the set-up paid once for all of them)
-    // while that gives two waves each; fewer groups per thread, then 4 and 16 trial parts, below
-    const int64_t waves = (a.T * a.d) / 4 / 64;  // of one group per thread
-    if (waves >= 8 * 2048)
-      rc = launch_fresh_flat<X, 8, 1>(a, st);
-    else if (waves >= 2 * 2048 || a.K < 4)
-      rc = launch_fresh_flat<X, 2, 1>(a, st);
-    else if (waves >= 512 || a.K < 16)
-      rc = launch_fresh_flat<X, 2, 4>(a, st);
-    else
-      rc = launch_fresh_flat<X, 1, 16>(a, st);
+    rc = launch_fresh_flat(a.T * a.d, a.K, [&](auto g, auto ts, unsigned blocks, int nt) {
+      fresh_count_kernel<X, decltype(g)::value, decltype(ts)::value><<<blocks, nt, 0, st>>>(a);
+    });
   } else if (mode == FC_COLSUM) {
     // 64-column blocks with 4 or 8 trial parts where 256-column blocks leave SIMDs idle
     const unsigned rt = (unsigned)((a.T + 31) / 32);
@@ -585,20 +526,17 @@ bs_status launch_fresh_count(const float* u, int64_t T, int64_t d, int fmt, cons
 bs_status launch_amax_f32(const float* x, int64_t n, uint32_t* out, hipStream_t st) {
   if (n < 0 || (n > 0 && (!x || !out))) return BS_EINVAL;
   if (n == 0) return BS_OK;
-  const int64_t want = (n / 4 + 255) / 256 + 1;
-  amax_kernel<float><<<(int)(want < 1024 ? want : 1024), 256, 0, st>>>(x, n, out);
+  amax_kernel<float><<<amax_blocks(n / 4), 256, 0, st>>>(x, n, out, AMAX_SLOTS);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }
 bs_status launch_amax_bf16(const u16* x, int64_t n, uint32_t* out, hipStream_t st, bool finite) {
   if (n < 0 || (n > 0 && (!x || !out))) return BS_EINVAL;
   if (n == 0) return BS_OK;
-  const int64_t want = (n / 8 + 255) / 256 + 1;
-  const int blocks = (int)(want < 1024 ? want : 1024);
   if (finite)
-    amax_kernel<u16, true><<<blocks, 256, 0, st>>>(x, n, out);
+    amax_kernel<u16, true><<<amax_blocks(n / 8), 256, 0, st>>>(x, n, out, AMAX_SLOTS);
   else
-    amax_kernel<u16><<<blocks, 256, 0, st>>>(x, n, out);
+    amax_kernel<u16><<<amax_blocks(n / 8), 256, 0, st>>>(x, n, out, AMAX_SLOTS);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }

@@ -68,6 +68,24 @@ def test_grid_widths_and_policy_order(lib, bits):
     assert torch.equal(out["dW"]["mean"][0], out["dW"]["mean"][3])
 
 
+@pytest.mark.parametrize("T,d,n,K,shift", [
+    (33, 40, 72, 3, 0),      # fewer trials than parts; a ragged 256-column gain block
+    (70, 64, 40, 20, 0),     # 16 trial parts, uneven; two gain chunks and a ragged third
+    (700, 264, 16, 6, 0),    # two groups per thread in 4 trial parts
+    (90, 48, 24, 7, 1),      # 2-byte aligned X, W and dY: the element-wise loads and transposes
+])
+def test_bf16_operands_as_fp16_splits(lib, T, d, n, K, shift):
+    """bf16 inputs enter the contractions as scaled fp16 (u_q and the residuals as two terms) and the N bias
+    is the sum of the U and R+e biases; every split of the trials over a block."""
+    X, g, W, dY = synth.rmsnorm_linear_inputs(T, d, n, torch.bfloat16, 8)
+    place = lambda t: torch.cat((torch.zeros(shift, dtype=t.dtype), t.reshape(-1))).cuda()[shift:].view(t.shape)
+    print(f"[grid_store] fp16 T={T} d={d} n={n} K={K} shift={shift}", flush=True)
+    out = lib.rmsnorm_linear_grid(place(X), g.cuda(), place(W), place(dY), bits=6, K=K, seed=T, store_id=3)
+    torch.cuda.synchronize()
+    ref = gs.check(X.float().numpy(), g.numpy(), W.float().numpy(), dY.float().numpy(), bits=6, K=K, seed=T, store_id=3)
+    compare(lib, out, ref, gs.POLICIES, d, n)
+
+
 @pytest.mark.slow
 def test_full_size_sampled_entries(lib):
     """X [8192, 1024] bf16, W [1024, 4096], K = 256 (the benchmark's launch): every code and step,
