@@ -219,7 +219,8 @@ def diag_dict(d):
 
 
 def new_diag(device):
-    return torch.zeros(16, dtype=torch.uint8, device=device)
+    # every call that takes one overwrites it completely
+    return torch.empty(16, dtype=torch.uint8, device=device)
 
 
 # ----------------------------------------------------------------------------------
@@ -641,7 +642,7 @@ def decoder_layer_policy(x, p, dOut, *, B, S, H, eps=1e-5, fmt="e4m3", fwd_mode=
            "codes_O": torch.empty(B, H, S, d // H, dtype=torch.uint8, device=dev),
            "codes_u2": torch.empty(T, d, dtype=torch.uint8, device=dev),
            "codes_a": torch.empty(T, F, dtype=torch.uint8, device=dev),
-           "scales": e(4), "diags": torch.zeros(4, 16, dtype=torch.uint8, device=dev),
+           "scales": e(4), "diags": torch.empty(4, 16, dtype=torch.uint8, device=dev),
            "table_raw": torch.empty(len(LAYER_ROWS), 3, 3, dtype=torch.float64, device=dev)}
     grads = LayerGrads(*[out[k].data_ptr() for k in ("dx", "dgain1", "dWqkv", "dWo", "dgain2", "dWg", "dWu", "dWd")])
     stores = LayerStores(*[out[k].data_ptr() for k in ("codes_u1", "codes_O", "codes_u2", "codes_a", "scales")])

@@ -110,20 +110,25 @@ inline int amax_blocks(int64_t nvec) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(1024, std::max<int64_t>(nvec / 2048, std::min<int64_t>(64, (nvec + 255) / 256))));
 }
 
-__global__ void finalize_scale_kernel(bs_diag* diag, const float* scale_in, float* scale_out, float fmax) {
-  if (threadIdx.x != 0) return;
-  const uint32_t bits = __float_as_uint(diag->amax);
-  const bool bad = bits >= 0x7F800000u;
-  diag->nonfinite = bad ? 1u : 0u;
-  float s;
-  if (scale_in) {
-    s = *scale_in;
-  } else {
-    const float amax = diag->amax;
-    s = (amax == 0.0f || bad) ? 1.0f : __fdiv_rn(amax, fmax);
+// The store's scale and flag from the amax in diag: amax / FMAX (1 for an all-zero or non-finite
+// tensor), or the caller's. `write`: record them (one thread of the launch; nothing of the launch
+// reads the fields it writes).
+__device__ __forceinline__ float store_scale(bs_diag* diag, const float* scale_in, float* scale_out, float fmax,
+                                             bool write, bool& bad) {
+  const float amax = diag->amax;
+  bad = __float_as_uint(amax) >= 0x7F800000u;
+  const float s = scale_in ? *scale_in : ((amax == 0.0f || bad) ? 1.0f : __fdiv_rn(amax, fmax));
+  if (write) {
+    diag->nonfinite = bad ? 1u : 0u;
+    diag->scale = s;
+    if (scale_out) *scale_out = s;
   }
-  diag->scale = s;
-  if (scale_out) *scale_out = s;
+  return s;
+}
+
+__global__ void finalize_scale_kernel(bs_diag* diag, const float* scale_in, float* scale_out, float fmax) {
+  bool bad;
+  if (threadIdx.x == 0) store_scale(diag, scale_in, scale_out, fmax, true, bad);
 }
 
 // gfx950's conversion instructions to the OCP formats ("fp8" = E4M3, "bf8" = E5M2), on values
@@ -184,13 +189,16 @@ __device__ __forceinline__ uint32_t codes4(const float* y, const uint32_t* R) {
 // Groups of eight consecutive elements (two Philox groups), grid-stride: one 16- or 32-byte load
 // and an 8-byte store of the codes per group. The last group of a ragged tensor takes the
 // element-wise path. A thread takes several groups, so that the per-wave set-up is paid once
-// per several groups.
+// per several groups. Every block forms the scale from the amax (a launch of one thread for it cost
+// 5 us of a 137 us store of 16384 x 8192).
 template <typename T, int FMT, int MODE>
-__global__ __launch_bounds__(256) void quantize_kernel(const T* __restrict__ x, int64_t n, float fmax,
-                                                       bs_diag* __restrict__ diag, uint8_t* __restrict__ codes,
-                                                       uint64_t seed, uint32_t trial, uint32_t use) {
-  if (diag->nonfinite) return;
-  const double rs = 1.0 / (double)diag->scale;
+__global__ __launch_bounds__(256) void quantize_kernel(const T* __restrict__ x, int64_t n, float fmax, bs_diag* diag,
+                                                       const float* scale_in, float* scale_out,
+                                                       uint8_t* __restrict__ codes, uint64_t seed, uint32_t trial,
+                                                       uint32_t use) {
+  bool bad;
+  const double rs = 1.0 / (double)store_scale(diag, scale_in, scale_out, fmax, blockIdx.x == 0 && threadIdx.x == 0, bad);
+  if (bad) return;
   const int64_t ngroups = (n + 7) / 8, stride = (int64_t)gridDim.x * blockDim.x;
   uint32_t nsat = 0;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < ngroups; t += stride) {
@@ -461,14 +469,15 @@ bs_status launch_store(const void* x, bs_dtype xt, int64_t n, int fmt, int mode,
         amax_kernel<u16><<<blocks, 256, 0, st>>>((const u16*)x, n, (uint32_t*)&diag->amax, 1);
     }
   }
-  finalize_scale_kernel<<<1, 64, 0, st>>>(diag, scale_in, scale_out, f.fmax);
-  if (n > 0 && codes) {  // codes == nullptr: the scale only
+  if (n == 0 || !codes) {  // codes == nullptr: the scale only
+    finalize_scale_kernel<<<1, 64, 0, st>>>(diag, scale_in, scale_out, f.fmax);
+  } else {
     // up to 8192 blocks (32 waves per CU), each thread then taking several groups of eight
     const int64_t threads = (n + 7) / 8;
     const unsigned blocks = (unsigned)std::min<int64_t>((threads + 255) / 256, 8192);
     ProfScope prof("quantize", st);
 #define QK(T, FM, M) \
-  quantize_kernel<T, FM, M><<<blocks, 256, 0, st>>>((const T*)x, n, f.fmax, diag, codes, seed, trial, use)
+  quantize_kernel<T, FM, M><<<blocks, 256, 0, st>>>((const T*)x, n, f.fmax, diag, scale_in, scale_out, codes, seed, trial, use)
 #define QKF(T)                                              \
   if (fmt == BS_E5M2) {                                     \
     if (mode == BS_SR) QK(T, BS_E5M2, BS_SR); else QK(T, BS_E5M2, BS_RNE); \
