@@ -148,14 +148,6 @@ __device__ __forceinline__ uint32_t cvt_sr1(float a, uint32_t R, uint32_t old) {
                         : (uint32_t)__builtin_amdgcn_cvt_sr_fp8_f32(a, (int)R, (int)old, BYTE);
 }
 
-// y = fl32(x / s) clamped to [-FMAX, FMAX] (sign of zero kept); counts the wave's clamped
-// values (a ballot and a scalar popcount: the count is wave-uniform)
-__device__ __forceinline__ float scaled_clamped(float x, double rs, float fmax, uint32_t& nsat) {
-  const float y = div_scale(x, rs);
-  nsat += (uint32_t)__popcll(__ballot(fabsf(y) > fmax));
-  return __builtin_amdgcn_fmed3f(y, -fmax, fmax);
-}
-
 // stochastic rounding of one clamped value by the integer codec
 __device__ __forceinline__ uint32_t sr_code(float y, uint32_t R, F8 f) {
   const Bracket b = f8_bracket(fabsf(y), f);
@@ -172,10 +164,8 @@ __device__ __forceinline__ uint32_t codes4(const float* y, const uint32_t* R) {
     w = cvt_sr1<FMT, 3>(y[3], R[3], w);
     const F8 f = f8_format(FMT);
     const float min_normal = __uint_as_float((uint32_t)(128 - f.bias) << 23);
-    bool sub = false;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) sub |= fabsf(y[q]) < min_normal && y[q] != 0.0f;
-    if (sub) {
+    // the smallest of the four decides (a zero takes the branch too, where it changes nothing)
+    if (fminf(fminf(fabsf(y[0]), fabsf(y[1])), fminf(fabsf(y[2]), fabsf(y[3]))) < min_normal) {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         if (fabsf(y[q]) < min_normal && y[q] != 0.0f)
@@ -232,8 +222,21 @@ __global__ __launch_bounds__(256) void quantize_kernel(const T* __restrict__ x, 
       R[4] = p1.w0; R[5] = p1.w1; R[6] = p1.w2; R[7] = p1.w3;
     }
     float y[8];
+    float big = 0.0f;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) y[q] = scaled_clamped(xv[q], rs, fmax, nsat);  // padding zeros never clamp
+    for (int q = 0; q < 8; ++q) {
+      y[q] = div_scale(xv[q], rs);
+      big = fmaxf(big, fabsf(y[q]));
+    }
+    // clamped to [-FMAX, FMAX] (sign of zero kept) and counted (a ballot and a scalar popcount: the
+    // count is wave-uniform) only where one of the wave's values needs it; padding zeros never do
+    if (__any(!(big <= fmax))) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        nsat += (uint32_t)__popcll(__ballot(fabsf(y[q]) > fmax));
+        y[q] = __builtin_amdgcn_fmed3f(y[q], -fmax, fmax);
+      }
+    }
     const uint32_t lo = codes4<FMT, MODE>(y, R), hi = codes4<FMT, MODE>(y + 4, R + 4);
     if (vec) {
       *(uint2*)(codes + e0) = make_uint2(lo, hi);
