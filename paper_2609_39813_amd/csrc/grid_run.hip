@@ -43,13 +43,17 @@ __device__ __forceinline__ GridBracket grid_bracket(float u, float s, float M) {
 }
 
 // fl32(q s) of the code sign * m
-__device__ __forceinline__ float grid_value(float m, bool neg, float s) { return (neg ? -m : m) * s; }
+__device__ __forceinline__ float grid_value(float m, bool neg, float s) {
+#pragma clang fp contract(off)
+  return (neg ? -m : m) * s;
+}
 
 // one wave per token: the step, the forward's codes (trial 0), u_q and e_U = u - u_q
 __global__ __launch_bounds__(256) void grid_store_kernel(const float* __restrict__ u, int64_t T, int64_t d, int bits,
                                                          uint64_t seed, uint32_t use, int8_t* __restrict__ codes,
                                                          float* __restrict__ step, float* __restrict__ uq,
                                                          float* __restrict__ eU, bs_diag* __restrict__ diag) {
+#pragma clang fp contract(off)  // e_U is u less the rounded q s, not a fused u - q s
   const int lane = threadIdx.x & 63;
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= T) return;
@@ -98,6 +102,7 @@ __global__ __launch_bounds__(fresh_nt(TS)) void grid_fresh_kernel(const float* _
                                                                   const float* __restrict__ step, int64_t T, int64_t d,
                                                                   int bits, uint64_t seed, uint32_t use, int K,
                                                                   float* __restrict__ eE) {
+#pragma clang fp contract(off)  // the grid values are rounded
   const FreshBlock<G, TS> blk;
   const uint64_t ngroups = (uint64_t)(T * d) >> 2;
   const float M = (float)((1 << (bits - 1)) - 1);
