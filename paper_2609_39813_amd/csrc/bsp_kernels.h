@@ -28,6 +28,7 @@ struct GemmArgs {
   // the pipelined kernel only)
   int batch = 1;
   int64_t sA = 0, sB = 0, sC = 0, s_alpha2 = 0;
+  int64_t s_amax = 0;  // stride of amax over the members
 };
 
 // alpha of a launch (batch member z) with its device multipliers
@@ -142,6 +143,11 @@ struct MoveSrc {
   const float* heads[3] = {nullptr, nullptr, nullptr};
   int64_t S = 0, H = 0, d = 0;
 };
+// Moves side by side in one launch (launch_split_move): nz moves, move z's arrays z strides on.
+struct MoveSpan {
+  int nz = 1;
+  int64_t s_src = 0, s_t = 0, s_rows = 0, s_amax = 0, s_inv = 0;  // source, tM, rows, amax_a, inv_out
+};
 // The scaled two-term fp16 planes (scale from sc, F16Scale) of a move m, from one read: tM =
 // transposed planes of m (tM_p[c*ldo + r], rows R..ldo zero), tS (with base non-null) those of
 // base + m (base [R][C] with leading dimension ldb), rows (nullable) the row-major planes
@@ -149,7 +155,7 @@ struct MoveSrc {
 // 16-byte aligned inputs and transposed planes, 8-byte aligned row planes (BS_EINVAL otherwise).
 bs_status launch_split_move(const MoveSrc& m, const float* base, int64_t ldb, int64_t R, int64_t C, F16Scale sc,
                             u16* const* tM, u16* const* tS, int64_t ldo, u16* const* rows, int64_t ldr,
-                            hipStream_t st);
+                            hipStream_t st, MoveSpan z = MoveSpan{});
 // out = fp16(in 2^e) of a bf16 tensor with e = f16_scale_exp of the max held in slots (an
 // AMAX_SLOTS array), 2^-e to inv_out (nullable). Exact where |in| 2^e >= 2^-17 (fp16 subnormal
 // spacing); below, the error is at most 2^-25 2^-e.

@@ -21,6 +21,16 @@ struct StoreRead {
   uint32_t trial, use;
 };
 
+// Trials side by side in one launch: nz trials, trial z reading and writing its own arrays (the
+// moves, outputs and partial sums) z strides further on and drawing trial + z.
+struct TrialSpan {
+  int nz = 1;
+  int64_t s = 0;       // stride of the [T][d] (D use: [rows][64]) moves and outputs
+  int64_t s_rows = 0;  // D use: stride of its row output
+  int64_t s_part = 0;  // gain use: stride of the partial sums
+  int64_t s_amax = 0;  // stride of the slot arrays
+};
+
 // Gain use of a normalization store (Eq. norm-uses): column partial sums over 16-row tiles of
 // z_g (du + ddu) - z du = (z_g - z)(du + ddu) + z ddu, z = fl32(X r) the original, z_g what the
 // letter reads (z; s val(C) / gain; s val(new rounding) / gain). ddu nullable (the incoming
@@ -35,6 +45,7 @@ struct AlluGainArgs {
   const float* ddu; // nullable [T][d]
   int64_t T, d;
   double* part;     // [ceil(T / 16)][d]
+  TrialSpan z;
 };
 template <typename XT>
 bs_status launch_allu_gain(const AlluGainArgs<XT>& a, hipStream_t st);
@@ -54,6 +65,7 @@ struct AlluDxArgs {
   int64_t T, d;
   float* out;        // [T][d]
   uint32_t* amax = nullptr;  // nullable: slots (AMAX_SLOTS) raised to max |out|
+  TrialSpan z;               // ddu, add, out and amax per trial
 };
 template <typename XT>
 bs_status launch_allu_dx(const AlluDxArgs<XT>& a, hipStream_t st);
@@ -66,7 +78,7 @@ template <typename XT>
 struct AlluGainDxArgs {
   AlluDxArgs<XT> dx;  // the normalization-input use (dx.rd its read of the store)
   StoreRead rd_g;     // the gain use's read of the same store (rd_g.x == dx.rd.x)
-  double* part;       // [ceil(T / 16)][d]
+  double* part;       // [ceil(T / 16)][d]; the trials of dx.z
 };
 template <typename XT>
 bs_status launch_allu_gain_dx(const AlluGainDxArgs<XT>& a, hipStream_t st);
@@ -81,6 +93,7 @@ struct AlluDArgs {
   float* out;        // [rows]
   uint32_t* amax = nullptr;  // nullable: slots (AMAX_SLOTS) raised to max |out|
   int ddo_heads = 0, ddo_S = 0;  // ddO token-major: heads and sequence length (row = (b H + h) S + s)
+  TrialSpan z;                   // ddO, out and amax per trial
 };
 bs_status launch_allu_d(const AlluDArgs& a, hipStream_t st);
 
@@ -88,5 +101,25 @@ bs_status launch_allu_d(const AlluDArgs& a, hipStream_t st);
 bs_status launch_trial_mean(const float* d1, const double* S1, int K, int64_t m, float* out, hipStream_t st);
 // out[i] = v for n floats (any v, NaN included)
 bs_status launch_fill(float* out, int64_t n, float v, hipStream_t st);
+// Copies (src) and fills (src null: the value v) of whole arrays, every job in one launch.
+constexpr int COPY_MAX = 48;
+struct CopyJob {
+  float* dst;
+  const float* src;
+  float v;
+  int64_t n;
+};
+struct CopyBatch {
+  CopyJob job[COPY_MAX];
+  int count = 0;
+  uint32_t first[COPY_MAX];  // set by launch_copy_batch
+  bool add(float* dst, const float* src, float v, int64_t n) {
+    if (!dst || n <= 0) return true;
+    if (count >= COPY_MAX) return false;
+    job[count++] = CopyJob{dst, src, v, n};
+    return true;
+  }
+};
+bs_status launch_copy_batch(CopyBatch& b, hipStream_t st);
 
 }  // namespace bsp

@@ -45,6 +45,16 @@ __device__ __forceinline__ void load4(const u16* p, int64_t e, float (&v)[4]) {
   v[3] = bf16_to_f32((u16)(q.y >> 16));
 }
 
+template <typename XT>
+__device__ __forceinline__ void at_trial(AlluDxArgs<XT>& a, int z) {
+  const int64_t o = z * a.z.s;
+  if (a.ddu) a.ddu += o;
+  if (a.add) a.add += o;
+  a.out += o;
+  a.rd.trial += (uint32_t)z;
+  if (a.amax) a.amax += z * a.z.s_amax;
+}
+
 constexpr int ALLU_RT = 16;  // rows per tile of the gain use's partial sums
 
 // block: 256 threads x 4 consecutive columns (1024 columns), rows [16 y, 16 y + 16)
@@ -52,6 +62,9 @@ template <typename XT>
 __global__ __launch_bounds__(256) void allu_gain_kernel(AlluGainArgs<XT> a) {
   const int64_t j0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (j0 >= a.d) return;
+  if (a.ddu) a.ddu += blockIdx.z * a.z.s;
+  a.part += blockIdx.z * a.z.s_part;
+  a.rd.trial += blockIdx.z;
   const int64_t t0 = (int64_t)blockIdx.y * ALLU_RT;
   const float s = a.rd.scale ? *a.rd.scale : 1.0f;
   const double rs = 1.0 / (double)s;
@@ -188,6 +201,7 @@ __device__ __forceinline__ float allu_dx_row(const AlluDxArgs<XT>& a, int64_t t,
 }
 template <typename XT, int NI>
 __global__ __launch_bounds__(256) void allu_dx_kernel(AlluDxArgs<XT> a) {
+  at_trial(a, blockIdx.y);
   const int lane = threadIdx.x & 63;
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const float mx = t < a.T ? allu_dx_row<XT, NI>(a, t, lane) : 0.0f;  // uniform per wave
@@ -199,6 +213,9 @@ __global__ __launch_bounds__(256) void allu_dx_kernel(AlluDxArgs<XT> a) {
 template <typename XT, int NI>
 __global__ __launch_bounds__(256, 3) void allu_gain_dx_kernel(AlluGainDxArgs<XT> a) {
   __shared__ double red[4][256 * NI];  // per wave, the gain terms of its rows by column
+  at_trial(a.dx, blockIdx.y);
+  a.rd_g.trial += blockIdx.y;
+  a.part += blockIdx.y * a.dx.z.s_part;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int j = lane; j < 256 * NI; j += 64) red[w][j] = 0.0;  // each lane's own columns below
   float mx = 0.0f;
@@ -214,6 +231,10 @@ __global__ __launch_bounds__(256, 3) void allu_gain_dx_kernel(AlluGainDxArgs<XT>
 
 // 16 lanes per row of 64, 4 elements each; 16 rows per block
 __global__ __launch_bounds__(256) void allu_d_kernel(AlluDArgs a) {
+  if (a.ddO) a.ddO += blockIdx.y * a.z.s;
+  a.out += blockIdx.y * a.z.s_rows;
+  a.rd.trial += blockIdx.y;
+  if (a.amax) a.amax += blockIdx.y * a.z.s_amax;
   const int64_t row = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
   const int sub = threadIdx.x & 15;
   const bool ok = row < a.rows;
@@ -253,6 +274,27 @@ __global__ __launch_bounds__(256) void fill_kernel(float* __restrict__ out, int6
     out[i] = v;
 }
 
+// job j's 4096-element pieces are blocks first[j] .. first[j + 1] - 1. Bound by memory; one launch
+// for the 48 arrays of the small layer check (22 us; its copies and fills one by one took about 195).
+__global__ __launch_bounds__(256) void copy_batch_kernel(CopyBatch b) {
+  int j = 0;
+  while (j + 1 < b.count && blockIdx.x >= b.first[j + 1]) ++j;  // uniform
+  const CopyJob c = b.job[j];
+  const int64_t e0 = (int64_t)(blockIdx.x - b.first[j]) * 4096;
+  const int64_t e1 = min(c.n, e0 + 4096);
+  if (e1 - e0 == 4096 && ((uintptr_t)c.dst | (uintptr_t)c.src) % 16 == 0) {
+    float4* dst = (float4*)(c.dst + e0) + threadIdx.x;
+    const float4* src = (const float4*)(c.src ? c.src + e0 : nullptr) + threadIdx.x;
+    float4 r[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = c.src ? src[256 * i] : make_float4(c.v, c.v, c.v, c.v);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dst[256 * i] = r[i];
+    return;
+  }
+  for (int64_t i = e0 + threadIdx.x; i < e1; i += 256) c.dst[i] = c.src ? c.src[i] : c.v;
+}
+
 unsigned blocks1d(int64_t n) {
   const int64_t b = (n + 255) / 256;
   return (unsigned)(b < 8192 ? (b > 0 ? b : 1) : 8192);
@@ -264,7 +306,7 @@ template <typename XT>
 bs_status launch_allu_gain(const AlluGainArgs<XT>& a, hipStream_t st) {
   if (a.T <= 0 || a.d <= 0) return BS_OK;
   if (a.d & 3) return BS_ESHAPE;
-  const dim3 grid((unsigned)((a.d + 1023) / 1024), (unsigned)((a.T + ALLU_RT - 1) / ALLU_RT));
+  const dim3 grid((unsigned)((a.d + 1023) / 1024), (unsigned)((a.T + ALLU_RT - 1) / ALLU_RT), (unsigned)a.z.nz);
   allu_gain_kernel<XT><<<grid, 256, 0, st>>>(a);
   BS_CHECK_LAUNCH();
   return BS_OK;
@@ -276,7 +318,7 @@ template <typename XT>
 bs_status launch_allu_dx(const AlluDxArgs<XT>& a, hipStream_t st) {
   if (a.T <= 0 || a.d <= 0) return BS_OK;
   if (a.d & 3) return BS_ESHAPE;
-  const unsigned grid = (unsigned)((a.T + 3) / 4);
+  const dim3 grid((unsigned)((a.T + 3) / 4), (unsigned)a.z.nz);
   if (a.d <= 256)
     allu_dx_kernel<XT, 1><<<grid, 256, 0, st>>>(a);
   else if (a.d <= 512)
@@ -299,11 +341,11 @@ bs_status launch_allu_gain_dx(const AlluGainDxArgs<XT>& a, hipStream_t st) {
   if (a.rd_g.x != x.rd.x || a.rd_g.codes != x.rd.codes || a.rd_g.scale != x.rd.scale || a.rd_g.letter != x.rd.letter)
     return BS_EINVAL;
   if (x.d > 1024) {
-    const AlluGainArgs<XT> g{x.X, x.rstd, x.gain, a.rd_g, x.du, x.ddu, x.T, x.d, a.part};
+    const AlluGainArgs<XT> g{x.X, x.rstd, x.gain, a.rd_g, x.du, x.ddu, x.T, x.d, a.part, x.z};
     const bs_status e = launch_allu_gain(g, st);
     return e != BS_OK ? e : launch_allu_dx(x, st);
   }
-  const unsigned grid = (unsigned)((x.T + ALLU_RT - 1) / ALLU_RT);
+  const dim3 grid((unsigned)((x.T + ALLU_RT - 1) / ALLU_RT), (unsigned)x.z.nz);
   if (x.d <= 256)
     allu_gain_dx_kernel<XT, 1><<<grid, 256, 0, st>>>(a);
   else if (x.d <= 512)
@@ -319,7 +361,7 @@ template bs_status launch_allu_gain_dx<u16>(const AlluGainDxArgs<u16>&, hipStrea
 bs_status launch_allu_d(const AlluDArgs& a, hipStream_t st) {
   if (a.ddo_heads < 0 || (a.ddo_heads > 0 && (a.ddo_S <= 0 || a.rows % a.ddo_S))) return BS_EINVAL;
   if (a.rows <= 0) return BS_OK;
-  allu_d_kernel<<<(unsigned)((a.rows + 15) / 16), 256, 0, st>>>(a);
+  allu_d_kernel<<<dim3((unsigned)((a.rows + 15) / 16), (unsigned)a.z.nz), 256, 0, st>>>(a);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }
@@ -327,6 +369,18 @@ bs_status launch_allu_d(const AlluDArgs& a, hipStream_t st) {
 bs_status launch_trial_mean(const float* d1, const double* S1, int K, int64_t m, float* out, hipStream_t st) {
   if (m <= 0) return BS_OK;
   trial_mean_kernel<<<blocks1d(m), 256, 0, st>>>(d1, S1, K, m, out);
+  BS_CHECK_LAUNCH();
+  return BS_OK;
+}
+
+bs_status launch_copy_batch(CopyBatch& b, hipStream_t st) {
+  int64_t blocks = 0;
+  for (int j = 0; j < b.count; ++j) {
+    b.first[j] = (uint32_t)blocks;
+    blocks += (b.job[j].n + 4095) / 4096;
+    if (blocks > 0x7FFFFFFF) return BS_ESHAPE;
+  }
+  if (blocks > 0) copy_batch_kernel<<<(unsigned)blocks, 256, 0, st>>>(b);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }

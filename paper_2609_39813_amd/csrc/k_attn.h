@@ -84,6 +84,10 @@ struct AttnBwdArgs {
   const u16 *Qt16 = nullptr, *Kt16 = nullptr;
   const float* f16_inv = nullptr;
   uint32_t* amax = nullptr;  // nullable: slots (AMAX_SLOTS) raised to max |.| of dQ_ref, dK_ref, dV
+  // fp16 operands: nz incoming gradients side by side in one launch, gradient z's planes, D, f16_inv,
+  // outputs and amax z strides on
+  int nz = 1;
+  int64_t z_dop = 0, z_dot = 0, z_rows = 0, z_inv = 0, z_out = 0, z_amax = 0;
 };
 
 bs_status launch_attn_fwd(const AttnArgs& a, int B, int H, hipStream_t st);
@@ -96,14 +100,21 @@ bs_status launch_attn_split(const float* dO32, int BH, int S, int Sp, u16* const
                             hipStream_t st);
 // the two fp16 planes (split2_f16) of dO32 2^e, e from the max in slots (an AMAX_SLOTS array,
 // f16_scale_exp), and their transposes (head-major [BH][S][64] planes); 2^-e to inv_out. dO32 is
-// head-major, or with htok > 0 token-major [BH / htok][S][htok 64] (htok heads)
+// head-major, or with htok > 0 token-major [BH / htok][S][htok 64] (htok heads). nz gradients side by
+// side: strides of dO32, dOp, dOt, slots, inv_out
+struct SplitSpan {
+  int nz = 1;
+  int64_t s_x = 0, s_p = 0, s_t = 0, s_amax = 0, s_inv = 0;
+};
 bs_status launch_attn_split_f16(const float* dO32, int BH, int S, int Sp, int htok, const uint32_t* slots,
-                                float* inv_out, u16* const* dOp, u16* const* dOt, hipStream_t st);
-// dS's scale of the fp16 backward (f16_inv above, entries 4..6 from entries 2, 3): 2^s from the
+                                float* inv_out, u16* const* dOp, u16* const* dOt, hipStream_t st,
+                                SplitSpan z = SplitSpan{});
+// dS's scale of the fp16 backward (f16_inv above, entries 1..6): 2^s from the
 // bound 64 max|dO| max|V| + max|D| of |dS| = P |dP - D| (P <= 1, 64 terms per dP), the maxima
-// held in the slot arrays (AMAX_SLOTS) sdO, sV, sD
-bs_status launch_attn_f16_scales(const uint32_t* sdO, const uint32_t* sV, const uint32_t* sD, float* f16_inv,
-                                 hipStream_t st);
+// held in the slot arrays (AMAX_SLOTS) sdO, sV, sD; entries 1..3 copied from vqk (2^-f, 2^-q, 2^-k). nz
+// gradients: sdO and sD s_amax, f16_inv s_inv apart
+bs_status launch_attn_f16_scales(const uint32_t* sdO, const uint32_t* sV, const uint32_t* sD, const float* vqk,
+                                 float* f16_inv, hipStream_t st, int nz = 1, int64_t s_amax = 0, int64_t s_inv = 0);
 bs_status launch_attn_bwd(const AttnBwdArgs& a, int B, int H, hipStream_t st);
 
 }  // namespace bsp

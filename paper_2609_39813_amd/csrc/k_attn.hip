@@ -293,8 +293,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_k_kernel(AttnBwdArgs a) {
   const int k0 = kb * AT;
   const int64_t hb = (int64_t)bh * a.S * AT, tb = (int64_t)bh * AT * a.Sp, rb = (int64_t)bh * a.S;
   const int key = k0 + 16 * w + c16;
-  const float dps = H ? a.f16_inv[0] * a.f16_inv[1] : 1.0f, avs = H ? a.f16_inv[0] * 0x1p-14f : 1.0f;
-  const float dsc = H ? a.f16_inv[4] : 1.0f, dkm = H ? a.f16_inv[5] : 1.0f;
+  const int z = H ? blockIdx.z : 0;  // gradient z of the launch
+  const float* inv = a.f16_inv + z * a.z_inv;
+  const float dps = H ? inv[0] * inv[1] : 1.0f, avs = H ? inv[0] * 0x1p-14f : 1.0f;
+  const float dsc = H ? inv[4] : 1.0f, dkm = H ? inv[5] : 1.0f;
   // H: P comes out at its split's scale 2^14 (1/l scaled), and dS at its split's scale 2^s (dP's
   // multiplier and D scaled by 2^s 2^-14), so neither split multiplies per element
   const float lsc = H ? 0x1p14f : 1.0f, dpm = H ? dps * dsc * 0x1p-14f : dps, dmul = H ? dsc * 0x1p-14f : 1.0f;
@@ -316,8 +318,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_k_kernel(AttnBwdArgs a) {
   rT[0] = attn_rsrc((H ? a.Qt16 : a.Qt) + tb, (int64_t)AT * a.Sp * 2);
 #pragma unroll
   for (int i = 0; i < NDO; ++i) {
-    rR[1 + i] = attn_rsrc((NDO == 1 ? a.dO : a.dOp[i]) + hb, (int64_t)a.S * AT * 2);
-    rT[1 + i] = attn_rsrc(a.dOt[i] + tb, (int64_t)AT * a.Sp * 2);
+    rR[1 + i] = attn_rsrc((NDO == 1 ? a.dO : a.dOp[i] + z * a.z_dop) + hb, (int64_t)a.S * AT * 2);
+    rT[1 + i] = attn_rsrc(a.dOt[i] + z * a.z_dot + tb, (int64_t)AT * a.Sp * 2);
   }
   // lane l of load j (two per wave and tile) fills tile row 8 (2 w + j) + l / 8 at chunk
   // position l % 8, which holds logical chunk (l % 8) ^ (l / 8) of the row (the sw layout)
@@ -349,7 +351,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_k_kernel(AttnBwdArgs a) {
   // wave w loads row arrays NRW w .. NRW w + NRW - 1 of (m, l, D[, dD_R, dD_N, -, -, -]).
   // Queries past S, a missing dD_v and the padding (empty resources) read as zero; every wave
   // issues NL + NRW loads per query block.
-  const float* row_src[8] = {a.m, a.l, a.D_ref, BIAS ? a.dD_R : nullptr, BIAS ? a.dD_N : nullptr,
+  const float* row_src[8] = {a.m, a.l, a.D_ref + z * a.z_rows, BIAS ? a.dD_R : nullptr, BIAS ? a.dD_N : nullptr,
                              nullptr, nullptr, nullptr};
   __amdgpu_buffer_rsrc_t rq[NRW];
 #pragma unroll
@@ -510,6 +512,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_k_kernel(AttnBwdArgs a) {
     if (qb + 1 < nqb) step(qb + 1, rows1, rows0);
   }
   const float c = a.scale;
+  float *dK = a.dK_ref + z * a.z_out, *dV = a.dV + z * a.z_out;
   float mx = 0.0f;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -519,9 +522,9 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_k_kernel(AttnBwdArgs a) {
     for (int n = 0; n < 4; ++n) {
       const int64_t e = hb + (int64_t)kr * AT + 16 * n + c16;
       const float dk = c * (ak[n][r] * dkm);
-      a.dV[e] = av[n][r] * avs;
+      dV[e] = av[n][r] * avs;
       mx = fmaxf(mx, fmaxf(fabsf(dk), fabsf(av[n][r] * avs)));
-      a.dK_ref[e] = dk;
+      dK[e] = dk;
       for (int pi = 0; pi < a.n_pol; ++pi) {
         const int kind = a.pol[pi];
         const float bias = kind == BS_READ_U ? 0.0f : -c * (kind == BS_READ_R ? akr[n][r] : akn[n][r]);
@@ -530,7 +533,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_k_kernel(AttnBwdArgs a) {
       }
     }
   }
-  if (a.amax) wave_amax_to_slot(mx, a.amax);
+  if (a.amax) wave_amax_to_slot(mx, a.amax + z * a.z_amax);
 }
 
 // ------------------------------------------------------------------------------------
@@ -557,6 +560,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_kernel(AttnBwdArgs a) {
   const int64_t hb = (int64_t)bh * a.S * AT, tb = (int64_t)bh * AT * a.Sp, rb = (int64_t)bh * a.S;
   const int q = q0 + 16 * w + c16;
   const bool qok = q < a.S;
+  const int z = H ? blockIdx.z : 0;  // gradient z of the launch
+  const float* inv = a.f16_inv + z * a.z_inv;
   bf16x8 fq[2], fdo[NDO][2];
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
@@ -564,16 +569,16 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_kernel(AttnBwdArgs a) {
     fq[s] = __builtin_bit_cast(bf16x8, qok ? *(const uint4*)(a.Q + e) : make_uint4(0, 0, 0, 0));
 #pragma unroll
     for (int i = 0; i < NDO; ++i) {
-      const u16* src = NDO == 1 ? a.dO : a.dOp[i];
+      const u16* src = NDO == 1 ? a.dO : a.dOp[i] + z * a.z_dop;
       fdo[i][s] = __builtin_bit_cast(bf16x8, qok ? *(const uint4*)(src + e) : make_uint4(0, 0, 0, 0));
     }
   }
   const float mq = qok ? a.m[rb + q] : 0.0f;
   const float c2 = a.scale * kLog2e;
   const float ilq = qok ? 1.0f / a.l[rb + q] : 0.0f;
-  const float dq_ref = qok ? a.D_ref[rb + q] : 0.0f;
-  const float dps = H ? a.f16_inv[0] * a.f16_inv[1] : 1.0f;
-  const float dsc = H ? a.f16_inv[4] : 1.0f, dqm = H ? a.f16_inv[6] : 1.0f;
+  const float dq_ref = qok ? a.D_ref[z * a.z_rows + rb + q] : 0.0f;
+  const float dps = H ? inv[0] * inv[1] : 1.0f;
+  const float dsc = H ? inv[4] : 1.0f, dqm = H ? inv[6] : 1.0f;
   // H: dS comes out at its split's scale 2^s (dP's multiplier and D scaled)
   const float dpm = dps * dsc, dq_s = dq_ref * dsc;
 
@@ -688,6 +693,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_kernel(AttnBwdArgs a) {
   }
   const float c = a.scale;
   const float rk = a.ntrial > 0 ? 1.0f / sqrtf((float)a.ntrial) : 0.0f;
+  float* dQ = a.dQ_ref + z * a.z_out;
   float mx = 0.0f;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
@@ -701,7 +707,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_kernel(AttnBwdArgs a) {
       const int64_t e = hb + (int64_t)qr * AT + 16 * n + c16;
       const float dq = c * (aq[n][r] * dqm);
       const float gg = ag[n][r];
-      a.dQ_ref[e] = dq;
+      dQ[e] = dq;
       mx = fmaxf(mx, fabsf(dq));
       for (int pi = 0; G && pi < a.n_pol; ++pi) {
         const int kind = a.pol[pi];
@@ -712,7 +718,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_q_kernel(AttnBwdArgs a) {
       }
     }
   }
-  if (a.amax) wave_amax_to_slot(mx, a.amax);
+  if (a.amax) wave_amax_to_slot(mx, a.amax + z * a.z_amax);
 }
 
 // ------------------------------------------------------------------------------------
@@ -728,7 +734,17 @@ __global__ __launch_bounds__(256) void attn_prep_kernel(const X* __restrict__ x,
                                                         u16* __restrict__ xt0,
                                                         u16* __restrict__ xt1, u16* __restrict__ xt2,
                                                         u16* __restrict__ xp0, u16* __restrict__ xp1,
-                                                        u16* __restrict__ xp2) {
+                                                        u16* __restrict__ xp2, SplitSpan sp) {
+  if constexpr (H) {  // gradient z of the launch
+    const int z = blockIdx.z;
+    x += z * sp.s_x;
+    slots += z * sp.s_amax;
+    if (inv_out) inv_out += z * sp.s_inv;
+    xt0 += z * sp.s_t;
+    xt1 += z * sp.s_t;
+    xp0 += z * sp.s_p;
+    xp1 += z * sp.s_p;
+  }
   constexpr int NP = sizeof(X) == 4 ? (H ? 2 : 3) : 1;
   __shared__ u16 t[NP][AT][AT + 2];
   float scl = 1.0f;
@@ -1030,32 +1046,38 @@ bs_status launch_attn_split(const float* dO32, int BH, int S, int Sp, u16* const
   dim3 grid((unsigned)(Sp / AT), (unsigned)BH);
   ProfScope prof("attn_prep", st);
   attn_prep_kernel<float, false><<<grid, 256, 0, st>>>(dO32, S, Sp, 0, nullptr, nullptr, dOt[0], dOt[1], dOt[2],
-                                                       dOp[0], dOp[1], dOp[2]);
+                                                       dOp[0], dOp[1], dOp[2], SplitSpan{});
   BS_CHECK_LAUNCH();
   return BS_OK;
 }
-__global__ void attn_f16_scales_kernel(const uint32_t* sdO, const uint32_t* sV, const uint32_t* sD, float* inv) {
+__global__ void attn_f16_scales_kernel(const uint32_t* sdO, const uint32_t* sV, const uint32_t* sD, const float* vqk,
+                                       float* inv, int64_t s_amax, int64_t s_inv) {
   if (threadIdx.x != 0) return;
-  const float bound = 64.0f * amax_of_slots(sdO) * amax_of_slots(sV) + amax_of_slots(sD);
+  const int z = blockIdx.x;
+  inv += z * s_inv;
+  const float bound = 64.0f * amax_of_slots(sdO + z * s_amax) * amax_of_slots(sV) + amax_of_slots(sD + z * s_amax);
   const int e = f16_scale_exp(bound);
+  inv[1] = vqk[0];
+  inv[2] = vqk[1];
+  inv[3] = vqk[2];
   inv[4] = ldexpf(1.0f, e);
-  inv[5] = ldexpf(inv[2], -e);
-  inv[6] = ldexpf(inv[3], -e);
+  inv[5] = ldexpf(vqk[1], -e);
+  inv[6] = ldexpf(vqk[2], -e);
 }
-bs_status launch_attn_f16_scales(const uint32_t* sdO, const uint32_t* sV, const uint32_t* sD, float* f16_inv,
-                                 hipStream_t st) {
-  if (!sdO || !sV || !sD || !f16_inv) return BS_EINVAL;
-  attn_f16_scales_kernel<<<1, 64, 0, st>>>(sdO, sV, sD, f16_inv);
+bs_status launch_attn_f16_scales(const uint32_t* sdO, const uint32_t* sV, const uint32_t* sD, const float* vqk,
+                                 float* f16_inv, hipStream_t st, int nz, int64_t s_amax, int64_t s_inv) {
+  if (!sdO || !sV || !sD || !vqk || !f16_inv || nz < 1) return BS_EINVAL;
+  attn_f16_scales_kernel<<<(unsigned)nz, 64, 0, st>>>(sdO, sV, sD, vqk, f16_inv, s_amax, s_inv);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }
 bs_status launch_attn_split_f16(const float* dO32, int BH, int S, int Sp, int htok, const uint32_t* slots,
-                                float* inv_out, u16* const* dOp, u16* const* dOt, hipStream_t st) {
-  if (!slots || !dO32 || htok < 0 || (htok > 0 && BH % htok)) return BS_EINVAL;
-  dim3 grid((unsigned)(Sp / AT), (unsigned)BH);
+                                float* inv_out, u16* const* dOp, u16* const* dOt, hipStream_t st, SplitSpan z) {
+  if (!slots || !dO32 || htok < 0 || (htok > 0 && BH % htok) || z.nz < 1 || z.nz > 65535) return BS_EINVAL;
+  dim3 grid((unsigned)(Sp / AT), (unsigned)BH, (unsigned)z.nz);
   ProfScope prof("attn_prep", st);
   attn_prep_kernel<float, true><<<grid, 256, 0, st>>>(dO32, S, Sp, htok, slots, inv_out, dOt[0], dOt[1], nullptr,
-                                                      dOp[0], dOp[1], nullptr);
+                                                      dOp[0], dOp[1], nullptr, z);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }
@@ -1065,8 +1087,9 @@ bs_status launch_attn_bwd(const AttnBwdArgs& a, int B, int H, hipStream_t st) {
   ProfScope prof("attn_bwd", st);
   if (a.V16) {
     if (a.dD_R || a.dD_N || a.n_pol > 0 || !a.f16_inv || !a.Qt16 || !a.Kt16 || !a.dOp[0] || !a.dOp[1] || !a.dOt[0] ||
-        !a.dOt[1])
+        !a.dOt[1] || a.nz < 1 || a.nz > 65535)
       return BS_EINVAL;
+    grid.z = (unsigned)a.nz;
     attn_bwd_k_kernel<2, 0, true><<<grid, 256, 0, st>>>(a);
     if (!a.k_only) attn_bwd_q_kernel<2, false, true><<<grid, 256, 0, st>>>(a);
   } else if (a.dO32) {

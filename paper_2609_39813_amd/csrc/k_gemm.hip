@@ -358,7 +358,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_lds_kernel(GemmArgs g, in
       }
     }
   }
-  if (g.amax && !g.part) wave_amax_to_slot(mx, g.amax);  // split partials: the split sum takes it
+  if (g.amax && !g.part) wave_amax_to_slot(mx, g.amax + zb * g.s_amax);  // split partials: the split sum takes it
 }
 
 // C = alpha * sum_s part[s] (+ C), splits summed in order
@@ -515,7 +515,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_wave_kernel(GemmArgs g) {
       }
     }
   }
-  if (g.amax) wave_amax_to_slot(mx, g.amax);
+  if (g.amax) wave_amax_to_slot(mx, g.amax + zb * g.s_amax);
 }
 
 template <int FM, int FN, int NW, bool F16>

@@ -510,8 +510,10 @@ __global__ __launch_bounds__(256) void gain_partials_kernel(GainArgs<T> a) {
 // in order, then the segments by a fixed tree (deterministic). 16 columns per block.
 __global__ __launch_bounds__(256) void gain_final_kernel(const double* __restrict__ part, int64_t nrt, int64_t d,
                                                          float* __restrict__ ref, float* __restrict__ bias_r,
-                                                         float* __restrict__ bias_n) {
+                                                         float* __restrict__ bias_n, int64_t s_part, int64_t s_ref) {
   __shared__ double red[3][16][17];
+  part += blockIdx.y * s_part;
+  ref += blockIdx.y * s_ref;
   const int c = threadIdx.x & 15, sgi = threadIdx.x >> 4;
   const int64_t j = (int64_t)blockIdx.x * 16 + c;
   const int64_t per = (nrt + 15) / 16;
@@ -786,7 +788,7 @@ bs_status launch_gain_t(const GainArgs<T>& a, float* ref, float* bias_r, float* 
   }
   dim3 grid((unsigned)((a.d + 255) / 256), (unsigned)nrt);
   gain_partials_kernel<T><<<grid, 256, 0, st>>>(a);
-  gain_final_kernel<<<(unsigned)((a.d + 15) / 16), 256, 0, st>>>(a.part, nrt, a.d, ref, bias_r, bias_n);
+  gain_final_kernel<<<(unsigned)((a.d + 15) / 16), 256, 0, st>>>(a.part, nrt, a.d, ref, bias_r, bias_n, 0, 0);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }
@@ -863,9 +865,11 @@ __global__ __launch_bounds__(256) void combine_multi_kernel(CombineMulti c, int6
 }
 
 bs_status launch_gain_final(const double* part, int64_t nrt, int64_t d, float* ref, float* bias_r, float* bias_n,
-                            hipStream_t st) {
+                            hipStream_t st, int nz, int64_t s_part, int64_t s_ref) {
+  if (nz < 1 || nz > 65535 || (nz > 1 && (bias_r || bias_n))) return BS_EINVAL;
   if (d <= 0 || nrt <= 0) return BS_OK;
-  gain_final_kernel<<<(unsigned)((d + 15) / 16), 256, 0, st>>>(part, nrt, d, ref, bias_r, bias_n);
+  gain_final_kernel<<<dim3((unsigned)((d + 15) / 16), (unsigned)nz), 256, 0, st>>>(part, nrt, d, ref, bias_r, bias_n,
+                                                                                   s_part, s_ref);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }

@@ -319,13 +319,15 @@ __device__ __forceinline__ const float* move_at(const MoveSrc& m, int64_t t, int
 template <bool BASE>
 __global__ __launch_bounds__(256) void split_move_f16_kernel(MoveSrc src, const float* __restrict__ base, int64_t ldb,
                                                              int64_t R, int64_t C, F16Scale sc, PlaneOut tM,
-                                                             PlaneOut tS, int64_t ldo, PlaneOut rows, int64_t ldr) {
+                                                             PlaneOut tS, int64_t ldo, PlaneOut rows, int64_t ldr,
+                                                             MoveSpan sp) {
   __shared__ float tile[64][65];
   __shared__ float tileS[BASE ? 64 : 1][65];
-  const float a = amax_of_slots(sc.amax_a), b = sc.amax_b ? amax_of_slots(sc.amax_b) : 0.0f;
+  const int64_t z = blockIdx.z, z_src = z * sp.s_src, z_rows = z * sp.s_rows;
+  const float a = amax_of_slots(sc.amax_a + z * sp.s_amax), b = sc.amax_b ? amax_of_slots(sc.amax_b) : 0.0f;
   const int e = f16_scale_exp(fmaxf(a, b)) - (sc.amax_b ? 1 : 0);
   const float scl = ldexpf(1.0f, e);
-  if (sc.inv_out && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *sc.inv_out = ldexpf(1.0f, -e);
+  if (sc.inv_out && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) sc.inv_out[z * sp.s_inv] = ldexpf(1.0f, -e);
   const int c4 = threadIdx.x & 15, rq = threadIdx.x >> 4;
   const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
 #pragma unroll
@@ -335,7 +337,7 @@ __global__ __launch_bounds__(256) void split_move_f16_kernel(MoveSrc src, const 
     const bool in = r < R && c < C;
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f), w = v;
     if (in) {
-      v = *(const float4*)move_at(src, r, c);
+      v = *(const float4*)(move_at(src, r, c) + z_src);
       if (BASE) {
         const float4 g = *(const float4*)(base + r * ldb + c);
         w = make_float4(g.x + v.x, g.y + v.y, g.z + v.z, g.w + v.w);
@@ -354,16 +356,16 @@ __global__ __launch_bounds__(256) void split_move_f16_kernel(MoveSrc src, const 
       u16 hi[4], lo[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) split2_f16(x[q], hi[q], lo[q]);
-      *(uint2*)(rows.p[0] + r * ldr + c) = make_uint2((uint32_t)hi[0] | ((uint32_t)hi[1] << 16),
+      *(uint2*)(rows.p[0] + z_rows + r * ldr + c) = make_uint2((uint32_t)hi[0] | ((uint32_t)hi[1] << 16),
                                                       (uint32_t)hi[2] | ((uint32_t)hi[3] << 16));
-      *(uint2*)(rows.p[1] + r * ldr + c) = make_uint2((uint32_t)lo[0] | ((uint32_t)lo[1] << 16),
+      *(uint2*)(rows.p[1] + z_rows + r * ldr + c) = make_uint2((uint32_t)lo[0] | ((uint32_t)lo[1] << 16),
                                                       (uint32_t)lo[2] | ((uint32_t)lo[3] << 16));
     }
   }
   __syncthreads();
   // a thread splits 8 consecutive rows of one column: one 16-byte piece per plane
   const int rg = threadIdx.x & 7;
-  auto put = [&](float (*t)[65], const PlaneOut& out, int cc, int64_t c) {
+  auto put = [&](float (*t)[65], const PlaneOut& out, int64_t zo, int cc, int64_t c) {
     uint32_t h[4], l[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -373,29 +375,30 @@ __global__ __launch_bounds__(256) void split_move_f16_kernel(MoveSrc src, const 
       h[i] = (uint32_t)h0 | ((uint32_t)h1 << 16);
       l[i] = (uint32_t)l0 | ((uint32_t)l1 << 16);
     }
-    *(uint4*)(out.p[0] + c * ldo + r0 + 8 * rg) = make_uint4(h[0], h[1], h[2], h[3]);
-    *(uint4*)(out.p[1] + c * ldo + r0 + 8 * rg) = make_uint4(l[0], l[1], l[2], l[3]);
+    *(uint4*)(out.p[0] + zo + c * ldo + r0 + 8 * rg) = make_uint4(h[0], h[1], h[2], h[3]);
+    *(uint4*)(out.p[1] + zo + c * ldo + r0 + 8 * rg) = make_uint4(l[0], l[1], l[2], l[3]);
   };
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass) {
     const int cc = (threadIdx.x >> 3) + 32 * pass;
     const int64_t c = c0 + cc;
     if (c >= C) continue;
-    put(tile, tM, cc, c);
-    if (BASE) put(tileS, tS, cc, c);
+    put(tile, tM, z * sp.s_t, cc, c);
+    if (BASE) put(tileS, tS, 0, cc, c);
   }
 }
 
 bs_status launch_split_move(const MoveSrc& m, const float* base, int64_t ldb, int64_t R, int64_t C, F16Scale sc,
                             u16* const* tM, u16* const* tS, int64_t ldo, u16* const* rows, int64_t ldr,
-                            hipStream_t st) {
+                            hipStream_t st, MoveSpan z) {
   auto a16 = [](const void* p) { return ((uintptr_t)p & 15) == 0; };
   if (!sc.amax_a || !tM || !tM[0] || !tM[1] || (base && (!tS || !tS[0] || !tS[1])) ||
       (rows && (!rows[0] || !rows[1])))
     return BS_EINVAL;
-  if (R < 0) return BS_EINVAL;
+  if (R < 0 || z.nz < 1 || z.nz > 65535 || (base && z.nz > 1)) return BS_EINVAL;
   if (C <= 0 || ldo <= 0) return BS_OK;  // R = 0: the transposed planes are zero
-  bool ok = C % 4 == 0 && ldo % 64 == 0 && ldo >= R && a16(tM[0]) && a16(tM[1]);
+  bool ok = C % 4 == 0 && ldo % 64 == 0 && ldo >= R && a16(tM[0]) && a16(tM[1]) && z.s_src % 4 == 0 &&
+            z.s_t % 8 == 0 && z.s_rows % 4 == 0;
   if (m.rows) {
     ok = ok && m.ldi % 4 == 0 && m.ldi >= C && a16(m.rows);
   } else {
@@ -410,11 +413,11 @@ bs_status launch_split_move(const MoveSrc& m, const float* base, int64_t ldb, in
   const PlaneOut pm{{tM[0], tM[1], nullptr}};
   const PlaneOut ps{{base ? tS[0] : nullptr, base ? tS[1] : nullptr, nullptr}};
   const PlaneOut pr{{rows ? rows[0] : nullptr, rows ? rows[1] : nullptr, nullptr}};
-  const dim3 grid((unsigned)((C + 63) / 64), (unsigned)(ldo / 64));
+  const dim3 grid((unsigned)((C + 63) / 64), (unsigned)(ldo / 64), (unsigned)z.nz);
   if (base)
-    split_move_f16_kernel<true><<<grid, 256, 0, st>>>(m, base, ldb, R, C, sc, pm, ps, ldo, pr, ldr);
+    split_move_f16_kernel<true><<<grid, 256, 0, st>>>(m, base, ldb, R, C, sc, pm, ps, ldo, pr, ldr, z);
   else
-    split_move_f16_kernel<false><<<grid, 256, 0, st>>>(m, base, ldb, R, C, sc, pm, ps, ldo, pr, ldr);
+    split_move_f16_kernel<false><<<grid, 256, 0, st>>>(m, base, ldb, R, C, sc, pm, ps, ldo, pr, ldr, z);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }

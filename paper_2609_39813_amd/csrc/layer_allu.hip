@@ -36,22 +36,34 @@ constexpr int DH = 64;
 constexpr float kAttnScale = 0.125f;  // 1 / sqrt(64)
 enum { G_DX = 0, G_DGAIN1, G_DWQKV, G_DWO, G_DGAIN2, G_DWG, G_DWU, G_DWD, NGRAD };
 constexpr int NCOMP = 4;  // gradients formed here per trial: dx, dgain1, dWqkv, dWo
-constexpr int NB = 16;    // N trials per update of the shifted sums (one read-modify-write per NB)
-constexpr int KCH = 16;   // N trials per chunk of the batched weight-use contractions (a multiple of NB)
+constexpr int KCH = 16;   // N trials per chunk: its weight uses are batched contractions, and the shifted sums
+                          // are updated once with its moves
 // maxima (slot arrays) of the scaled fp16 operands: per call dh, dQKV, Wo, Wqkv, V, Q, K; per pass
 // the moves dh_d, dQKV_d, dO_d, D_d
 enum { AM_DH, AM_DQKV, AM_WO, AM_WQKV, AM_V, AM_Q, AM_K, AM_DHD, AM_DQKVD, AM_DOD, AM_DDD, AM_N };
-// their 2^-e: the splits of dh_d, dQKV_d, Wo, Wqkv, dh, dQKV, the U residuals of O and u1; then
-// the attention backward's seven in its order (dO_d, V, Q, K, dS's 2^s, 2^-s-q, 2^-s-k)
-enum {
-  IV_DHD, IV_DQKVD, IV_WO, IV_WQKV, IV_DH, IV_DQKV, IV_RO, IV_RU,
-  IV_DOD, IV_V, IV_Q, IV_K, IV_DS, IV_DKM, IV_DQM, IV_N
-};
+constexpr int64_t AM_SET = (int64_t)(AM_N - AM_DHD) * AMAX_SLOTS * AMAX_STRIDE;  // a pass's arrays
+// their 2^-e: the splits of dh_d, dQKV_d (R), Wo, Wqkv, dh, dQKV, the U residuals of O and u1, V, Q, K
+enum { IV_DHD, IV_DQKVD, IV_WO, IV_WQKV, IV_DH, IV_DQKV, IV_RO, IV_RU, IV_V, IV_Q, IV_K, IV_N };
+// per pass, the attention backward's seven in its order (dO_d, V, Q, K, dS's 2^s, 2^-s-q, 2^-s-k)
+constexpr int IV_ATT = 8;
+
+// N trials side by side in each launch of a chunk (a power of two, so it divides KCH): a pass is a
+// chain of 15 dependent launches, and a small layer's do not fill the chip. At 2 sequences of 250,
+// d = 512, 8 trials took 904 us one by one and take about 290 together (the whole check 2658 and,
+// with its copies in one launch, 1840). Past 2^22 elements of a [T][d] move a trial's launches fill
+// the chip by themselves, and its moves (44 bytes an element) would only leave the caches: 8
+// sequences of 2048 at d = 1024 take one at a time.
+int trials_together(int64_t T, int64_t d, int K) {
+  int b = 1;
+  while (b < KCH && b < K && 2 * b * T * d <= (int64_t)1 << 22) b *= 2;
+  return b;
+}
 
 struct AlluWs {
   float *m, *l;
   u16 *Vt, *Qt, *Kt, *valT_u1, *valT_O;
-  u16 *pA[2], *rows3[3], *tB[3], *dOp[3], *dOt[3];
+  u16 *pA[2], *tB[2];
+  u16 *rows3[2], *dOp[2], *dOt[2];  // per trial of a launch, as the moves below and gpart
   u16 *tH[2], *tQ[2];    // dh, dQKV as scaled two-term fp16 splits, transposed
   u16 *pAn[2], *pWn[2];  // a chunk of N trials' difference and value planes at O's and u1's weight uses
   float *dWo_n, *dWqkv_n;  // the chunk's weight-use moves [KCH][d][d], [KCH][d][3d]
@@ -63,43 +75,45 @@ struct AlluWs {
   u16 *Wo16, *Wqkv16, *V16;  // the weights and V as scaled fp16 (the moves' contractions)
   u16 *Q16, *K16, *Qt16, *Kt16;  // Q, K as scaled fp16 and their transposed copies
   double* gpart;
-  float* delta[NCOMP];      // the passes' moves: dx, dgain1 [min(K, NB)][n] (N's trial k in row
-                            // (k - 1) % NB); dWqkv, dWo [1][n] (U, R; N's are in the chunk buffers)
+  float* delta[2];          // N's moves of dx, dgain1 [min(K, KCH)][n] (trial k in row (k - 1) % KCH;
+                            // dWqkv's and dWo's are in the chunk buffers; R's and U's go to bias)
   float* bias[3][NCOMP];    // per letter
   float* se_n[NCOMP];       // N's se
   float *d1[NCOMP];
   double *S1[NCOMP], *S2[NCOMP];
-  float *wg[3], *wu[3], *ref_g, *ref_u, *nan_buf;
+  float *wg[3], *wu[3], *ref_g, *ref_u;
   float* part;
   int64_t part_cap;
   double* sumsq_part;
-  uint32_t* amax[AM_N];  // slot arrays (AMAX_SLOTS) of max |.|
+  uint32_t* amax[AM_N];  // slot arrays (AMAX_SLOTS) of max |.|, a pass's per trial AM_SET apart
   float* inv;            // [IV_N]
+  float* inv_att;        // [trial][IV_ATT]
 };
 
 AlluWs carve_allu(Carver& c, int B, int S, int d, int H, int F, int K) {
   AlluWs w{};
   const int64_t kc = std::max(1, std::min(K, KCH));
   const int64_t T = (int64_t)B * S, Td = T * d, Tp = round_up(T > 0 ? T : 1, 64), bh = (int64_t)B * H;
-  const int64_t Sp = round_up(S, 64), d3 = 3 * (int64_t)d, F2 = 2 * (int64_t)F;
+  const int64_t Sp = round_up(S, 64), d3 = 3 * (int64_t)d;
+  const int64_t nt = trials_together(T, d, K);
   const int64_t nc[NCOMP] = {Td, d, (int64_t)d * d3, (int64_t)d * d};
   w.m = c.take<float>(bh * S);
   w.l = c.take<float>(bh * S);
   for (u16** p : {&w.Vt, &w.Qt, &w.Kt}) *p = c.take<u16>(bh * DH * Sp);
   w.valT_u1 = c.take<u16>(d * Tp);
   w.valT_O = c.take<u16>(d * Tp);
-  for (int i = 0; i < 3; ++i) {
-    if (i < 2) w.pA[i] = c.take<u16>(d * Tp);
-    w.rows3[i] = c.take<u16>(T * std::max(F2, d3));
+  for (int i = 0; i < 2; ++i) {
+    w.pA[i] = c.take<u16>(d * Tp);
     w.tB[i] = c.take<u16>(d3 * Tp);
-    w.dOp[i] = c.take<u16>(Td);
-    w.dOt[i] = c.take<u16>(bh * DH * Sp);
+    w.rows3[i] = c.take<u16>(nt * T * d3);
+    w.dOp[i] = c.take<u16>(nt * Td);
+    w.dOt[i] = c.take<u16>(nt * bh * DH * Sp);
   }
-  for (float** p : {&w.dh_d, &w.dO_dt, &w.du1_d}) *p = c.take<float>(Td);
-  w.dQ_d = c.take<float>(3 * Td);  // dQ, dK, dV of the move, one block (one max over the three)
+  for (float** p : {&w.dh_d, &w.dO_dt, &w.du1_d}) *p = c.take<float>(nt * Td);
+  w.dQ_d = c.take<float>(nt * 3 * Td);  // dQ, dK, dV of the move, one block (one max over the three)
   w.dK_d = w.dQ_d ? w.dQ_d + Td : nullptr;
   w.dV_d = w.dQ_d ? w.dQ_d + 2 * Td : nullptr;
-  w.dD = c.take<float>(bh * S);
+  w.dD = c.take<float>(nt * bh * S);
   w.Wo16 = c.take<u16>((int64_t)d * d);
   w.Wqkv16 = c.take<u16>((int64_t)d * d3);
   w.V16 = c.take<u16>(bh * S * DH);
@@ -119,9 +133,9 @@ AlluWs carve_allu(Carver& c, int B, int S, int d, int H, int F, int K) {
   w.tBq = c.take<u16>(kc * 2 * d3 * Tp);
   w.invo = c.take<float>(kc);
   w.invq = c.take<float>(kc);
-  w.gpart = c.take<double>(3 * ((T + 15) / 16) * (int64_t)d);
+  w.gpart = c.take<double>(nt * ((T + 15) / 16) * (int64_t)d);
   for (int i = 0; i < NCOMP; ++i) {
-    w.delta[i] = c.take<float>((i < 2 ? std::max(1, std::min(K, NB)) : 1) * nc[i]);
+    if (i < 2) w.delta[i] = c.take<float>(std::max(1, std::min(K, KCH)) * nc[i]);
     for (int l = 0; l < 3; ++l) w.bias[l][i] = c.take<float>(nc[i]);
     w.se_n[i] = c.take<float>(nc[i]);
     w.d1[i] = c.take<float>(nc[i]);
@@ -134,15 +148,15 @@ AlluWs carve_allu(Carver& c, int B, int S, int d, int H, int F, int K) {
   }
   w.ref_g = c.take<float>((int64_t)d * F);
   w.ref_u = c.take<float>((int64_t)d * F);
-  w.nan_buf = c.take<float>(std::max<int64_t>({Td, (int64_t)d * F2, (int64_t)d * d3}));
   w.part_cap = 8 * (int64_t)d * d3;  // split-K partials of the few-tile weight contractions
   w.part = c.take<float>(w.part_cap);
   w.sumsq_part = c.take<double>(sumsq_part_size());
   {
-    uint32_t* a = c.take<uint32_t>(AM_N * AMAX_SLOTS * AMAX_STRIDE);
+    uint32_t* a = c.take<uint32_t>(AM_DHD * AMAX_SLOTS * AMAX_STRIDE + nt * AM_SET);
     for (int i = 0; i < AM_N; ++i) w.amax[i] = a ? a + i * AMAX_SLOTS * AMAX_STRIDE : nullptr;
   }
   w.inv = c.take<float>(IV_N);
+  w.inv_att = c.take<float>(nt * IV_ATT);
   return w;
 }
 
@@ -172,11 +186,6 @@ struct Gemm {
   }
   bool ok = true;
 };
-
-bs_status copy_f32(float* dst, const float* src, int64_t n, hipStream_t st) {
-  if (!dst || n <= 0) return BS_OK;
-  return hipMemcpyAsync(dst, src, sizeof(float) * n, hipMemcpyDeviceToDevice, st) == hipSuccess ? BS_OK : BS_EHIP;
-}
 
 }  // namespace
 
@@ -230,7 +239,7 @@ bs_status allu_run(const AlluIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
   BS_TRY(planes_of(NP_VAL, io.u1, io.c_u1, s_u1, &w.valT_u1, 1));
   BS_TRY(planes_of(NP_VAL, io.Otok, io.c_Otok, s_O, &w.valT_O, 1));
   pa.f16 = 0;
-  BS_TRY(launch_fill2d((float*)w.amax[0], AM_N * AMAX_SLOTS, 1, AMAX_STRIDE, 0.0f, st));
+  BS_TRY(launch_fill2d((float*)w.amax[0], AM_DHD * AMAX_SLOTS, 1, AMAX_STRIDE, 0.0f, st));
   BS_TRY(launch_amax_f32(io.dh, Td, w.amax[AM_DH], st));
   BS_TRY(launch_amax_f32(io.dqkv, 3 * Td, w.amax[AM_DQKV], st));
   BS_TRY(launch_amax_bf16(io.Wo, (int64_t)d * d, w.amax[AM_WO], st));
@@ -265,15 +274,16 @@ bs_status allu_run(const AlluIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
                              Tp, nullptr, 0, st));
   }
 
-  // ---- one pass per letter (K per-trial passes for N) ----
+  // ---- one pass per letter (N: the K trials, nz of them side by side in each launch) ----
+  const int together = trials_together(T, d, K);
   for (int l = 0; l < 3; ++l) {
     const int ntr = l == LETTER_N ? K : 1;
-    for (int k = 1; k <= ntr; ++k) {
+    for (int k = 1, nz = 1; k <= ntr; k += nz) {
       const auto rd = [&](const float* x, const uint8_t* codes, const float* scale, uint32_t use) {
         return StoreRead{x, codes, scale, f, l, io.seed, (uint32_t)k, use};
       };
-      const int slot = l == LETTER_N ? (k - 1) % NB : 0;
-      const int kk = (k - 1) % KCH;  // N: the trial's index in its chunk
+      const int kk = (k - 1) % KCH;  // N: trial k's index in its chunk (and its row of the moves)
+      nz = std::min({together, KCH - kk, ntr - k + 1});
       if (l == LETTER_N && kk == 0) {
         // the chunk's new roundings at O's and u1's weight uses (difference and value planes), and
         // their differences' products with the reference incoming gradients, the chunk in one
@@ -296,9 +306,12 @@ bs_status allu_run(const AlluIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
         gg.g.alpha_dev2 = w.inv + IV_DQKV;
         BS_TRY(gg.add(&w.pAn[1], 1, w.tQ, 2).run(w.part, w.part_cap, st));
       }
+      // the pass's moves: the letter's bias (U, R), or N's rows from kk on
       float* dl[NCOMP];
-      for (int i = 0; i < NCOMP; ++i) dl[i] = w.delta[i] + slot * nc[i];
+      for (int i = 0; i < NCOMP; ++i) dl[i] = w.bias[l][i];
       if (l == LETTER_N) {
+        dl[0] = w.delta[0] + kk * nc[0];
+        dl[1] = w.delta[1] + kk * nc[1];
         dl[2] = w.dWqkv_n + kk * nc[2];
         dl[3] = w.dWo_n + kk * nc[3];
       }
@@ -309,10 +322,11 @@ bs_status allu_run(const AlluIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
       const u16* valU = w.valT_u1;
       // u2's normalization-input use: the move of dh (and its max |.|)
       if (l != LETTER_U) {
-        BS_TRY(launch_fill2d((float*)w.amax[AM_DHD], (AM_N - AM_DHD) * AMAX_SLOTS, 1, AMAX_STRIDE, 0.0f, st));
+        BS_TRY(launch_fill2d((float*)w.amax[AM_DHD], (int64_t)nz * (AM_N - AM_DHD) * AMAX_SLOTS, 1, AMAX_STRIDE, 0.0f, st));
         AlluDxArgs<float> ax{io.h, io.r2, io.gain2, rd(io.u2, io.c_u2, s_u2, 2 * 256 + 3), io.du2, nullptr,
                              nullptr, T, d, w.dh_d};
         ax.amax = w.amax[AM_DHD];
+        ax.z = TrialSpan{nz, Td, 0, 0, AM_SET};
         BS_TRY(launch_allu_dx(ax, st));
       }
       const F16Scale sc_o{w.amax[AM_DHD], nullptr, w.inv + IV_DHD};
@@ -341,7 +355,8 @@ bs_status allu_run(const AlluIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
           to[1] = to[0] + d * Tp;
           so.inv_out = w.invo + kk;
         }
-        BS_TRY(launch_split_move(mo, nullptr, 0, T, d, so, to, nullptr, Tp, w.rows3, d, st));
+        BS_TRY(launch_split_move(mo, nullptr, 0, T, d, so, to, nullptr, Tp, w.rows3, d, st,
+                                 MoveSpan{nz, Td, 2 * d * Tp, Td, AM_SET, 1}));
         if (l != LETTER_N) {
           Gemm gw(d, d, (int)Tp, Tp, Tp, dWo, d, s_O);
           gw.g.f16 = 1;
@@ -353,9 +368,14 @@ bs_status allu_run(const AlluIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
         gm.g.f16 = 1;
         gm.g.alpha_dev2 = so.inv_out;
         gm.g.amax = w.amax[AM_DOD];
+        gm.g.batch = nz;
+        gm.g.sA = gm.g.sC = Td;
+        gm.g.s_alpha2 = 1;
+        gm.g.s_amax = AM_SET;
         BS_TRY(gm.add(w.rows3, 2, &w.Wo16, 1).run(nullptr, 0, st));
       }
       // the D use: U reads the original and dO does not move: no move downstream of it
+      // (dx and dgain1: bias zero)
       if (l == LETTER_U) {
         pa.inv_out = w.inv + IV_RU;
         BS_TRY(planes_of(NP_RESU, io.u1, io.c_u1, s_u1, w.pA, 2));
@@ -365,22 +385,22 @@ bs_status allu_run(const AlluIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
         gr.g.f16 = 1;
         gr.g.alpha_dev2 = w.inv + IV_DQKV;
         BS_TRY(gr.add(w.pA, 2, w.tQ, 2, 1).run(w.part, w.part_cap, st));
-        BS_TRY(launch_fill(dl[0], Td, 0.0f, st));
-        BS_TRY(launch_fill(dl[1], d, 0.0f, st));
       } else {
         AlluDArgs ad{rd(io.O, io.c_O, s_O, 1 * 256 + 1), io.dOh, w.dO_dt, rows_h, w.dD};
         ad.amax = w.amax[AM_DDD];
         ad.ddo_heads = H;
         ad.ddo_S = S;
+        ad.z = TrialSpan{nz, Td, rows_h, 0, AM_SET};
         BS_TRY(launch_allu_d(ad, st));
         // dO_d as the scaled two-term fp16 split (V as scaled fp16) for the attention backward
-        BS_TRY(launch_attn_split_f16(w.dO_dt, (int)bh, S, (int)Sp, H, w.amax[AM_DOD], w.inv + IV_DOD, w.dOp, w.dOt,
-                                     st));
-        BS_TRY(launch_attn_f16_scales(w.amax[AM_DOD], w.amax[AM_V], w.amax[AM_DDD], w.inv + IV_DOD, st));
+        BS_TRY(launch_attn_split_f16(w.dO_dt, (int)bh, S, (int)Sp, H, w.amax[AM_DOD], w.inv_att, w.dOp, w.dOt, st,
+                                     SplitSpan{nz, Td, Td, bh * DH * Sp, AM_SET, IV_ATT}));
+        BS_TRY(launch_attn_f16_scales(w.amax[AM_DOD], w.amax[AM_V], w.amax[AM_DDD], w.inv + IV_V, w.inv_att, st, nz,
+                                      AM_SET, IV_ATT));
         AttnBwdArgs ba{};
         ba.Qt = w.Qt;
         ba.Kt = w.Kt;
-        for (int i = 0; i < 3; ++i) {
+        for (int i = 0; i < 2; ++i) {
           ba.dOp[i] = w.dOp[i];
           ba.dOt[i] = w.dOt[i];
         }
@@ -392,7 +412,14 @@ bs_status allu_run(const AlluIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
         ba.V16 = w.V16;
         ba.Qt16 = w.Qt16;
         ba.Kt16 = w.Kt16;
-        ba.f16_inv = w.inv + IV_DOD;
+        ba.f16_inv = w.inv_att;
+        ba.nz = nz;
+        ba.z_dop = Td;
+        ba.z_dot = bh * DH * Sp;
+        ba.z_rows = rows_h;
+        ba.z_inv = IV_ATT;
+        ba.z_out = 3 * Td;
+        ba.z_amax = AM_SET;
         ba.amax = w.amax[AM_DQKVD];  // the max of dQKV_d, for its split
         ba.m = w.m;
         ba.l = w.l;
@@ -422,7 +449,8 @@ bs_status allu_run(const AlluIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
           tq[1] = tq[0] + d3 * Tp;
           sq.inv_out = w.invq + kk;
         }
-        BS_TRY(launch_split_move(mq, nullptr, 0, T, d3, sq, tq, nullptr, Tp, w.rows3, d3, st));
+        BS_TRY(launch_split_move(mq, nullptr, 0, T, d3, sq, tq, nullptr, Tp, w.rows3, d3, st,
+                                 MoveSpan{nz, 3 * Td, 2 * d3 * Tp, 3 * Td, AM_SET, 1}));
         if (l != LETTER_N) {
           Gemm gq(d, (int)d3, (int)Tp, Tp, Tp, dWqkv, d3, s_u1);
           gq.g.f16 = 1;
@@ -433,18 +461,23 @@ bs_status allu_run(const AlluIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
         Gemm gu((int)T, d, (int)d3, d3, d3, w.du1_d, d, w.inv + IV_WQKV);
         gu.g.f16 = 1;
         gu.g.alpha_dev2 = sq.inv_out;
+        gu.g.batch = nz;
+        gu.g.sA = 3 * Td;
+        gu.g.sC = Td;
+        gu.g.s_alpha2 = 1;
         BS_TRY(gu.add(w.rows3, 2, &w.Wqkv16, 1).run(nullptr, 0, st));
         // (one pass over u1's operands for both uses)
         AlluDxArgs<u16> ax{io.x, io.r1, io.gain1, rd(io.u1, io.c_u1, s_u1, 0 * 256 + 3), io.du1, w.du1_d, w.dh_d,
                            T, d, dl[0]};
+        ax.z = TrialSpan{nz, Td, 0, (T + 15) / 16 * (int64_t)d, 0};
         const AlluGainDxArgs<u16> agx{ax, rd(io.u1, io.c_u1, s_u1, 0 * 256 + 1), w.gpart};
         BS_TRY(launch_allu_gain_dx(agx, st));
-        BS_TRY(launch_gain_final(w.gpart, (T + 15) / 16, d, dl[1], nullptr, nullptr, st));
+        BS_TRY(launch_gain_final(w.gpart, (T + 15) / 16, d, dl[1], nullptr, nullptr, st, nz, ax.z.s_part, d));
       }
       // the chunk's last trial: its weight uses' products val_k^T g_d,k, one batched contraction
       // each, added to the chunk's difference products
-      if (l == LETTER_N && (kk == KCH - 1 || k == ntr)) {
-        const int nbk = kk + 1;
+      if (l == LETTER_N && (kk + nz == KCH || k + nz > ntr)) {
+        const int nbk = kk + nz;
         Gemm gw(d, d, (int)Tp, Tp, Tp, w.dWo_n, d, s_O);
         gw.g.f16 = 1;
         gw.g.accumulate = 1;
@@ -468,17 +501,11 @@ bs_status allu_run(const AlluIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
         const u16* tbq[2] = {w.tBq, w.tBq + d3 * Tp};
         BS_TRY(gq.add(&w.pWn[1], 1, tbq, 2).run(nullptr, 0, st));
       }
-      // this pass's moves: the letter's bias (U, R), or N's trials k - slot .. k, in order, once
-      // NB of them (or the last) are in
-      for (int i = 0; i < NCOMP; ++i) {
-        if (l == LETTER_N) {
-          if (slot == NB - 1 || k == ntr)
-            BS_TRY(launch_trial_accum(dl[i] - (int64_t)slot * nc[i], slot + 1, k - slot, nc[i], w.d1[i], w.S1[i],
-                                      w.S2[i], st));
-        } else {
-          BS_TRY(copy_f32(w.bias[l][i], dl[i], nc[i], st));
-        }
-      }
+      // N: the chunk's moves, in order of the trial, into the shifted sums
+      if (l == LETTER_N && (kk + nz == KCH || k + nz > ntr))
+        for (int i = 0; i < NCOMP; ++i)
+          BS_TRY(launch_trial_accum(dl[i] - (int64_t)kk * nc[i], kk + nz, k - kk, nc[i], w.d1[i], w.S1[i], w.S2[i],
+                                    st));
     }
   }
   for (int i = 0; i < NCOMP; ++i) {
@@ -491,12 +518,11 @@ bs_status allu_run(const AlluIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
   BS_TRY(launch_split_cols(io.ref[G_DWG], w.ref_g, w.ref_u, d, F, st));
   for (int l = 0; l < 3; ++l)
     BS_TRY(launch_split_cols(io.wgu_bias + (int64_t)l * d * F2, w.wg[l], w.wu[l], d, F, st));
-  BS_TRY(launch_fill(w.nan_buf, std::max<int64_t>({Td, (int64_t)d * F2, (int64_t)d * d3}), __builtin_nanf(""),
-                     st));
   const int64_t n_of[NGRAD] = {Td, d, (int64_t)d * d3, (int64_t)d * d, d, dF, dF, Fd};
   const float* ref_of[NGRAD] = {io.ref[G_DX], io.ref[G_DGAIN1], io.ref[G_DWQKV], io.ref[G_DWO], io.ref[G_DGAIN2],
                                 w.ref_g, w.ref_u, io.ref[G_DWD]};
   SumsqBatch batch{};
+  CopyBatch copies{};
   const float* const kZero = (const float*)1;
   const float* const kNaN = (const float*)2;
   for (int gi = 0; gi < NGRAD; ++gi)
@@ -517,16 +543,14 @@ bs_status allu_run(const AlluIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
         if (gi <= G_DWO) se = w.se_n[gi];
         if (gi == G_DGAIN2) se = io.g2_se + (int64_t)l * d;
       }
-      BS_TRY(copy_f32(io.bias[l][gi], bias, n_of[gi], st));
-      if (io.se[l][gi]) {
-        if (se == kZero)
-          BS_TRY(launch_fill(io.se[l][gi], n_of[gi], 0.0f, st));
-        else
-          BS_TRY(copy_f32(io.se[l][gi], se == kNaN ? w.nan_buf : se, n_of[gi], st));
-      }
+      if (l == LETTER_U && (gi == G_DX || gi == G_DGAIN1)) bias = nullptr;  // zero
+      const bool held = se != kZero && se != kNaN;
+      if (!copies.add(io.bias[l][gi], bias, 0.0f, n_of[gi]) ||
+          !copies.add(io.se[l][gi], held ? se : nullptr, se == kNaN ? __builtin_nanf("") : 0.0f, n_of[gi]))
+        return BS_EINVAL;
       if (io.table) {
         double* out = io.table + ((int64_t)gi * 3 + l) * 3;
-        batch.job[batch.count++] = SumsqJob{bias, n_of[gi], out};
+        batch.job[batch.count++] = SumsqJob{bias, bias ? n_of[gi] : 1, out};
         batch.job[batch.count++] = SumsqJob{ref_of[gi], n_of[gi], out + 1};
         if (se == kZero)
           batch.job[batch.count++] = SumsqJob{nullptr, 1, out + 2};
@@ -536,6 +560,7 @@ bs_status allu_run(const AlluIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
           batch.job[batch.count++] = SumsqJob{se, n_of[gi], out + 2};
       }
     }
+  BS_TRY(launch_copy_batch(copies, st));
   if (io.table) BS_TRY(launch_sumsq_batch(batch, w.sumsq_part, st));
   return BS_OK;
 }
