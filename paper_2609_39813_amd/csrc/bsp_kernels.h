@@ -99,13 +99,18 @@ struct FreshArgs {
   const float* w1;     // [T][d] weights (FC_COLSUM, FC_BLOCKSUM)
   const float* w2;     // [T][d] second weight (FC_BLOCKSUM, nullable)
   double* partial;     // FC_BLOCKSUM: [K][2][nblocks]
-  float* colsum = nullptr;  // FC_COLSUM: [K][ceil(T/32)][d]
+  float* colsum = nullptr;  // FC_COLSUM: [K][ceil(T / colsum_rows)][d]
   int trial0 = 1;      // the K trials are trial0 .. trial0 + K - 1
 };
 template <typename X>
 bs_status launch_fresh_count_t(const FreshArgs<X>& a, int mode, hipStream_t st);
 inline int64_t fresh_count_blocks(int64_t T, int64_t d) { return ((d + 255) / 256) * ((T + 31) / 32); }
 
+// rows per tile of the column sums: 32, or 8 where 32 would leave SIMDs idle and the sums stay small
+// (at most 64 MB). 256 x 64 x 64 trials: 20.3 us with 32, 8.0 with 8; 1111 x 520 x 24: 19.1, 13.2
+inline int64_t colsum_rows(int64_t T, int64_t d, int K) {
+  return K >= 4 && ((d + 63) / 64) * ((T + 31) / 32) < 1024 && (int64_t)K * T * d <= (int64_t)1 << 27 ? 8 : 32;
+}
 bs_status launch_fresh_count(const float* u, int64_t T, int64_t d, int fmt, const float* scale, uint64_t seed,
                              uint32_t use, int K, u16* counts, const float* w, float* colsum, hipStream_t st);
 

@@ -60,7 +60,9 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const T* __restrict__ 
 // squares pass through LDS, and lane l adds the entries l, l + 64, ... of the chunk, chunks in
 // order, so partial l still takes j = l, l + 64, ... ascending. A wave takes RMS_RPW rows (the
 // same trip count in every wave, so the block barriers are uniform); one amax atomic per block.
-constexpr int RMS_RPW = 4;
+// Below RMS_T4 rows a wave takes one (four leave CUs idle, each a chain of loads and barriers: 256 x
+// 64 8.7 us, now 4.2; 1111 x 520 13.6, now 7.6), above four (a quarter of the atomics).
+constexpr int64_t RMS_T4 = 8192;
 
 template <typename T>
 __device__ __forceinline__ void load8_f32(const T* p, float (&x)[8]);
@@ -81,7 +83,7 @@ __device__ __forceinline__ void load8_f32<u16>(const u16* p, float (&x)[8]) {
   }
 }
 
-template <typename T>
+template <typename T, int RMS_RPW>
 __global__ __launch_bounds__(256) void rmsnorm_fwd8_kernel(const T* __restrict__ X, const float* __restrict__ gain,
                                                            int64_t Tn, int64_t d, float eps, float* __restrict__ u,
                                                            float* __restrict__ rstd, uint32_t* __restrict__ amax_bits) {
@@ -89,6 +91,7 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd8_kernel(const T* __restrict__
   __shared__ float sq[4][512];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   uint32_t m = 0;
+#pragma unroll 1
   for (int k = 0; k < RMS_RPW; ++k) {
     const int64_t t = ((int64_t)blockIdx.x * RMS_RPW + k) * 4 + w;
     const bool ok = t < Tn;
@@ -471,7 +474,9 @@ __global__ __launch_bounds__(256) void val_rows_kernel(const uint8_t* __restrict
 //   q1: (s val(C_u) - gain z) / gain * du          (R: reads deq(C_u) / gain)
 //   q2: (s mean_k val(C_k) - gain z) / gain * du   (N: reads a new rounding; mean over
 //       the K trials = sign (lo + n_up step / K))
-// z = fl32(x r) is recomputed exactly as in the forward.
+// z = fl32(x r) is recomputed exactly as in the forward. Few columns make few waves: GAIN_RB rows'
+// loads are in flight at once (256 x 64: 16.5 us one row at a time, now 11.8).
+constexpr int GAIN_RB = 8;
 template <typename T>
 __global__ __launch_bounds__(256) void gain_partials_kernel(GainArgs<T> a) {
 #pragma clang fp contract(off)
@@ -484,20 +489,35 @@ __global__ __launch_bounds__(256) void gain_partials_kernel(GainArgs<T> a) {
   const double g = a.gain[j], ig = 1.0 / g;
   double q0 = 0.0, q1 = 0.0, q2 = 0.0;
   const int64_t tend = (rt + 1) * GAIN_RT < a.T ? (rt + 1) * GAIN_RT : a.T;
-  for (int64_t t = rt * GAIN_RT; t < tend; ++t) {
-    const int64_t e = t * a.d + j;
-    const float z = load_f32(a.X, e) * a.rstd[t];
-    const double du = a.du[e];
-    const double gz = g * (double)z;
-    q0 += (double)z * du;
-    if (a.want_r) q1 += (s * (double)f8_value(a.codes[e], a.f) - gz) * ig * du;
-    if (a.counts) {
-      const float y = div_scale(a.u[e], rsf);
-      const Bracket b = f8_bracket(fminf(fabsf(y), a.f.fmax), a.f);
-      const double step = f8_step(b);
-      double mv = (double)b.mi * step + (double)a.counts[e] * step / a.K;
-      if (signbit(y)) mv = -mv;
-      q2 += (s * mv - gz) * ig * du;
+  for (int64_t t0 = rt * GAIN_RT; t0 < tend; t0 += GAIN_RB) {
+    float xv[GAIN_RB], rs[GAIN_RB], duv[GAIN_RB], uv[GAIN_RB];
+    uint32_t cd[GAIN_RB], cn[GAIN_RB];
+#pragma unroll
+    for (int i = 0; i < GAIN_RB; ++i) {
+      const int64_t t = t0 + i < tend ? t0 + i : tend - 1, e = t * a.d + j;
+      xv[i] = load_f32(a.X, e);
+      rs[i] = a.rstd[t];
+      duv[i] = a.du[e];
+      cd[i] = a.want_r ? a.codes[e] : 0u;
+      uv[i] = a.counts ? a.u[e] : 0.0f;
+      cn[i] = a.counts ? a.counts[e] : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < GAIN_RB; ++i) {
+      if (t0 + i >= tend) break;
+      const float z = xv[i] * rs[i];
+      const double du = duv[i];
+      const double gz = g * (double)z;
+      q0 += (double)z * du;
+      if (a.want_r) q1 += (s * (double)f8_value(cd[i], a.f) - gz) * ig * du;
+      if (a.counts) {
+        const float y = div_scale(uv[i], rsf);
+        const Bracket b = f8_bracket(fminf(fabsf(y), a.f.fmax), a.f);
+        const double step = f8_step(b);
+        double mv = (double)b.mi * step + (double)cn[i] * step / a.K;
+        if (signbit(y)) mv = -mv;
+        q2 += (s * mv - gz) * ig * du;
+      }
     }
   }
   const int64_t nrt = gridDim.y;
@@ -560,21 +580,26 @@ __global__ __launch_bounds__(256) void gain_final_kernel(const double* __restric
 // (trial, column) (row tiles summed in order), then Welford over k in order per column.
 __global__ __launch_bounds__(256) void gain_trial_sum_kernel(const float* __restrict__ part, int64_t nrt, int64_t d,
                                                              double* __restrict__ S) {
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t k = blockIdx.y;
-  if (j >= d) return;
-  const float* p = part + k * nrt * d + j;
+  __shared__ double red[4][64];
+  const int lane = threadIdx.x & 63, seg = threadIdx.x >> 6;
+  const int64_t j = (int64_t)blockIdx.x * 64 + lane, k = blockIdx.y;
+  const int64_t per = (nrt + 3) / 4, r1 = min(nrt, (seg + 1) * per);
   double acc = 0.0;
-  int64_t rt = 0;
-  for (; rt + 8 <= nrt; rt += 8) {  // eight loads in flight, added in row-tile order
-    float v[8];
+  if (j < d) {
+    const float* p = part + k * nrt * d + j;
+    int64_t rt = seg * per;
+    for (; rt + 8 <= r1; rt += 8) {  // eight loads in flight, added in row-tile order
+      float v[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = p[(rt + q) * d];
+      for (int q = 0; q < 8; ++q) v[q] = p[(rt + q) * d];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) acc += v[q];
+      for (int q = 0; q < 8; ++q) acc += v[q];
+    }
+    for (; rt < r1; ++rt) acc += p[rt * d];
   }
-  for (; rt < nrt; ++rt) acc += p[rt * d];
-  S[k * d + j] = acc;
+  red[seg][lane] = acc;
+  __syncthreads();
+  if (seg == 0 && j < d) S[k * d + j] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
 }
 
 // se of the gain use under N: 16 lanes per column, each over trials k = lane, lane + 16, ...
@@ -607,6 +632,8 @@ __global__ __launch_bounds__(256) void gain_se_kernel(const double* __restrict__
 
 // Normalization input gradient, one wave64 per row:
 //   dz = gain du; dx = r (dz - zhat (sum_j dz zhat) / d), zhat = z (U) or s val(C_u) / gain (R).
+// 1111 x 520: 11.8 us with one column's loads at a time, 8.9 with DX_B columns'.
+constexpr int DX_B = 8;
 template <typename T>
 __global__ __launch_bounds__(256) void norm_dx_kernel(DxArgs<T> a) {
 #pragma clang fp contract(off)
@@ -616,27 +643,49 @@ __global__ __launch_bounds__(256) void norm_dx_kernel(DxArgs<T> a) {
   const float r = a.rstd[t];
   const double s = a.scale ? (double)*a.scale : 1.0;
   double dot_u = 0.0, dot_r = 0.0;
-  for (int64_t j = lane; j < a.d; j += 64) {
-    const int64_t e = t * a.d + j;
-    const double z = (double)(load_f32(a.X, e) * r);
-    const double g = a.gain[j];
-    const double dz = g * (double)a.du[e];
-    dot_u += dz * z;
-    if (a.dx_r) dot_r += dz * (s * (double)f8_value(a.codes[e], a.f) / g);
+  // DX_B columns per lane loaded before the first is used, in both walks
+  float xv[DX_B], gv[DX_B], dv[DX_B];
+  uint32_t cv[DX_B];
+  auto load = [&](int64_t j0) {
+#pragma unroll
+    for (int i = 0; i < DX_B; ++i) {
+      const int64_t j = j0 + 64 * i < a.d ? j0 + 64 * i : a.d - 1, e = t * a.d + j;
+      xv[i] = load_f32(a.X, e);
+      gv[i] = a.gain[j];
+      dv[i] = a.du[e];
+      cv[i] = a.dx_r ? a.codes[e] : 0u;
+    }
+  };
+  for (int64_t j0 = lane; j0 < a.d; j0 += 64 * DX_B) {
+    load(j0);
+#pragma unroll
+    for (int i = 0; i < DX_B; ++i) {
+      if (j0 + 64 * i >= a.d) break;
+      const double z = (double)(xv[i] * r);
+      const double g = gv[i];
+      const double dz = g * (double)dv[i];
+      dot_u += dz * z;
+      if (a.dx_r) dot_r += dz * (s * (double)f8_value(cv[i], a.f) / g);
+    }
   }
   dot_u = wave_sum_f64(dot_u);
   dot_r = wave_sum_f64(dot_r);
   dot_u = __shfl(dot_u, 0, 64) / (double)a.d;
   dot_r = __shfl(dot_r, 0, 64) / (double)a.d;
-  for (int64_t j = lane; j < a.d; j += 64) {
-    const int64_t e = t * a.d + j;
-    const double z = (double)(load_f32(a.X, e) * r);
-    const double g = a.gain[j];
-    const double dz = g * (double)a.du[e];
-    a.dx_ref[e] = (float)((double)r * (dz - z * dot_u));
-    if (a.dx_r) {
-      const double zr = s * (double)f8_value(a.codes[e], a.f) / g;
-      a.dx_r[e] = (float)((double)r * (dz - zr * dot_r));
+  for (int64_t j0 = lane; j0 < a.d; j0 += 64 * DX_B) {
+    if (a.d > 64 * DX_B) load(j0);  // else the first walk's are still held
+#pragma unroll
+    for (int i = 0; i < DX_B; ++i) {
+      const int64_t j = j0 + 64 * i, e = t * a.d + j;
+      if (j >= a.d) break;
+      const double z = (double)(xv[i] * r);
+      const double g = gv[i];
+      const double dz = g * (double)dv[i];
+      a.dx_ref[e] = (float)((double)r * (dz - z * dot_u));
+      if (a.dx_r) {
+        const double zr = s * (double)f8_value(cv[i], a.f) / g;
+        a.dx_r[e] = (float)((double)r * (dz - zr * dot_r));
+      }
     }
   }
 }
@@ -695,13 +744,18 @@ bs_status launch_rmsnorm_fwd(const void* X, bs_dtype dt, const float* gain, int6
     const unsigned blocks = (unsigned)((T + 3) / 4);
     ProfScope prof("rmsnorm_fwd", st);
     const bool vec = d % 8 == 0 && ((uintptr_t)X & 15) == 0 && ((uintptr_t)gain & 15) == 0 && ((uintptr_t)u & 15) == 0;
-    const unsigned blocks8 = (unsigned)((T + 4 * RMS_RPW - 1) / (4 * RMS_RPW));
+    auto fwd8 = [&](auto x, auto rpw) {
+      using X8 = decltype(x);
+      constexpr int R = decltype(rpw)::value;
+      rmsnorm_fwd8_kernel<X8, R><<<(unsigned)((T + 4 * R - 1) / (4 * R)), 256, 0, st>>>(
+          (const X8*)X, gain, T, d, eps, u, rstd, (uint32_t*)&diag->amax);
+    };
+    using One = std::integral_constant<int, 1>;
+    using Four = std::integral_constant<int, 4>;
     if (vec && dt == BS_F32)
-      rmsnorm_fwd8_kernel<float><<<blocks8, 256, 0, st>>>((const float*)X, gain, T, d, eps, u, rstd,
-                                                          (uint32_t*)&diag->amax);
+      T < RMS_T4 ? fwd8(float{}, One{}) : fwd8(float{}, Four{});
     else if (vec)
-      rmsnorm_fwd8_kernel<u16><<<blocks8, 256, 0, st>>>((const u16*)X, gain, T, d, eps, u, rstd,
-                                                        (uint32_t*)&diag->amax);
+      T < RMS_T4 ? fwd8(u16{}, One{}) : fwd8(u16{}, Four{});
     else if (dt == BS_F32)
       rmsnorm_fwd_kernel<float><<<blocks, 256, 0, st>>>((const float*)X, gain, T, d, eps, u, rstd,
                                                         (uint32_t*)&diag->amax);
@@ -798,8 +852,8 @@ template bs_status launch_gain_t<u16>(const GainArgs<u16>&, float*, float*, floa
 bs_status launch_gain_se(const float* part, int K, int64_t T, int64_t d, const float* scale, const float* gain,
                          double* S, float* se, hipStream_t st) {
   if (d <= 0) return BS_OK;
-  const int64_t nrt = (T + 31) / 32;
-  gain_trial_sum_kernel<<<dim3((unsigned)((d + 255) / 256), (unsigned)K), 256, 0, st>>>(part, nrt, d, S);
+  const int64_t rows = colsum_rows(T, d, K), nrt = (T + rows - 1) / rows;
+  gain_trial_sum_kernel<<<dim3((unsigned)((d + 63) / 64), (unsigned)K), 256, 0, st>>>(part, nrt, d, S);
   gain_se_kernel<<<(unsigned)((d + 15) / 16), 256, 0, st>>>(S, K, d, scale, gain, se);
   BS_CHECK_LAUNCH();
   return BS_OK;

@@ -252,7 +252,7 @@ __global__ __launch_bounds__(256) void quantize_kernel(const T* __restrict__ x, 
 // K-trial counters of new roundings of a [T, d] store y = fl32(x / s) (d % 4 == 0):
 // counts[t, j] = number of trials k whose rounding of element t*d + j goes up. With c = sign(y)
 // step (t, j) w(t, j) the variants with weights also give
-//   FC_COLSUM: colsum[k-1][rt][j] = sum over 32 rows (row tile rt) of up_k c (w = w1), fp32
+//   FC_COLSUM: colsum[k-1][rt][j] = sum over 4 RPT rows (row tile rt) of up_k c (w = w1), fp32
 //   FC_BLOCKSUM: partial[k-1][i][b] = sum over block b's elements of up_k c_i (w1, w2), fp64
 // Bound by the Philox rounds (8.5 VALU per word beside the shared first rounds) and the decision.
 // Counts alone: the tensor as flat groups (k_fresh.h). 16384 x 8192 x 64 trials: 2.80 ms, 3.07 T
@@ -282,8 +282,8 @@ __global__ __launch_bounds__(fresh_nt(TS)) void fresh_count_kernel(FreshArgs<X> 
     if (blk.group(r) < ngroups) *(uint2*)(a.counts + 4 * blk.group(r)) = out[r];
 }
 
-// With weights. Block: 256 threads = 64 column groups (4 columns each) x 4 row lanes, 8 rows per
-// thread, so one block covers 32 rows x 256 columns. The row lane is the wave, except for
+// With weights. Block: 256 threads = 64 column groups (4 columns each) x 4 row lanes, RPT rows per
+// thread, so one block covers 4 RPT rows x 256 columns. The row lane is the wave, except for
 // FC_COLSUM, where a wave holds 16 column groups x 4 row lanes so that the column sums reduce
 // inside the wave (cross-lane adds in a fixed order, no barrier) and, with TS > 1 trial parts, the
 // block's TS waves share the 16 column groups (64 columns).
@@ -303,10 +303,10 @@ __device__ __forceinline__ float swap_add(float a, float b) {
   return __uint_as_float(r.x) + __uint_as_float(r.y);
 }
 
-template <typename X, int MODE, int TS>
+template <typename X, int MODE, int TS, int RPT>
 __device__ __forceinline__ void fresh_weighted_body(const FreshArgs<X>& a) {
-  static_assert(TS == 1 || MODE == FC_COLSUM, "trial parts: the column sums only");
-  constexpr int RT = 32, RPT = 8, TB = MODE == FC_COLSUM ? 1 : 4;
+  static_assert((TS == 1 && RPT == 8) || MODE == FC_COLSUM, "trial parts, fewer rows: the column sums only");
+  constexpr int RT = 4 * RPT, TB = MODE == FC_COLSUM ? 1 : 4;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int part = TS > 1 ? wave : 0;
   const int tx = MODE == FC_COLSUM ? (TS > 1 ? 0 : wave * 16) + (lane & 15) : lane;
@@ -445,11 +445,11 @@ __device__ __forceinline__ void fresh_weighted_body(const FreshArgs<X>& a) {
 // three waves share each SIMD (the Philox latency needs them).
 template <typename X>
 __global__ __launch_bounds__(256) void fresh_blocksum_kernel(FreshArgs<X> a) {
-  fresh_weighted_body<X, FC_BLOCKSUM, 1>(a);
+  fresh_weighted_body<X, FC_BLOCKSUM, 1, 8>(a);
 }
-template <typename X, int TS>
+template <typename X, int TS, int RPT>
 __global__ __launch_bounds__(TS > 4 ? 64 * TS : 256) void fresh_colsum_kernel(FreshArgs<X> a) {
-  fresh_weighted_body<X, FC_COLSUM, TS>(a);
+  fresh_weighted_body<X, FC_COLSUM, TS, RPT>(a);
 }
 
 // ------------------------------------------------------------------------------------
@@ -509,16 +509,18 @@ bs_status launch_fresh_count_t(const FreshArgs<X>& a, int mode, hipStream_t st) 
       fresh_count_kernel<X, decltype(g)::value, decltype(ts)::value><<<blocks, nt, 0, st>>>(a);
     });
   } else if (mode == FC_COLSUM) {
-    // 64-column blocks with 4 or 8 trial parts where 256-column blocks leave SIMDs idle
-    const unsigned rt = (unsigned)((a.T + 31) / 32);
-    const int64_t waves = ((a.d + 63) / 64) * rt;
-    const dim3 g64((unsigned)((a.d + 63) / 64), rt);
+    // 64-column blocks with 4 or 8 trial parts (and 8-row tiles) where 256-column blocks leave SIMDs idle
+    const int rows = (int)colsum_rows(a.T, a.d, a.K);
+    const int64_t waves = ((a.d + 63) / 64) * ((a.T + 31) / 32);
+    const dim3 g64((unsigned)((a.d + 63) / 64), (unsigned)((a.T + rows - 1) / rows));
     if (waves >= 1024 || a.K < 4)
-      fresh_colsum_kernel<X, 1><<<dim3((unsigned)((a.d + 255) / 256), rt), 256, 0, st>>>(a);
+      fresh_colsum_kernel<X, 1, 8><<<dim3((unsigned)((a.d + 255) / 256), g64.y), 256, 0, st>>>(a);
+    else if (rows == 32)
+      fresh_colsum_kernel<X, 4, 8><<<g64, 256, 0, st>>>(a);
     else if (waves >= 256 || a.K < 8)
-      fresh_colsum_kernel<X, 4><<<g64, 256, 0, st>>>(a);
+      fresh_colsum_kernel<X, 4, 2><<<g64, 256, 0, st>>>(a);
     else
-      fresh_colsum_kernel<X, 8><<<g64, 512, 0, st>>>(a);
+      fresh_colsum_kernel<X, 8, 2><<<g64, 512, 0, st>>>(a);
   } else {
     fresh_blocksum_kernel<X><<<dim3((unsigned)((a.d + 255) / 256), (unsigned)((a.T + 31) / 32)), 256, 0, st>>>(a);
   }

@@ -167,7 +167,7 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(const u16* __restri
     uint32_t w[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) w[i] = (uint32_t)tile[q + 2 * i][cc] | ((uint32_t)tile[q + 2 * i + 1][cc] << 16);
-    if (c < C) *(uint4*)(out + c * ldo + r0 + q) = make_uint4(w[0], w[1], w[2], w[3]);
+    if (c < C && r0 + q < ldo) *(uint4*)(out + c * ldo + r0 + q) = make_uint4(w[0], w[1], w[2], w[3]);
   }
 }
 
@@ -200,7 +200,7 @@ __global__ __launch_bounds__(256) void transpose_split_f32_kernel(const float* _
   for (int pass = 0; pass < 2; ++pass) {
     const int cc = (threadIdx.x >> 3) + 32 * pass;
     const int64_t c = c0 + cc;
-    if (c >= C) continue;
+    if (c >= C || r0 + 8 * rg >= ldo) continue;
     u16 o[8][3];
 #pragma unroll
     for (int i = 0; i < 8; ++i) split_to(tile[8 * rg + i][cc], nterms, o[i]);
@@ -250,9 +250,9 @@ bs_status launch_planes(const void* in, bs_dtype dt, int64_t R, int64_t C, int64
   if (transpose) {
     if (C <= 0 || ldo <= 0) return BS_OK;
     dim3 grid((unsigned)((C + 63) / 64), (unsigned)((ldo + 63) / 64));
-    const bool vec = dt == BS_BF16 && nterms == 1 && scale == 1.0f && C % 8 == 0 && ldi % 8 == 0 && ldo % 64 == 0 &&
+    const bool vec = dt == BS_BF16 && nterms == 1 && scale == 1.0f && C % 8 == 0 && ldi % 8 == 0 && ldo % 8 == 0 &&
                      ((uintptr_t)in & 15) == 0 && ((uintptr_t)outp[0] & 15) == 0;
-    bool vecf = dt == BS_F32 && C % 4 == 0 && ldi % 4 == 0 && ldo % 64 == 0 && ((uintptr_t)in & 15) == 0;
+    bool vecf = dt == BS_F32 && C % 4 == 0 && ldi % 4 == 0 && ldo % 8 == 0 && ((uintptr_t)in & 15) == 0;
     for (int p = 0; p < nterms; ++p) vecf = vecf && ((uintptr_t)outp[p] & 15) == 0;
     if (vec)
       transpose_bf16_kernel<false><<<grid, 256, 0, st>>>((const u16*)in, R, C, ldi, outp[0], ldo, nullptr, nullptr);

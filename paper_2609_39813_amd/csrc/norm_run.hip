@@ -82,7 +82,7 @@ NormWs carve_norm(Carver& c, int64_t T, int64_t d, int64_t n, int K, bs_dtype wt
   if (p.gain_n || p.weight_n[0]) w.counts_g = c.take<u16>(T * d);
   if (p.weight_n[1]) w.counts_w = c.take<u16>(T * d);
   if (p.gain_se) {
-    w.partial = c.take<float>((int64_t)K * ((T + 31) / 32) * d + 1);
+    w.partial = c.take<float>((int64_t)K * ((T + colsum_rows(T, d, K) - 1) / colsum_rows(T, d, K)) * d + 1);
     w.trial_sums = c.take<double>((int64_t)K * d);
   }
   if (p.want_dxr) w.dx_r = c.take<float>(T * d);

@@ -77,6 +77,7 @@ def test_ragged_all_policies(lib, dtype, fwd_mode):
     (70, 64, 20),      # 16 trial parts (counts), 8 (column sums), uneven
     (600, 264, 17),    # 4 parts (counts), a ragged last 64-column block
     (1100, 1024, 5),   # one part (counts), 4 (column sums), uneven
+    (1100, 1024, 120), # column sums of 32-row tiles (8-row tiles' would pass 64 MB)
     (4200, 1024, 5),   # 8 groups per thread, 256-column blocks
 ])
 def test_trial_parts_of_the_new_rounding_counters(lib, T, d, K):
