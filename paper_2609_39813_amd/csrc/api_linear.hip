@@ -228,8 +228,7 @@ bs_status bs_linear_bwd_policy(const void* X, const void* W, const void* dY, bs_
       cx.bias[i] = w.bx[0];
       cw.bias[i] = w.bw[sharing[i]];
     }
-    BS_TRY(launch_combine_multi(cx, mk, st));
-    BS_TRY(launch_combine_multi(cw, kn, st));
+    BS_TRY(launch_combine_multi(cx, mk, cw, kn, CombineMulti{}, 0, st));
   }
   // se over trials (App. C.4), the per-trial path: trial k's residual fresh_k - dY moves dX and dW
   // by contractions of its planes; shifted fp64 sums over trials. dX reads use +1 under both

@@ -165,6 +165,10 @@ bs_status launch_split_move(const MoveSrc& m, const float* base, int64_t ldb, in
 // AMAX_SLOTS array), 2^-e to inv_out (nullable). Exact where |in| 2^e >= 2^-17 (fp16 subnormal
 // spacing); below, the error is at most 2^-25 2^-e.
 bs_status launch_scale_f16(const u16* in, int64_t n, const uint32_t* slots, u16* out, float* inv_out, hipStream_t st);
+// launch_planes of a contiguous fp32 [R, C] in both layouts from one read: transposed into outT
+// [C][ldo], row-major into rows [R][C]
+bs_status launch_planes_both(const float* in, int64_t R, int64_t C, u16* const* outT, int64_t ldo, u16* const* rows,
+                             int nterms, hipStream_t st);
 // its transpose: out[c*ldo + r] for r < ldo (zero for r >= R) of a bf16 [R][C]
 bs_status launch_transpose_f16(const u16* in, int64_t R, int64_t C, int64_t ldi, const uint32_t* slots, u16* out,
                                int64_t ldo, float* inv_out, hipStream_t st);

@@ -478,8 +478,7 @@ bs_status grid_run(const GridIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
                                                   : nullptr;
     if (q.weight_use == BS_WREAD_N) cw.bias2[i] = w.bias_w[1];
   }
-  BS_TRY(launch_combine_multi(cg, d, st));
-  BS_TRY(launch_combine_multi(cw, d * n, st));
+  BS_TRY(launch_combine_multi(cg, d, cw, d * n, CombineMulti{}, 0, st));
   return BS_OK;
 }
 

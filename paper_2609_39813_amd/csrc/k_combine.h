@@ -18,6 +18,8 @@ struct CombineMulti {
   const float* alt[COMBINE_MAX_POL];
   float *mean, *bias_out, *se_out;  // bases of [n_pol][n] outputs (nullable)
 };
-bs_status launch_combine_multi(CombineMulti c, int64_t n, hipStream_t st);
+// Up to three gradients' estimates in one launch, n elements each (0: none).
+bs_status launch_combine_multi(const CombineMulti& a, int64_t na, const CombineMulti& b, int64_t nb,
+                                const CombineMulti& c, int64_t nc, hipStream_t st);
 
 }  // namespace bsp

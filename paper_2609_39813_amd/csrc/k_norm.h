@@ -25,6 +25,7 @@ struct NormPlaneArgs {
   const float* amax_u = nullptr;  // device max |u| (nullable)
   float* inv_out = nullptr;
   float resn_scale = 1.0f;        // a power of two that keeps K max-step within fp16
+  u16* rows = nullptr;            // NP_VAL, nullable: the values row-major too, [T, d] bf16 (d % 4 == 0, 16-byte planes)
 };
 
 // rows per block of the gain use's column partial sums (the partial array holds one row of

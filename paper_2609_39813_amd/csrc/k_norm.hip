@@ -254,6 +254,7 @@ __global__ __launch_bounds__(256) void norm_planes_t4_kernel(NormPlaneArgs a) {
         uv[2] = u4.z;
         uv[3] = u4.w;
       }
+      u16 rowv[4] = {0, 0, 0, 0};
       uint32_t cn[4] = {0, 0, 0, 0};
       if (MODE == NP_RESN) {
         const uint2 c2 = *(const uint2*)(a.counts + e);
@@ -268,6 +269,7 @@ __global__ __launch_bounds__(256) void norm_planes_t4_kernel(NormPlaneArgs a) {
         if (MODE == NP_VAL) {
           const float v = f8_value(code, a.f);
           o[0][c][i] = a.f16 ? f16_bits(v) : bf16_bits(v);
+          rowv[c] = bf16_bits(v);
         } else if (MODE == NP_RESU) {
           const float r = fmaf(-s, f8_value(code, a.f), uv[c]);
           if (a.f16) {
@@ -288,6 +290,9 @@ __global__ __launch_bounds__(256) void norm_planes_t4_kernel(NormPlaneArgs a) {
             split3(signbit(y) ? -v : v, o[0][c][i], o[1][c][i], o[2][c][i]);
         }
       }
+      if (MODE == NP_VAL && a.rows)
+        *(uint2*)(a.rows + e) = make_uint2((uint32_t)rowv[0] | ((uint32_t)rowv[1] << 16),
+                                           (uint32_t)rowv[2] | ((uint32_t)rowv[3] << 16));
     }
   }
 #pragma unroll
@@ -773,7 +778,7 @@ bs_status launch_norm_planes(int mode, const NormPlaneArgs& a, hipStream_t st) {
   if (a.d <= 0 || a.ldo <= 0) return BS_OK;
   dim3 grid((unsigned)((a.d + 63) / 64), (unsigned)((a.ldo + 63) / 64));
   bool vec = a.d % 4 == 0 && a.ldo % 64 == 0 && ((uintptr_t)a.u & 15) == 0 && ((uintptr_t)a.codes & 3) == 0 &&
-             ((uintptr_t)a.counts & 7) == 0;
+             ((uintptr_t)a.counts & 7) == 0 && ((uintptr_t)a.rows & 7) == 0;
   for (int p = 0; p < a.nterms; ++p) vec = vec && ((uintptr_t)a.out[p] & 15) == 0;
   if (vec) {
     if (mode == NP_VAL)
@@ -782,7 +787,9 @@ bs_status launch_norm_planes(int mode, const NormPlaneArgs& a, hipStream_t st) {
       norm_planes_t4_kernel<NP_RESU><<<grid, 256, 0, st>>>(a);
     else
       norm_planes_t4_kernel<NP_RESN><<<grid, 256, 0, st>>>(a);
-  } else if (mode == NP_VAL)
+  } else if (a.rows)
+    return BS_EINVAL;  // the general kernel writes planes only
+  else if (mode == NP_VAL)
     norm_planes_t_kernel<NP_VAL><<<grid, 256, 0, st>>>(a);
   else if (mode == NP_RESU)
     norm_planes_t_kernel<NP_RESU><<<grid, 256, 0, st>>>(a);
@@ -878,11 +885,12 @@ __device__ __forceinline__ void store4_nt(float* p, float4 v) {
   __builtin_nontemporal_store(w, (f32x4*)p);
 }
 
-__global__ __launch_bounds__(256) void combine_multi_kernel(CombineMulti c, int64_t n) {
+// blocks first .. first + blocks - 1 of the launch
+__device__ __forceinline__ void combine_body(const CombineMulti& c, int64_t n, unsigned first, unsigned blocks) {
   const int64_t n4 = c.vec ? n / 4 : 0;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t stride = (int64_t)blocks * 256, i0 = (int64_t)(blockIdx.x - first) * 256 + threadIdx.x;
   const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) {
+  for (int64_t i = i0; i < n4; i += stride) {
     const float4 r = ((const float4*)c.ref)[i];
     for (int p = 0; p < c.n_pol; ++p) {
       const int64_t o = (int64_t)p * n4 + i;
@@ -904,7 +912,7 @@ __global__ __launch_bounds__(256) void combine_multi_kernel(CombineMulti c, int6
       if (c.se_out) store4_nt(c.se_out + 4 * o, c.se[p] ? ((const float4*)c.se[p])[i] : z);
     }
   }
-  for (int64_t i = 4 * n4 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+  for (int64_t i = 4 * n4 + i0; i < n; i += stride) {
     const float r = c.ref[i];
     for (int p = 0; p < c.n_pol; ++p) {
       const int64_t o = (int64_t)p * n + i;
@@ -917,6 +925,16 @@ __global__ __launch_bounds__(256) void combine_multi_kernel(CombineMulti c, int6
     }
   }
 }
+// One launch for a call's gradients: three launches of 256 x 64 x 64 took 10 us.
+__global__ __launch_bounds__(256) void combine_multi_kernel(CombineMulti a, int64_t na, CombineMulti b, int64_t nb,
+                                                             CombineMulti c, int64_t nc, unsigned ba, unsigned bb) {
+  if (blockIdx.x < ba)
+    combine_body(a, na, 0, ba);
+  else if (blockIdx.x < ba + bb)
+    combine_body(b, nb, ba, bb);
+  else
+    combine_body(c, nc, ba + bb, gridDim.x - ba - bb);
+}
 
 bs_status launch_gain_final(const double* part, int64_t nrt, int64_t d, float* ref, float* bias_r, float* bias_n,
                             hipStream_t st, int nz, int64_t s_part, int64_t s_ref) {
@@ -928,18 +946,30 @@ bs_status launch_gain_final(const double* part, int64_t nrt, int64_t d, float* r
   return BS_OK;
 }
 
-bs_status launch_combine_multi(CombineMulti c, int64_t n, hipStream_t st) {
-  if (n <= 0 || c.n_pol < 1 || (!c.mean && !c.bias_out && !c.se_out)) return BS_OK;
-  if (c.n_pol > COMBINE_MAX_POL) return BS_EINVAL;
-  // the float4 path needs every array 16-byte aligned, including each policy's output slice
-  bool vec = n % 4 == 0;
-  for (const void* q : {(const void*)c.ref, (const void*)c.mean, (const void*)c.bias_out, (const void*)c.se_out})
+// whether there is anything to write, and c.vec: 16-byte accesses throughout
+static bool combine_ready(CombineMulti& c, int64_t n) {
+  if (n <= 0 || c.n_pol < 1 || (!c.mean && !c.bias_out && !c.se_out)) return false;
+  bool vec = n % 4 == 0 && ((uintptr_t)c.ref & 15) == 0;
+  for (const void* q : {(const void*)c.mean, (const void*)c.bias_out, (const void*)c.se_out})
     vec = vec && ((uintptr_t)q & 15) == 0;
   for (int p = 0; p < c.n_pol; ++p)
     for (const void* q : {(const void*)c.bias[p], (const void*)c.bias2[p], (const void*)c.se[p], (const void*)c.alt[p]})
       vec = vec && ((uintptr_t)q & 15) == 0;
   c.vec = vec ? 1 : 0;
-  combine_multi_kernel<<<grid1d((n + 3) / 4, 4096), 256, 0, st>>>(c, n);
+  return true;
+}
+bs_status launch_combine_multi(const CombineMulti& a, int64_t na, const CombineMulti& b, int64_t nb,
+                                const CombineMulti& c, int64_t nc, hipStream_t st) {
+  CombineMulti m[3] = {a, b, c};
+  const int64_t n[3] = {na, nb, nc};
+  unsigned blocks[3];
+  for (int i = 0; i < 3; ++i) {
+    if (m[i].n_pol > COMBINE_MAX_POL) return BS_EINVAL;
+    blocks[i] = combine_ready(m[i], n[i]) ? grid1d((n[i] + 3) / 4, 4096) : 0;
+  }
+  if (blocks[0] + blocks[1] + blocks[2] == 0) return BS_OK;
+  combine_multi_kernel<<<blocks[0] + blocks[1] + blocks[2], 256, 0, st>>>(m[0], na, m[1], nb, m[2], nc, blocks[0],
+                                                                           blocks[1]);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }

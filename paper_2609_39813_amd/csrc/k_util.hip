@@ -179,7 +179,7 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(const u16* __restri
 // output row.
 __global__ __launch_bounds__(256) void transpose_split_f32_kernel(const float* __restrict__ in, int64_t R, int64_t C,
                                                                   int64_t ldi, PlaneOut out, int nterms, int64_t ldo,
-                                                                  float scale) {
+                                                                  float scale, PlaneOut rows) {
   __shared__ float tile[64][65];
   const int c4 = threadIdx.x & 15, rq = threadIdx.x >> 4;
   const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
@@ -193,6 +193,16 @@ __global__ __launch_bounds__(256) void transpose_split_f32_kernel(const float* _
     tile[rr][4 * c4 + 1] = v.y * scale;
     tile[rr][4 * c4 + 2] = v.z * scale;
     tile[rr][4 * c4 + 3] = v.w * scale;
+    if (rows.p[0] && r < R && c < C) {  // row-major planes of the same terms, leading dimension C
+      u16 o[4][3];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) split_to(tile[rr][4 * c4 + q], nterms, o[q]);
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        if (p < nterms)
+          *(uint2*)(rows.p[p] + r * C + c) = make_uint2((uint32_t)o[0][p] | ((uint32_t)o[1][p] << 16),
+                                                        (uint32_t)o[2][p] | ((uint32_t)o[3][p] << 16));
+    }
   }
   __syncthreads();
   const int rg = threadIdx.x & 7;
@@ -257,7 +267,7 @@ bs_status launch_planes(const void* in, bs_dtype dt, int64_t R, int64_t C, int64
     if (vec)
       transpose_bf16_kernel<false><<<grid, 256, 0, st>>>((const u16*)in, R, C, ldi, outp[0], ldo, nullptr, nullptr);
     else if (vecf)
-      transpose_split_f32_kernel<<<grid, 256, 0, st>>>((const float*)in, R, C, ldi, out, nterms, ldo, scale);
+      transpose_split_f32_kernel<<<grid, 256, 0, st>>>((const float*)in, R, C, ldi, out, nterms, ldo, scale, PlaneOut{});
     else if (dt == BS_F32)
       planes_t_kernel<float><<<grid, 256, 0, st>>>((const float*)in, R, C, ldi, out, nterms, ldo, scale, nullptr, nullptr);
     else
@@ -283,6 +293,26 @@ bs_status launch_planes(const void* in, bs_dtype dt, int64_t R, int64_t C, int64
     else
       planes_rows_kernel<u16><<<blocks, 256, 0, st>>>((const u16*)in, R, C, ldi, out, nterms, ldo, scale);
   }
+  BS_CHECK_LAUNCH();
+  return BS_OK;
+}
+
+bs_status launch_planes_both(const float* in, int64_t R, int64_t C, u16* const* outT, int64_t ldo, u16* const* rows,
+                             int nterms, hipStream_t st) {
+  bool vec = nterms >= 1 && nterms <= 3 && R > 0 && C > 0 && C % 4 == 0 && ldo % 8 == 0 && ldo >= R &&
+             ((uintptr_t)in & 15) == 0;
+  PlaneOut t{}, r{};
+  for (int p = 0; vec && p < nterms; ++p) {
+    t.p[p] = outT[p];
+    r.p[p] = rows[p];
+    vec = ((uintptr_t)outT[p] & 15) == 0 && ((uintptr_t)rows[p] & 7) == 0;
+  }
+  if (!vec) {
+    const bs_status rc = launch_planes(in, BS_F32, R, C, C, false, rows, nterms, C, 1.0f, st);
+    return rc != BS_OK ? rc : launch_planes(in, BS_F32, R, C, C, true, outT, nterms, ldo, 1.0f, st);
+  }
+  transpose_split_f32_kernel<<<dim3((unsigned)((C + 63) / 64), (unsigned)((ldo + 63) / 64)), 256, 0, st>>>(
+      in, R, C, C, t, nterms, ldo, 1.0f, r);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }

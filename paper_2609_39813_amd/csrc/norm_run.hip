@@ -187,10 +187,42 @@ bs_status norm_run(const NormIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
   if (io.u_out) w.u = io.u_out;
   BS_TRY(launch_store(w.u, BS_F32, T * d, fmt, fwd_mode, seed, 0, base, nullptr, u_codes, u_scale, diag, st, true));
 
+  const bool h16 = !fwd_only && use_f16(wt, gt, K);
+  // the forward's values: the weight use's operand [d, Tp] and the Linear's rows, one read of the codes
+  NormPlaneArgs pa{};
+  pa.u = w.u;
+  pa.codes = u_codes;
+  pa.scale = u_scale;
+  pa.K = K;
+  pa.f = f;
+  pa.T = T;
+  pa.d = d;
+  pa.ldo = Tp;
+  pa.out[0] = w.uvalT;
+  pa.nterms = 1;
+  pa.f16 = h16;
+  pa.amax_u = &diag->amax;
+  pa.inv_out = h16 ? w.inv + 2 : nullptr;
+  // the N residual is an up-count difference (|.| <= K <= 256) times a step: exact in fp16 for
+  // E4M3 (steps 2^-9 .. 2^5); E5M2's steps 2^-16 .. 2^13 take the scale 2^-8 (2^-24 .. 2^13)
+  pa.resn_scale = fmt == BS_E5M2 ? 0x1p-8f : 1.0f;
+  // (caller's codes at an odd address: the rows by a launch of their own)
+  const bool val_both = Y && !fwd_only && ((uintptr_t)u_codes & 3) == 0 && ((uintptr_t)w.u & 15) == 0;
+  if (Y && !val_both) BS_TRY(launch_val_rows(u_codes, T * d, fmt, w.uval_rows, st));
+  if (!fwd_only) {
+    pa.rows = val_both ? w.uval_rows : nullptr;
+    BS_TRY(launch_norm_planes(NP_VAL, pa, st));
+    pa.rows = nullptr;
+  }
+  // W's planes in both layouts from one read where the forward and du both take them
+  const bool w_both = Y && !fwd_only && wt == BS_F32;
+
   // Linear forward Y = s val(C_u) W  (A = val rows [T, d], B = W^T [n, d])
   if (Y) {
-    BS_TRY(launch_val_rows(u_codes, T * d, fmt, w.uval_rows, st));
-    BS_TRY(launch_planes(W, wt, d, n, n, true, w.wT, ntw, d, 1.0f, st));
+    if (w_both)
+      BS_TRY(launch_planes_both((const float*)W, d, n, w.wT, d, w.w_rows, 3, st));
+    else
+      BS_TRY(launch_planes(W, wt, d, n, n, true, w.wT, ntw, d, 1.0f, st));
     GemmArgs g{};
     g.M = (int)T;
     g.N = (int)n;
@@ -206,7 +238,6 @@ bs_status norm_run(const NormIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
   }
   if (fwd_only) return BS_OK;
 
-  const bool h16 = use_f16(wt, gt, K);
   const bool du16 = h16 && n % 64 == 0;  // du's fp16 contraction runs on the pipelined kernel (K % 64)
   const int ntd = h16 ? 2 : nt;  // terms of the incoming gradient's planes
   if (h16) {
@@ -257,11 +288,14 @@ bs_status norm_run(const NormIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
     u16* const* Aops = &A0;
     u16* const* Bops = &B0;
     if (gt == BS_F32) {
-      BS_TRY(launch_planes(dY, gt, T, n, n, false, w.dy_rows, 3, n, 1.0f, st));
+      if (h16)
+        BS_TRY(launch_planes(dY, gt, T, n, n, false, w.dy_rows, 3, n, 1.0f, st));
+      else
+        BS_TRY(launch_planes_both((const float*)dY, T, n, w.dyT, Tp, w.dy_rows, 3, st));
       Aops = w.dy_rows;
     }
     if (wt == BS_F32) {
-      BS_TRY(launch_planes(W, wt, d, n, n, false, w.w_rows, 3, n, 1.0f, st));
+      if (!w_both) BS_TRY(launch_planes(W, wt, d, n, n, false, w.w_rows, 3, n, 1.0f, st));
       Bops = w.w_rows;
     }
     gemm_add_products(g, Aops, gt == BS_F32 ? 3 : 1, Bops, wt == BS_F32 ? 3 : 1);
@@ -269,26 +303,7 @@ bs_status norm_run(const NormIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
   }
 
   // weight-use operands in the contraction layout [*, Tp]
-  if (!h16) BS_TRY(launch_planes(dY, gt, T, n, n, true, w.dyT, nt, Tp, 1.0f, st));
-  NormPlaneArgs pa{};
-  pa.u = w.u;
-  pa.codes = u_codes;
-  pa.scale = u_scale;
-  pa.K = K;
-  pa.f = f;
-  pa.T = T;
-  pa.d = d;
-  pa.ldo = Tp;
-  pa.out[0] = w.uvalT;
-  pa.nterms = 1;
-  pa.f16 = h16;
-  pa.amax_u = &diag->amax;
-  pa.inv_out = h16 ? w.inv + 2 : nullptr;
-  // the N residual is an up-count difference (|.| <= K <= 256) times a step: exact in fp16 for
-  // E4M3 (steps 2^-9 .. 2^5); E5M2's steps 2^-16 .. 2^13 take the scale 2^-8 (2^-24 .. 2^13)
-  pa.resn_scale = fmt == BS_E5M2 ? 0x1p-8f : 1.0f;
-  BS_TRY(launch_norm_planes(NP_VAL, pa, st));
-
+  if (!h16 && gt != BS_F32) BS_TRY(launch_planes(dY, gt, T, n, n, true, w.dyT, nt, Tp, 1.0f, st));
   auto weight_gemm = [&](u16* const* A, int nA, float* C, float alpha, const float* alpha_dev) -> bs_status {
     GemmArgs g{};
     g.M = (int)d;
@@ -417,9 +432,7 @@ bs_status norm_run(const NormIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
       cw.se[i] = (q.weight_use == BS_READ_N && p.weight_se[fs]) ? w.se_w[fs] : nullptr;
       cx.alt[i] = q.norm_input_use == BS_READ_R ? w.dx_r : nullptr;
     }
-    BS_TRY(launch_combine_multi(cg, d, st));
-    BS_TRY(launch_combine_multi(cw, d * n, st));
-    BS_TRY(launch_combine_multi(cx, T * d, st));
+    BS_TRY(launch_combine_multi(cg, d, cw, d * n, cx, T * d, st));
   }
   return BS_OK;
 }

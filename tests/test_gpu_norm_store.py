@@ -93,6 +93,21 @@ def test_trial_parts_of_the_new_rounding_counters(lib, T, d, K):
     compare(out, ref, pols, rows=rows, cols=cols, xrows=xrows, d=d, n=n)
 
 
+def test_operands_off_16_bytes_take_the_same_values(lib):
+    """fp32 W and dY one element past a 16-byte boundary: planes of each layout by a launch of their
+    own, the same terms."""
+    X, g, W, dY = [t.cuda() for t in synth.rmsnorm_linear_inputs(130, 72, 64, torch.float32, 2)]
+    off = [torch.cat([t.new_zeros(1), t.reshape(-1)])[1:].view(t.shape) for t in (W, dY)]
+    kw = dict(fmt="e4m3", policies=["U/N", "N/R"], K=5, seed=3)
+    a = lib.rmsnorm_linear(X, g, W, dY, **kw)
+    b = lib.rmsnorm_linear(X, g, *off, **kw)
+    torch.cuda.synchronize()
+    for k in ("Y", "dgain_ref", "dW_ref", "dX_ref"):
+        assert torch.equal(a[k], b[k]), k
+    for k in ("dgain", "dW", "dX"):
+        assert torch.equal(a[k]["mean"], b[k]["mean"]), k
+
+
 def test_shared_new_rounding_and_norm_input_R(lib):
     T, d, n = 130, 64, 72
     pols = ("N/N", "U/N", "R/R")
