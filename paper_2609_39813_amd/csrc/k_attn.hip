@@ -351,12 +351,17 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_k_kernel(AttnBwdArgs a) {
   // wave w loads row arrays NRW w .. NRW w + NRW - 1 of (m, l, D[, dD_R, dD_N, -, -, -]).
   // Queries past S, a missing dD_v and the padding (empty resources) read as zero; every wave
   // issues NL + NRW loads per query block.
-  const float* row_src[8] = {a.m, a.l, a.D_ref + z * a.z_rows, BIAS ? a.dD_R : nullptr, BIAS ? a.dD_N : nullptr,
-                             nullptr, nullptr, nullptr};
+  // (by the wave's index as a scalar: by a lane's, the resources would be loaded lane by lane)
+  const int wu = __builtin_amdgcn_readfirstlane(w);
+  auto row_src = [&](int i) -> const float* {
+    const float* p = i == 0 ? a.m : (i == 1 ? a.l : (i == 2 ? a.D_ref + z * a.z_rows : nullptr));
+    if (BIAS) p = i == 3 ? a.dD_R : (i == 4 ? a.dD_N : p);
+    return p;
+  };
   __amdgpu_buffer_rsrc_t rq[NRW];
 #pragma unroll
   for (int k = 0; k < NRW; ++k) {
-    const float* base = row_src[NRW * w + k];
+    const float* base = row_src(NRW * wu + k);
     rq[k] = __builtin_amdgcn_make_buffer_rsrc((void*)(base ? base + rb : a.m), (short)0, base ? a.S * 4 : 0,
                                               0x00020000);
   }

@@ -407,7 +407,9 @@ __global__ __launch_bounds__(TE_BLOCK) __attribute__((amdgpu_waves_per_eu(3, 8))
   block_total(v, mx, a.part_dq + 4 * block_linear());
 }
 
-// key-major: dK = c s_dS sum_q val(dS_q) Q, dV = s_P s_dO sum_q val(P_q) val(dO_q), both cast at s_g
+// key-major: dK = c s_dS sum_q val(dS_q) Q, dV = s_P s_dO sum_q val(P_q) val(dO_q), both cast at s_g.
+// Bound by the latency of a tile's loads: they are issued a query block ahead. 64 heads of 1024: 23 us
+// (56 with the tiles' registers in scratch, see below).
 __global__ __launch_bounds__(TE_BLOCK) void te_dkv_kernel(TeArgs a) {
   __shared__ __attribute__((aligned(16))) u16 sm[2][2][AT * AT];  // Q^T, dO_q^T
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, c16 = lane & 15;
@@ -419,15 +421,11 @@ __global__ __launch_bounds__(TE_BLOCK) void te_dkv_kernel(TeArgs a) {
   floatx4 ak[4], av[4];
 #pragma unroll
   for (int n = 0; n < 4; ++n) ak[n] = av[n] = floatx4{0.f, 0.f, 0.f, 0.f};
-  TileRegs pf[2];
-  auto fetch = [&](int q0) {
-    tile_fetch_t(pf[0], a.Qt + tb, q0, a.Sp);
-    tile_fetch_t(pf[1], a.dOt + tb, q0, a.Sp);
-  };
-  auto put = [&](int st) {
-    tile_put_t(sm[st][0], pf[0]);
-    tile_put_t(sm[st][1], pf[1]);
-  };
+  // this thread's 16-byte pieces of a tile (rows r, r + 32 of Q^T and dO_q^T), held by name and
+  // loaded under no condition: in an array filled under one they pass through scratch, and the
+  // loop waits for them where they are issued
+  const int64_t po = tb + (int64_t)(threadIdx.x >> 3) * a.Sp + (threadIdx.x & 7) * 8, p32 = (int64_t)32 * a.Sp;
+  const u16 *pq = a.Qt + po, *pd = a.dOt + po;
   // the lane's key's codes of one query block: bytes 16 g .. 16 g + 15 of its tile row (queries
   // 32 s2 + 16 hh + 4 g + r at byte 8 s2 + 4 hh + r), loaded one step ahead of their use
   auto load_codes = [&](int qb_, uint4& d, uint4& p) {
@@ -438,14 +436,21 @@ __global__ __launch_bounds__(TE_BLOCK) void te_dkv_kernel(TeArgs a) {
   const int qb0 = a.causal ? kb : 0;
   uint4 cd, cp;
   load_codes(qb0, cd, cp);
-  fetch(qb0 * AT);
-  put(0);
+  tile_put(sm[0][0], TileRegs{{*(const uint4*)(pq + qb0 * AT), *(const uint4*)(pq + p32 + qb0 * AT)}});
+  tile_put(sm[0][1], TileRegs{{*(const uint4*)(pd + qb0 * AT), *(const uint4*)(pd + p32 + qb0 * AT)}});
   __syncthreads();
-  for (int qb = qb0; qb < nqb; ++qb) {
-    const int st = (qb - qb0) & 1, q0 = qb * AT;
-    if (qb + 1 < nqb) fetch(q0 + AT);
-    uint4 nd = make_uint4(0, 0, 0, 0), np = make_uint4(0, 0, 0, 0);
-    if (qb + 1 < nqb) load_codes(qb + 1, nd, np);
+  auto step = [&](int qb, auto last) {
+    constexpr bool LAST = decltype(last)::value;
+    const int st = (qb - qb0) & 1, q1 = (qb + 1) * AT;
+    uint4 q0{}, q32{}, d0{}, d32{}, nd{}, np{};
+    if constexpr (!LAST) {
+      q0 = *(const uint4*)(pq + q1);
+      q32 = *(const uint4*)(pq + p32 + q1);
+      d0 = *(const uint4*)(pd + q1);
+      d32 = *(const uint4*)(pd + p32 + q1);
+      load_codes(qb + 1, nd, np);
+      __builtin_amdgcn_sched_barrier(0);  // issued here, not at their use
+    }
     const uint32_t dwd[4] = {cd.x, cd.y, cd.z, cd.w}, dwp[4] = {cp.x, cp.y, cp.z, cp.w};
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2) {
@@ -474,11 +479,16 @@ __global__ __launch_bounds__(TE_BLOCK) void te_dkv_kernel(TeArgs a) {
         av[n] = mfma(tp, frag_t(sm[st][1], 16 * n + c16, s2, g), av[n]);
       }
     }
-    cd = nd;
-    cp = np;
-    if (qb + 1 < nqb) put(st ^ 1);
-    __syncthreads();
-  }
+    if constexpr (!LAST) {
+      cd = nd;
+      cp = np;
+      tile_put(sm[st ^ 1][0], TileRegs{{q0, q32}});
+      tile_put(sm[st ^ 1][1], TileRegs{{d0, d32}});
+      __syncthreads();
+    }
+  };
+  for (int qb = qb0; qb + 1 < nqb; ++qb) step(qb, std::false_type{});
+  step(nqb - 1, std::true_type{});
   const float ck = (a.qkv ? a.scale * a.qkv[0] : a.scale) * sdS, cv = sP * sdO;  // dK: c (s_Q) s_dS
   const double rg = 1.0 / (double)sg;
   const int64_t numel = (int64_t)a.BH * a.S * AT;
