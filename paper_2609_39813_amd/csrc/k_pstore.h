@@ -54,12 +54,13 @@ struct PstoreArgs {
                                     // bit 2 (jn - 1 - j)), tiles as the fields, each tile's words
                                     // thread-major (16 per thread)
   int draw_a, draw_b;               // a policy reads new rounding a / b (else their draws are skipped)
-  float* fld[PF_COUNT];             // [BH][pstore_tiles][64 k][64 q] fp32, tile by (query block, key block)
+  float* fld[PF_COUNT];             // [BH][pstore_tiles][64 x 64] fp32, tile by (query block, key block)
   float *dQ_ref, *dK_ref, *dV_ref;  // [BH][S][64]
   // the policies' estimates, written by the passes' epilogues: mean = reference + bias
   int n_pol;
   int sm_field[PSTORE_MAXPOL];      // bias field of the softmax read: PF_R .. PF_Q2, or PF_REF = none
   int v_field[PSTORE_MAXPOL];       // dV read: 0 none (R), 1 p - p_q (U), 2 mean a - p_q (N)
+  uint32_t need;                    // bit i: field i enters an estimate (the reference's always); others are skipped
   PstoreOut dQ, dK, dV;
 };
 

@@ -41,18 +41,32 @@ __device__ __forceinline__ Resid resid(float p, float val, float s, double rs, F
   return o;
 }
 
-// one output element of every policy: mean = ref + bias[field], bias = bias[field] (b[0] = 0
-// for a read that is the reference's own)
+// place of (query q, key k) of a 64 x 64 tile in a field: 16 queries, then 16 keys, together, so that
+// the query-major pass stores 256 contiguous bytes at once (a lane's query, keys 4 g + r for fixed r)
+// and the key-major pass loads 1 KB (four queries of a lane's key). Row-major tiles made 64-byte
+// pieces of both.
+__device__ __forceinline__ int fld_at(int q, int k) {
+  return (q >> 4) * 1024 + (k >> 4) * 256 + (k & 3) * 64 + ((k >> 2) & 3) * 16 + (q & 15);
+}
+
+// one output element of the policies that read field id[j] (0: the reference's own read, bias 0):
+// mean = ref + b[j], bias = b[j]
 template <int NF>
 __device__ __forceinline__ void write_policies(const PstoreArgs& a, const int (&field)[PSTORE_MAXPOL],
-                                               const PstoreOut& o, int64_t e, float ref, const float (&b)[NF]) {
+                                               const PstoreOut& o, int64_t e, float ref, const int (&id)[NF],
+                                               const float (&b)[NF]) {
 #pragma unroll
   for (int i = 0; i < PSTORE_MAXPOL; ++i) {
     if (i >= a.n_pol) break;
     const int fi = field[i];
     float bi = 0.0f;
+    bool mine = false;
 #pragma unroll
-    for (int j = 1; j < NF; ++j) bi = fi == j ? b[j] : bi;
+    for (int j = 0; j < NF; ++j) {
+      mine |= fi == id[j];
+      bi = fi == id[j] && fi ? b[j] : bi;
+    }
+    if (!mine) continue;
     if (o.mean[i]) o.mean[i][e] = fi ? ref + bi : ref;
     if (o.bias[i]) o.bias[i][e] = bi;
   }
@@ -379,9 +393,12 @@ __global__ __launch_bounds__(256, 2) void pstore_rows_kernel(PstoreArgs a) {
 
 // ------------------------------------------------------------------------------------
 // bias fields and dQ: per element the sums over trials, then the fields of every read; the
-// fields go to memory for the key-major pass and into dQ = c sum_k field K (three bf16 terms)
+// fields go to memory for the key-major pass and into dQ = c sum_k field K (three bf16 terms).
+// Bound by the VALU work (445 instructions an element with every field, 256 of them the trial
+// sums of K = 32) at one wave per SIMD (six fields' accumulators): 730 us at 64 heads of 1024.
 // ------------------------------------------------------------------------------------
-template <int FMT>
+// ALL: every field is needed; AB: the trial sums of b too (J2 is)
+template <int FMT, bool ALL, bool AB>
 __global__ __launch_bounds__(256) void pstore_dq_kernel(PstoreArgs a) {
   __shared__ __attribute__((aligned(16))) u16 sm[2][3][AT * AT];  // K, V, K^T
   __shared__ float tv[3][AT][PSTORE_KMAX + 1];                     // Ga, Ha, Gb of the block's queries
@@ -417,7 +434,7 @@ __global__ __launch_bounds__(256) void pstore_dq_kernel(PstoreArgs a) {
   mGb *= iK;
   const float dDa = E + mGa, dDb = E + mGb, rho = Ee + mHa;
   const int nqb = (a.S + AT - 1) / AT;
-  const int nchunk = (a.ntrial + PSTORE_RC - 1) / PSTORE_RC;
+  const int nchunk = a.draw_a ? (a.ntrial + PSTORE_RC - 1) / PSTORE_RC : 0;  // no draw: no up-decision
   const int64_t plane = (int64_t)a.BH * pstore_tiles(nqb, a.causal) * AT * AT;
   // a chunk of jn trials fills the top 2 jn bits of its reversed word (an absent chunk: 0)
   int sh[2];
@@ -508,17 +525,19 @@ __global__ __launch_bounds__(256) void pstore_dq_kernel(PstoreArgs a) {
 #pragma unroll 2
         for (int j = 0; j < jn; ++j) {
           const int k = PSTORE_RC * c + j;
-          const float gak = tv[0][ql][k], hak = tv[1][ql][k], gbk = tv[2][ql][k];
+          const float gak = tv[0][ql][k], hak = tv[1][ql][k], gbk = AB ? tv[2][ql][k] : 0.0f;
 #pragma unroll
           for (int tt = 0; tt < 2; ++tt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
               const float ua = (float)((nw[c][tt][r] >> (2 * j)) & 1u);
-              const float vb = (float)((nw[c][tt][r] >> (2 * j + 1)) & 1u);
               uga[tt][r] = fmaf(ua, gak, uga[tt][r]);
               uha[tt][r] = fmaf(ua, hak, uha[tt][r]);
-              ugab[tt][r] = fmaf(ua, gbk, ugab[tt][r]);
-              ugba[tt][r] = fmaf(vb, gak, ugba[tt][r]);
+              if (AB) {
+                const float vb = (float)((nw[c][tt][r] >> (2 * j + 1)) & 1u);
+                ugab[tt][r] = fmaf(ua, gbk, ugab[tt][r]);
+                ugba[tt][r] = fmaf(vb, gak, ugba[tt][r]);
+              }
             }
         }
       }
@@ -544,12 +563,13 @@ __global__ __launch_bounds__(256) void pstore_dq_kernel(PstoreArgs a) {
           fl[PF_VU][tt][r] = -rr;
           fl[PF_VN][tt][r] = m1a - rr;
         }
-        // store: tile (qb, kb) as [key][query]
+        // store: fld_at (one store instruction's 256 bytes are contiguous)
 #pragma unroll
         for (int i = 0; i < PF_COUNT; ++i) {
+          if (!ALL && !(a.need >> i & 1u)) continue;
           float* T = a.fld[i] + tile;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) T[(16 * t + 4 * z.g + r) * AT + 16 * z.w + z.c16] = fl[i][tt][r];
+          for (int r = 0; r < 4; ++r) T[1024 * z.w + 256 * t + 64 * r + 16 * z.g + z.c16] = fl[i][tt][r];
         }
       }
       // dQ terms of the softmax fields (k index: keys 32 s2 + 16 (v >> 2) + 4 g + (v & 3))
@@ -558,6 +578,7 @@ __global__ __launch_bounds__(256) void pstore_dq_kernel(PstoreArgs a) {
       for (int n = 0; n < 4; ++n) fk[n] = frag_t(sm[st][2], 16 * n + z.c16, s2, z.g);
 #pragma unroll
       for (int i = 0; i < PF_SOFTMAX; ++i) {
+        if (!ALL && !(a.need >> i & 1u)) continue;
         float vd[8];
 #pragma unroll
         for (int v = 0; v < 8; ++v) vd[v] = fl[i][v >> 2][v & 3];
@@ -588,22 +609,35 @@ __global__ __launch_bounds__(256) void pstore_dq_kernel(PstoreArgs a) {
       const int64_t e = z.hb + (int64_t)qr * AT + 16 * n + z.c16;
       const float ref = c * aq[PF_REF][n][r];
       float b[PF_SOFTMAX];
+      int id[PF_SOFTMAX];
 #pragma unroll
-      for (int i = 0; i < PF_SOFTMAX; ++i) b[i] = c * aq[i][n][r];
+      for (int i = 0; i < PF_SOFTMAX; ++i) {
+        b[i] = c * aq[i][n][r];
+        id[i] = i;
+      }
       a.dQ_ref[e] = ref;
-      write_policies(a, a.sm_field, a.dQ, e, ref, b);
+      write_policies(a, a.sm_field, a.dQ, e, ref, id, b);
     }
   }
 }
 
 // ------------------------------------------------------------------------------------
-// key-major, one launch per gradient (PART 0: dK, PART 1: dV). dK = c sum_q field Q (three bf16
-// terms per field); dV = s sum_q val(C) dO (one term), its biases sum_q (p - p_q) dO and
-// sum_q (mean a - p_q) dO (three terms each). Lane (g, c16) of wave w owns key k0 + 16 w + c16.
+// key-major, the needed fields: dK = c sum_q field Q (three bf16 terms per field) for the fields
+// id[0..NF-1] (the reference first); DV: dV = s sum_q val(C) dO (one term) and its biases
+// sum_q field dO. Lane (g, c16) of wave w owns key k0 + 16 w + c16.
+// Bound by the fields' bytes, read back at 2.6 TB/s (64 heads of 1024, all eight fields: 1.14 GB,
+// 435 us; half the registers at twice the waves, or other orders of a tile, read no faster). A half
+// tile's fields are loaded while the half before is multiplied, and no load is under a condition:
+// behind one the compiler waits for every load before it, and an array filled there goes through
+// scratch. Fields no policy reads are neither stored nor read: J(p_q), J(a), K(a) and a mean of a
+// over dV, K = 32, take 1339 us in all, 1627 with every field.
 // ------------------------------------------------------------------------------------
-template <int FMT, int PART>
-__global__ __launch_bounds__(256) void pstore_dkv_kernel(PstoreArgs a) {
-  constexpr int NACC = PART == 0 ? PF_SOFTMAX : 3;
+struct PstoreIds {
+  int id[PF_SOFTMAX];
+};
+template <int FMT, int NF, bool DV>
+__global__ __launch_bounds__(256) void pstore_dkv_kernel(PstoreArgs a, PstoreIds f) {
+  constexpr int NA = NF + (DV ? 1 : 0);  // DV: the codes' accumulator is the last
   __shared__ __attribute__((aligned(16))) u16 sm[2][AT * AT];  // Q^T (dK) or dO^T (dV)
   if (a.diag->nonfinite) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = lane >> 4, c16 = lane & 15;
@@ -613,86 +647,99 @@ __global__ __launch_bounds__(256) void pstore_dkv_kernel(PstoreArgs a) {
   const int key = k0 + 16 * w + c16;
   const int64_t hb = (int64_t)bh * a.S * AT, tb = (int64_t)bh * AT * a.Sp;
   const int nqb = (a.S + AT - 1) / AT;
-  const float s = a.diag->scale;
-  const u16* src = PART == 0 ? a.Qt : a.dOt;
-  floatx4 acc[NACC][4];
+  const u16* src = (DV ? a.dOt : a.Qt) + tb;
+  const float* fld[NF + 1];
+#pragma unroll
+  for (int i = 0; i < NF; ++i) fld[i] = a.fld[f.id[i]] + fld_at(0, 16 * w + c16) + 4 * g;
+  const uint8_t* codes = a.codes + (int64_t)bh * a.S * a.S + min(key, a.S - 1);
+  floatx4 acc[NA][4];
 #pragma unroll
   for (int n = 0; n < 4; ++n)
 #pragma unroll
-    for (int i = 0; i < NACC; ++i) acc[i][n] = floatx4{0.f, 0.f, 0.f, 0.f};
-  TileRegs pf;
+    for (int i = 0; i < NA; ++i) acc[i][n] = floatx4{0.f, 0.f, 0.f, 0.f};
+  // this thread's two 16-byte pieces of a tile (rows r, r + 32 of the transposed operand)
+  const u16* pr = src + (int64_t)(threadIdx.x >> 3) * a.Sp + (threadIdx.x & 7) * 8;
+  const int64_t pr32 = (int64_t)32 * a.Sp;
   const int qb0 = a.causal ? kb : 0;
-  tile_fetch_t(pf, src + tb, qb0 * AT, a.Sp);
-  tile_put_t(sm[0], pf);
+  // queries 32 s2 + 16 hh + 4 g + (0..3) of this lane's key, as the k index of the products
+  auto load = [&](int64_t tile, int qb, int s2, float4 (&v)[NF + 1][2], uint32_t (&cd)[8]) {
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh) v[i][hh] = *(const float4*)(fld[i] + tile + fld_at(32 * s2 + 16 * hh, 0));
+    if (DV) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int qq = qb * AT + 32 * s2 + 16 * (u >> 2) + 4 * g + (u & 3);
+        cd[u] = codes[(int64_t)min(qq, a.S - 1) * a.S];
+      }
+    }
+  };
+  float4 cur[NF + 1][2];
+  uint32_t ccur[8] = {};
+  int64_t tile = fld_tile(a, bh, qb0, kb, nqb);
+  load(tile, qb0, 0, cur, ccur);
+  tile_put(sm[0], TileRegs{{*(const uint4*)(pr + qb0 * AT), *(const uint4*)(pr + pr32 + qb0 * AT)}});
   __syncthreads();
-  for (int qb = qb0; qb < nqb; ++qb) {
-    const int st = (qb - qb0) & 1, q0 = qb * AT;
-    if (qb + 1 < nqb) tile_fetch_t(pf, src + tb, q0 + AT, a.Sp);
-    const int64_t tile = fld_tile(a, bh, qb, kb, nqb);
+  auto step = [&](int qb, auto last) {
+    constexpr bool LAST = decltype(last)::value;
+    const int st = (qb - qb0) & 1;
+    const int64_t tile_n = tile + (int64_t)(a.causal ? qb + 1 : nqb) * (AT * AT);
+    uint4 p0{}, p1{};
+    if constexpr (!LAST) {
+      p0 = *(const uint4*)(pr + (qb + 1) * AT);
+      p1 = *(const uint4*)(pr + pr32 + (qb + 1) * AT);
+    }
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2) {
-      // queries 32 s2 + 16 hh + 4 g + (0..3) of this lane's key, as the k index of the products
+      float4 nxt[NF + 1][2] = {};
+      uint32_t cnxt[8] = {};
+      if (!LAST || s2 == 0) load(s2 == 0 ? tile : tile_n, qb + s2, s2 ^ 1, nxt, cnxt);
+      __builtin_amdgcn_sched_barrier(0);  // issued here, not at their use
       bf16x8 fo[4];
 #pragma unroll
       for (int n = 0; n < 4; ++n) fo[n] = frag_t(sm[st], 16 * n + c16, s2, g);
-      auto fields = [&](int i, float (&v)[8]) {
-        const float* T = a.fld[i] + tile + (int64_t)(16 * w + c16) * AT + 32 * s2 + 4 * g;
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-          const float4 x = *(const float4*)(T + 16 * hh);
-          v[4 * hh + 0] = x.x;
-          v[4 * hh + 1] = x.y;
-          v[4 * hh + 2] = x.z;
-          v[4 * hh + 3] = x.w;
-        }
-      };
-      if (PART == 0) {
-        float vals[PF_SOFTMAX][8];
+      for (int i = 0; i < NF; ++i) {
+        const float4 x = cur[i][0], y = cur[i][1];
+        const float v[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+        bf16x8 td[3];
+        pack3(v, td);
 #pragma unroll
-        for (int i = 0; i < PF_SOFTMAX; ++i) fields(i, vals[i]);
+        for (int n = 0; n < 4; ++n)
 #pragma unroll
-        for (int i = 0; i < PF_SOFTMAX; ++i) {
-          bf16x8 td[3];
-          pack3(vals[i], td);
+          for (int j = 0; j < 3; ++j) acc[i][n] = mfma(td[j], fo[n], acc[i][n]);
+      }
+      if (DV) {  // val(C) of (query, key) for the same eight queries (exact in bf16), 0 past S
+        float cv[8];
 #pragma unroll
-          for (int n = 0; n < 4; ++n)
-#pragma unroll
-            for (int j = 0; j < 3; ++j) acc[i][n] = mfma(td[j], fo[n], acc[i][n]);
-        }
-      } else {
-        float vu[8], vn[8], cv[8];
-        fields(PF_VU, vu);
-        fields(PF_VN, vn);
-        // val(C) of (query, key) for the same eight queries (exact in bf16)
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-          const int qq = q0 + 32 * s2 + 16 * (v >> 2) + 4 * g + (v & 3);
-          const bool ok = qq < a.S && key < a.S;
-          const uint32_t b = ok ? a.codes[((int64_t)bh * a.S + qq) * a.S + key] : 0u;
-          cv[v] = f8_val<FMT>(b, 0);
+        for (int u = 0; u < 8; ++u) {
+          const int qq = qb * AT + 32 * s2 + 16 * (u >> 2) + 4 * g + (u & 3);
+          cv[u] = f8_val<FMT>(qq < a.S && key < a.S ? ccur[u] : 0u, 0);
         }
         uint32_t pk[4];
 #pragma unroll
-        for (int i2 = 0; i2 < 4; ++i2) pk[i2] = pk_bf16(cv[2 * i2], cv[2 * i2 + 1]);
+        for (int u = 0; u < 4; ++u) pk[u] = pk_bf16(cv[2 * u], cv[2 * u + 1]);
         const bf16x8 tv = __builtin_bit_cast(bf16x8, make_uint4(pk[0], pk[1], pk[2], pk[3]));
-        bf16x8 tu[3], tn[3];
-        pack3(vu, tu);
-        pack3(vn, tn);
 #pragma unroll
-        for (int n = 0; n < 4; ++n) {
-          acc[0][n] = mfma(tv, fo[n], acc[0][n]);
-#pragma unroll
-          for (int j = 0; j < 3; ++j) {
-            acc[1][n] = mfma(tu[j], fo[n], acc[1][n]);
-            acc[2][n] = mfma(tn[j], fo[n], acc[2][n]);
-          }
-        }
+        for (int n = 0; n < 4; ++n) acc[NF][n] = mfma(tv, fo[n], acc[NF][n]);
       }
+#pragma unroll
+      for (int i = 0; i < NF; ++i)
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) cur[i][hh] = nxt[i][hh];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) ccur[u] = cnxt[u];
     }
-    if (qb + 1 < nqb) tile_put_t(sm[st ^ 1], pf);
-    __syncthreads();
-  }
-  const float c = a.scale;
+    if constexpr (!LAST) {
+      tile_put(sm[st ^ 1], TileRegs{{p0, p1}});
+      tile = tile_n;
+      __syncthreads();
+    }
+  };
+  for (int qb = qb0; qb + 1 < nqb; ++qb) step(qb, std::false_type{});
+  step(nqb - 1, std::true_type{});
+  const float c = a.scale, s = a.diag->scale;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int kr = k0 + 16 * w + 4 * g + r;
@@ -700,18 +747,23 @@ __global__ __launch_bounds__(256) void pstore_dkv_kernel(PstoreArgs a) {
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
       const int64_t e = hb + (int64_t)kr * AT + 16 * n + c16;
-      if (PART == 0) {
-        const float ref = c * acc[PF_REF][n][r];
-        float b[PF_SOFTMAX];
+      float b[NF + 1];
+      int id[NF + 1];
 #pragma unroll
-        for (int i = 0; i < PF_SOFTMAX; ++i) b[i] = c * acc[i][n][r];
-        a.dK_ref[e] = ref;
-        write_policies(a, a.sm_field, a.dK, e, ref, b);
-      } else {
-        const float ref = s * acc[0][n][r];
-        const float b[3] = {0.0f, acc[1][n][r], acc[2][n][r]};
+      for (int i = 0; i < NF; ++i) {
+        b[i] = DV ? acc[i][n][r] : c * acc[i][n][r];
+        id[i] = DV ? (f.id[i] == PF_VU ? 1 : 2) : f.id[i];
+      }
+      b[NF] = 0.0f;
+      id[NF] = DV ? 0 : id[0];
+      if (DV) {
+        const float ref = s * acc[NF][n][r];
         a.dV_ref[e] = ref;
-        write_policies(a, a.v_field, a.dV, e, ref, b);
+        write_policies(a, a.v_field, a.dV, e, ref, id, b);
+      } else {
+        b[NF] = b[0];
+        a.dK_ref[e] = b[0];
+        write_policies(a, a.sm_field, a.dK, e, b[0], id, b);
       }
     }
   }
@@ -736,7 +788,6 @@ bs_status launch_pstore_fwd(const PstoreArgs& a, hipStream_t st) {
   return BS_OK;
 }
 
-#define BS_PSTORE_KM(KERNEL, FMTV) KERNEL<FMTV><<<pstore_grid(a), 256, 0, st>>>(a)
 
 template <int FMT>
 static void rows_draw(const PstoreArgs& a, hipStream_t st) {
@@ -760,27 +811,59 @@ bs_status launch_pstore_rows(const PstoreArgs& a, hipStream_t st) {
   return BS_OK;
 }
 
+template <int FMT>
+static void dq_fields(const PstoreArgs& a, hipStream_t st) {
+  if (a.need == (1u << PF_COUNT) - 1)
+    pstore_dq_kernel<FMT, true, true><<<pstore_grid(a), 256, 0, st>>>(a);
+  else if (a.draw_b)
+    pstore_dq_kernel<FMT, false, true><<<pstore_grid(a), 256, 0, st>>>(a);
+  else
+    pstore_dq_kernel<FMT, false, false><<<pstore_grid(a), 256, 0, st>>>(a);
+}
+
 bs_status launch_pstore_dq(const PstoreArgs& a, hipStream_t st) {
   if (a.ntrial < 1 || a.ntrial > PSTORE_KMAX) return BS_EINVAL;
   ProfScope prof("pstore_dq", st);
   if (a.fmt == BS_E5M2)
-    BS_PSTORE_KM(pstore_dq_kernel, BS_E5M2);
+    dq_fields<BS_E5M2>(a, st);
   else
-    BS_PSTORE_KM(pstore_dq_kernel, BS_E4M3);
+    dq_fields<BS_E4M3>(a, st);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }
-#undef BS_PSTORE_KM
+
+template <int FMT>
+static void dkv_parts(const PstoreArgs& a, hipStream_t st) {
+  const dim3 grid = pstore_grid(a);
+  int id[PF_COUNT], n = 0;
+  for (int i = 0; i < PF_SOFTMAX; ++i)
+    if (a.need >> i & 1u) id[n++] = i;
+  PstoreIds d{};
+  for (int i = 0; i < n; ++i) d.id[i] = id[i];
+  switch (n) {  // the reference is the first
+    case 1: pstore_dkv_kernel<BS_E4M3, 1, false><<<grid, 256, 0, st>>>(a, d); break;
+    case 2: pstore_dkv_kernel<BS_E4M3, 2, false><<<grid, 256, 0, st>>>(a, d); break;
+    case 3: pstore_dkv_kernel<BS_E4M3, 3, false><<<grid, 256, 0, st>>>(a, d); break;
+    case 4: pstore_dkv_kernel<BS_E4M3, 4, false><<<grid, 256, 0, st>>>(a, d); break;
+    case 5: pstore_dkv_kernel<BS_E4M3, 5, false><<<grid, 256, 0, st>>>(a, d); break;
+    default: pstore_dkv_kernel<BS_E4M3, 6, false><<<grid, 256, 0, st>>>(a, d); break;
+  }
+  const bool vu = a.need >> PF_VU & 1u, vn = a.need >> PF_VN & 1u;
+  const PstoreIds f{{vu ? PF_VU : PF_VN, PF_VN, 0}};
+  if (vu && vn)
+    pstore_dkv_kernel<FMT, 2, true><<<grid, 256, 0, st>>>(a, f);
+  else if (vu || vn)
+    pstore_dkv_kernel<FMT, 1, true><<<grid, 256, 0, st>>>(a, f);
+  else
+    pstore_dkv_kernel<FMT, 0, true><<<grid, 256, 0, st>>>(a, f);
+}
 
 bs_status launch_pstore_dkv(const PstoreArgs& a, hipStream_t st) {
   ProfScope prof("pstore_dkv", st);
-  if (a.fmt == BS_E5M2) {
-    pstore_dkv_kernel<BS_E5M2, 0><<<pstore_grid(a), 256, 0, st>>>(a);
-    pstore_dkv_kernel<BS_E5M2, 1><<<pstore_grid(a), 256, 0, st>>>(a);
-  } else {
-    pstore_dkv_kernel<BS_E4M3, 0><<<pstore_grid(a), 256, 0, st>>>(a);
-    pstore_dkv_kernel<BS_E4M3, 1><<<pstore_grid(a), 256, 0, st>>>(a);
-  }
+  if (a.fmt == BS_E5M2)
+    dkv_parts<BS_E5M2>(a, st);
+  else
+    dkv_parts<BS_E4M3>(a, st);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }

@@ -156,6 +156,7 @@ bs_status pstore_run(const PstoreIO& io, void* ws, size_t ws_bytes, hipStream_t 
     a.draw_a |= (sm == BS_SM_N || sm == BS_SM_K || sm == BS_SM_J2 || sm == BS_SM_Q2 || io.pol[i].v_read == BS_READ_N);
     a.draw_b |= sm == BS_SM_J2;
   }
+  a.need = 1u << PF_REF;
   a.dQ_ref = io.dQ_ref;
   a.dK_ref = io.dK_ref;
   a.dV_ref = io.dV_ref;
@@ -164,6 +165,8 @@ bs_status pstore_run(const PstoreIO& io, void* ws, size_t ws_bytes, hipStream_t 
     const int vr = io.pol[i].v_read;
     a.sm_field[i] = softmax_field(io.pol[i].softmax_read);
     a.v_field[i] = vr == BS_READ_U ? 1 : (vr == BS_READ_N ? 2 : 0);
+    a.need |= 1u << a.sm_field[i];
+    if (a.v_field[i]) a.need |= 1u << (a.v_field[i] == 1 ? PF_VU : PF_VN);
     auto at = [&](float* base) { return base ? base + (int64_t)i * numel : nullptr; };
     a.dQ.mean[i] = at(io.dQ.mean);
     a.dQ.bias[i] = at(io.dQ.bias);

@@ -96,6 +96,22 @@ def test_trial_count_limits_and_policy_order(lib, Kt):
         assert torch.equal(out[name]["mean"][0], out[name]["mean"][3])
 
 
+@pytest.mark.parametrize("pols", [
+    ("U/R",),                      # the reference alone
+    ("R/U",),                      # two fields of dK, one of dV
+    ("R/R", "N/N"),                # three; new rounding a alone
+    ("R/R", "N/N", "K/R"),         # four
+    ("K/U", "J2/N", "Q2/R", "R/R"),# five, without N's; a and b
+])
+def test_only_the_fields_read_are_formed(lib, pols):
+    """Every count of fields in the key-major passes, at two query blocks and a ragged third."""
+    Q, K, V, dO = inputs(1, 2, 132, seed=len(pols))
+    for causal in (True, False):
+        out = run(lib, Q, K, V, dO, causal=causal, pols=pols, Kt=18, seed=4)
+        ref = oracle_of(out, Q, K, V, dO, causal=causal, fmt="e4m3", fwd_mode="rne", pols=pols, Kt=18, seed=4)
+        compare(out, ref, pols, Q, K, causal)
+
+
 def test_exact_zeros_of_the_table(lib):
     """U/R and R/R read the reference at dV, U/U and U/R at the softmax: their biases are 0."""
     Q, K, V, dO = inputs(1, 1, 100, seed=9)
