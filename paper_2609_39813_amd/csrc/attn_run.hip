@@ -1,6 +1,9 @@
 // The attention runner: forward (row max / row sum, and O when not handed in), the FP8 store of
 // O, the D variants of every policy, and the two-pass multi-D backward.
 #include "attn_run.h"
+
+#include <algorithm>
+
 #include "k_attn.h"
 #include "k_norm.h"
 
@@ -18,15 +21,23 @@ struct AttnWs {
   u16 *Vt, *Qt, *Kt, *dOp[3], *dOt[3];
   float *dO_mean, *stat;   // level 2: mean incoming gradient; split of R and N [2][4][rows]
   uint8_t* codes;          // level 2: the trial-0 store when the caller takes none
-  float *dD_tr, *tdk, *d1, *sek, *dK_s, *dV_s;  // dK's se: per-trial dD, one trial's dK move, shift, scratch
+  float *dD_tr, *tdk, *d1, *sek;  // dK's se: per-trial dD, a launch's trials' dK moves, shift
   double *S1, *S2;
 };
+// trials of dK's se side by side in one launch: one alone does not fill the chip at small shapes (16 heads
+// of 250: 22 us for 1, 36 for 8). Past 2^22 elements of dK it does.
+int dk_trials_together(int64_t numel, int K) {
+  int n = 1;
+  while (n < 16 && n < K && 2 * n * numel <= (int64_t)1 << 22) n *= 2;
+  return n;
+}
 AttnWs carve_attn(Carver& c, int64_t rows, int64_t numel, bool need_o, bool need_dref, int64_t bh = 0, int64_t Sp = 0,
                   int ndo = 0, bool level2 = false, int K = 0) {
   AttnWs w{};
   if (K > 0) {
     w.dD_tr = c.take<float>((int64_t)K * rows);
-    for (float** p : {&w.tdk, &w.d1, &w.sek, &w.dK_s, &w.dV_s}) *p = c.take<float>(numel);
+    w.tdk = c.take<float>(dk_trials_together(numel, K) * numel);
+    for (float** p : {&w.d1, &w.sek}) *p = c.take<float>(numel);
     w.S1 = c.take<double>(numel);
     w.S2 = c.take<double>(numel);
   }
@@ -190,8 +201,7 @@ bs_status attn_run(const AttnIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
     if (dk_trials) {
       AttnBwdArgs bt = ba;
       bt.k_only = 1;
-      bt.dK_ref = w.dK_s;
-      bt.dV = w.dV_s;
+      bt.dK_ref = bt.dV = nullptr;
       bt.dD_N = nullptr;
       bt.sd_N = nullptr;
       bt.n_pol = 1;
@@ -199,10 +209,14 @@ bs_status attn_run(const AttnIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
       bt.kmean[0] = nullptr;
       bt.kbias[0] = w.tdk;
       bt.mean[0] = bt.bias[0] = bt.se[0] = nullptr;
-      for (int k = 1; k <= io.K; ++k) {
+      bt.z_dd = rows;
+      bt.z_kbias = numel;
+      const int together = dk_trials_together(numel, io.K);
+      for (int k = 1; k <= io.K; k += bt.nz) {
         bt.dD_R = w.dD_tr + (int64_t)(k - 1) * rows;
+        bt.nz = std::min(together, io.K - k + 1);
         BS_TRY(launch_attn_bwd(bt, io.B, io.H, st));
-        BS_TRY(launch_trial_accum(w.tdk, 1, k, numel, w.d1, w.S1, w.S2, st));
+        BS_TRY(launch_trial_accum(w.tdk, bt.nz, k, numel, w.d1, w.S1, w.S2, st));
       }
       BS_TRY(launch_trial_se(w.S1, w.S2, io.K, numel, w.sek, st));
     }

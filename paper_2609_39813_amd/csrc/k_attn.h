@@ -88,6 +88,8 @@ struct AttnBwdArgs {
   // outputs and amax z strides on
   int nz = 1;
   int64_t z_dop = 0, z_dot = 0, z_rows = 0, z_inv = 0, z_out = 0, z_amax = 0;
+  // other operands, k_only with dK_ref and dV null: nz dD_R side by side, dD_R and kbias z strides on
+  int64_t z_dd = 0, z_kbias = 0;
 };
 
 bs_status launch_attn_fwd(const AttnArgs& a, int B, int H, hipStream_t st);

@@ -293,7 +293,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_k_kernel(AttnBwdArgs a) {
   const int k0 = kb * AT;
   const int64_t hb = (int64_t)bh * a.S * AT, tb = (int64_t)bh * AT * a.Sp, rb = (int64_t)bh * a.S;
   const int key = k0 + 16 * w + c16;
-  const int z = H ? blockIdx.z : 0;  // gradient z of the launch
+  const int z = blockIdx.z;  // gradient (BIAS: dD_R) z of the launch
   const float* inv = a.f16_inv + z * a.z_inv;
   const float dps = H ? inv[0] * inv[1] : 1.0f, avs = H ? inv[0] * 0x1p-14f : 1.0f;
   const float dsc = H ? inv[4] : 1.0f, dkm = H ? inv[5] : 1.0f;
@@ -355,7 +355,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_k_kernel(AttnBwdArgs a) {
   const int wu = __builtin_amdgcn_readfirstlane(w);
   auto row_src = [&](int i) -> const float* {
     const float* p = i == 0 ? a.m : (i == 1 ? a.l : (i == 2 ? a.D_ref + z * a.z_rows : nullptr));
-    if (BIAS) p = i == 3 ? a.dD_R : (i == 4 ? a.dD_N : p);
+    if (BIAS) p = i == 3 ? (a.dD_R ? a.dD_R + z * a.z_dd : nullptr) : (i == 4 ? a.dD_N : p);
     return p;
   };
   __amdgpu_buffer_rsrc_t rq[NRW];
@@ -517,6 +517,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_k_kernel(AttnBwdArgs a) {
     if (qb + 1 < nqb) step(qb + 1, rows1, rows0);
   }
   const float c = a.scale;
+  const bool ref = a.dK_ref != nullptr;  // null with dV: the estimates alone
   float *dK = a.dK_ref + z * a.z_out, *dV = a.dV + z * a.z_out;
   float mx = 0.0f;
 #pragma unroll
@@ -527,14 +528,14 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_k_kernel(AttnBwdArgs a) {
     for (int n = 0; n < 4; ++n) {
       const int64_t e = hb + (int64_t)kr * AT + 16 * n + c16;
       const float dk = c * (ak[n][r] * dkm);
-      dV[e] = av[n][r] * avs;
+      if (ref) dV[e] = av[n][r] * avs;
       mx = fmaxf(mx, fmaxf(fabsf(dk), fabsf(av[n][r] * avs)));
-      dK[e] = dk;
+      if (ref) dK[e] = dk;
       for (int pi = 0; pi < a.n_pol; ++pi) {
         const int kind = a.pol[pi];
         const float bias = kind == BS_READ_U ? 0.0f : -c * (kind == BS_READ_R ? akr[n][r] : akn[n][r]);
         if (a.kmean[pi]) a.kmean[pi][e] = dk + bias;
-        if (a.kbias[pi]) a.kbias[pi][e] = bias;
+        if (a.kbias[pi]) a.kbias[pi][z * a.z_kbias + e] = bias;
       }
     }
   }
@@ -1088,13 +1089,15 @@ bs_status launch_attn_split_f16(const float* dO32, int BH, int S, int Sp, int ht
 }
 
 bs_status launch_attn_bwd(const AttnBwdArgs& a, int B, int H, hipStream_t st) {
-  dim3 grid((unsigned)(B * H), (unsigned)((a.S + AT - 1) / AT));
+  if (a.nz < 1 || a.nz > 65535 || (!a.dK_ref) != (!a.dV) || (!a.dK_ref && !a.k_only) ||
+      (a.nz > 1 && !a.V16 && (a.dK_ref || a.dD_N || !a.dD_R)))
+    return BS_EINVAL;
+  dim3 grid((unsigned)(B * H), (unsigned)((a.S + AT - 1) / AT), (unsigned)a.nz);
   ProfScope prof("attn_bwd", st);
   if (a.V16) {
     if (a.dD_R || a.dD_N || a.n_pol > 0 || !a.f16_inv || !a.Qt16 || !a.Kt16 || !a.dOp[0] || !a.dOp[1] || !a.dOt[0] ||
-        !a.dOt[1] || a.nz < 1 || a.nz > 65535)
+        !a.dOt[1])
       return BS_EINVAL;
-    grid.z = (unsigned)a.nz;
     attn_bwd_k_kernel<2, 0, true><<<grid, 256, 0, st>>>(a);
     if (!a.k_only) attn_bwd_q_kernel<2, false, true><<<grid, 256, 0, st>>>(a);
   } else if (a.dO32) {
