@@ -31,12 +31,12 @@ BF16_MFMA_PEAK_TFLOPS = 2500.0
 # operation per lane-slot per clock: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.32e12.
 VALU_LANE_OPS = 256 * 4 * 16 * 2.4e9
 # VALU instructions per element-trial of the K-trial counter as compiled for gfx950: one pass of
-# its trial loop (4 trials x 32 elements per lane) issues 544 v_mad_u64_u32 + 608 v_bitop3_b32
-# (Philox4x32-10; the key schedule and the uniform counter words run on the scalar unit) +
-# 128 v_add_co_u32 (round-up carry) + 128 v_addc_co_u32 (count) = 1408 / 128 = 11.0.
+# its trial loop (4 trials x 32 elements per lane) issues 1365 (Philox4x32-10 in v_mad_u64_u32 and
+# v_bitop3_b32, the key schedule, the uniform counter words and the shared first rounds on the
+# scalar unit; 128 v_add_co_u32 for the round-up carry, 128 v_addc_co_u32 for the count): 10.7.
 # (Written out, Philox needs 10 multiplies and 10 xors per 4 words: 12 per element-trial.)
-OPS_PER_ELEMENT_TRIAL = 1408 / 128
-# Ceiling on element-trials per second: 3.57e12.
+OPS_PER_ELEMENT_TRIAL = 1365 / 128
+# Ceiling on element-trials per second: 3.69e12.
 ALU_PEAK_ETPS = VALU_LANE_OPS / OPS_PER_ELEMENT_TRIAL
 
 # The P store's row-sum pass as compiled for gfx950: one trial of its draw loop over a thread's 16
@@ -132,14 +132,14 @@ def side_measurements(bsp, synth, torch, dev, reps=5):
                                                                 K=cfg4["K"], seed=cfg4["seed"], ws=lws),
                      ("gemm", "gemm_split_sum", "fresh_count", "amax", "quantize"), 3)
     mnk2 = 2.0 * cfg4["M"] * cfg4["k"] * cfg4["n"]
-    segs = 11  # dX_ref, dW_ref, dX bias (3 residual terms), dW bias shared (3), dW bias per use (3)
+    segs = 8  # dX_ref, dW_ref, dX bias (2 residual terms), dW bias shared (2), dW bias per use (2)
     g_s = (t["gemm"] + t["gemm_split_sum"]) / 1e3
     out["linear_bwd_e5m2_16384x2048x8192"] = {
         "policy_trials_per_s": round(len(cfg4["sharings"]) * cfg4["K"] / wall, 1), "call_ms": round(wall * 1e3, 3),
         "gemm_TFLOPs": round(segs * mnk2 / g_s / 1e12, 1),
         "gemm_mfma_frac": round(segs * mnk2 / g_s / 1e12 / BF16_MFMA_PEAK_TFLOPS, 4),
         "kernel_ms": {k: round(v, 4) for k, v in t.items()},
-        "flops": "11 bf16 contractions of 2 M k n each (references and residual terms)"}
+        "flops": "8 bf16 / fp16 contractions of 2 M k n each (references and residual terms)"}
     del Xd, Wd, dy, lws
     torch.cuda.empty_cache()
 
@@ -248,9 +248,9 @@ def side_measurements(bsp, synth, torch, dev, reps=5):
         "call_ms": round(wall * 1e3, 3), "policy_trials_per_s": round(8 * 256 / wall, 1),
         "kernel_ms": {k: round(v, 4) for k, v in t.items()},
         "fresh_Gelement_trials_per_s": round(et / (t["grid_fresh"] / 1e3) / 1e9, 1),
-        "gemm_TFLOPs": round(16 * 2.0 * 8192 * 1024 * 4096 / ((t["gemm"] + t["gemm_split_sum"]) / 1e3) / 1e12, 1),
-        "work": "8 policies, K = 256 new roundings (one Philox word per element-trial); 16 bf16 contractions of "
-                "2 T d n (Y, du, dW_ref and the U, N, R+e biases with 3-term residual operands)"}
+        "gemm_TFLOPs": round(9 * 2.0 * 8192 * 1024 * 4096 / ((t["gemm"] + t["gemm_split_sum"]) / 1e3) / 1e12, 1),
+        "work": "8 policies, K = 256 new roundings (one Philox word per element-trial); 9 fp16 contractions of "
+                "2 T d n (Y, du, dW_ref and the U and R+e biases, with two-term operands; N's is their sum)"}
     del Xg, gg, Wg, dYg, ws
     torch.cuda.empty_cache()
 
@@ -269,7 +269,7 @@ def side_measurements(bsp, synth, torch, dev, reps=5):
         out[tag] = {"call_ms": round(wall * 1e3, 4), "kernel_ms": {k: round(v, 4) for k, v in t.items()},
                     "Gelement_trials_per_s": round(et / (t["lsm_trial"] / 1e3) / 1e9, 2),
                     "stats_mean_se": dict(zip(bsp.LSM_STATS, [[round(a, 8), round(b, 8)] for a, b in st_])),
-                    "work": f"{et} element-trials in fp64 (3 Philox words, 3 exp per element-trial)"}
+                    "work": f"{et} element-trials in fp64 (2 Philox words per element-trial)"}
         del z, yv, ws
     torch.cuda.empty_cache()
 
@@ -362,7 +362,7 @@ def c2_measurement(bsp, synth, torch, dev, steps, warmup):
     bsp.profile_enable(False)
     et = cfg["T"] * cfg["d"] * cfg["K"]
     philox = {}
-    for name, kern, ops in (("fresh_count", "fresh_count_kernel<float, FC_COUNT>", OPS_PER_ELEMENT_TRIAL),
+    for name, kern, ops in (("fresh_count", "fresh_count_kernel<float>", OPS_PER_ELEMENT_TRIAL),
                             ("fresh_count_se", "fresh_colsum_kernel<float>", OPS_PER_ELEMENT_TRIAL + 2)):
         ms, n = prof[name]
         avg = ms / max(n, 1) / 1e3
