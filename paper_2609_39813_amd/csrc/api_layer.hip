@@ -42,9 +42,6 @@ struct WeightUseIO {
   const float* amax_x = nullptr;  // device max |X| (the store's amax; bounds the U residual)
 };
 
-// trials per per-trial contraction (stacked along the output rows)
-inline int wu_trial_batch(int K) { return K < 8 ? K : 8; }
-
 struct WeightUseWs {
   u16 *dyT[3], *valT, *res[3], *counts;
   float *bias_u, *bias_n, *gpart;
@@ -72,7 +69,7 @@ WeightUseWs carve_wu(Carver& c, int64_t T, int64_t k, int64_t n, int K = 1, bool
   w.gpart_cap = 16 * k * n;  // split-K partials: the long-T contraction has few output tiles
   w.gpart = c.take<float>(w.gpart_cap);
   if (se) {
-    const int bt = wu_trial_batch(K);
+    const int bt = se_trial_batch(k, n, Tp, K);
     w.tplanes = c.take<u16>(bt * k * Tp);
     w.tdelta = c.take<float>(bt * k * n);
     w.td1 = c.take<float>(k * n);
@@ -163,7 +160,7 @@ bs_status weight_use_run(const WeightUseIO& io, void* ws, size_t ws_bytes, hipSt
   for (int l = 0; l < 3; ++l)
     BS_TRY(launch_combine(io.dW_ref, b[l], nullptr, kn, nullptr, io.bias + l * kn, nullptr, st));
   if (se) {
-    const int bt = wu_trial_batch(io.K);
+    const int bt = se_trial_batch(io.k, io.n, Tp, io.K);
     for (int k0 = 1; k0 <= io.K; k0 += bt) {
       const int nb = io.K - k0 + 1 < bt ? io.K - k0 + 1 : bt;
       TrialPlaneArgs ta{io.Xs, io.codes, io.scale, pa.f, io.T, io.k, Tp, io.seed, io.use, k0, nb, w.tplanes};

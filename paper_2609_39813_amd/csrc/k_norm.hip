@@ -1,6 +1,8 @@
 // Normalization store (RMSNorm -> FP8 store -> Linear) kernels: forward in the fixed
 // fp32 order, operand planes for the contractions, the gain use's column reductions,
 // the gain use's per-trial standard error, and the normalization input gradient.
+#include <algorithm>
+
 #include "bsp_kernels.h"
 #include "k_norm.h"
 
@@ -362,7 +364,9 @@ __global__ __launch_bounds__(256) void trial_planes_kernel(TrialPlaneArgs a) {
       }
     }
   }
-  for (int b = 0; b < a.nb; ++b) {
+  // the launch's trials in gridDim.z parts
+  const int b1 = (int)((int64_t)(blockIdx.z + 1) * a.nb / gridDim.z);
+  for (int b = (int)((int64_t)blockIdx.z * a.nb / gridDim.z); b < b1; ++b) {
     const uint32_t k = (uint32_t)(a.k0 + b);
     u16 dv[4][4], wv[4][4];  // [c][q]: the difference and the new rounding's value
 #pragma unroll
@@ -806,6 +810,10 @@ bs_status launch_trial_planes(const TrialPlaneArgs& a, hipStream_t st) {
       ((uintptr_t)a.codes & 3))
     return BS_EINVAL;
   dim3 grid((unsigned)((a.d + 63) / 64), (unsigned)((a.ldo + 63) / 64));
+  // few tiles: the trials over enough blocks for four per CU (a part's preparation costs about a trial):
+  // 162 tiles, 8 trials 15.9 us in one part; 24 trials 23.8 us in 6
+  const int64_t tiles = (int64_t)grid.x * grid.y;
+  grid.z = (unsigned)std::min<int64_t>(a.nb, std::max<int64_t>(1, 1024 / std::max<int64_t>(1, tiles)));
   ProfScope prof("trial_planes", st);
   trial_planes_kernel<<<grid, 256, 0, st>>>(a);
   BS_CHECK_LAUNCH();

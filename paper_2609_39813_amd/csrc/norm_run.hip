@@ -15,9 +15,6 @@
 namespace bsp {
 namespace {
 
-// trials per per-trial contraction (stacked along the output rows)
-inline int trial_batch(int K) { return K < 8 ? K : 8; }
-
 struct NormPlan {
   bool gain_n = false, gain_r = false, weight_u = false, want_dxr = false;
   bool weight_n[2] = {false, false};  // use +1 (shared), use +2 (per use)
@@ -87,7 +84,7 @@ NormWs carve_norm(Carver& c, int64_t T, int64_t d, int64_t n, int K, bs_dtype wt
   }
   if (p.want_dxr) w.dx_r = c.take<float>(T * d);
   if (p.weight_se[0] || p.weight_se[1]) {
-    const int bt = trial_batch(K);
+    const int bt = se_trial_batch(d, n, Tp, K);
     w.tplanes = c.take<u16>((int64_t)bt * d * Tp);
     w.tdelta = c.take<float>((int64_t)bt * d * n);
     w.td1 = c.take<float>(d * n);
@@ -370,7 +367,7 @@ bs_status norm_run(const NormIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
   // the output), shifted fp64 sums over trials, sample SD / sqrt(K)
   for (int i = 0; i < 2; ++i) {
     if (!p.weight_se[i]) continue;
-    const int bt = trial_batch(K);
+    const int bt = se_trial_batch(d, n, Tp, K);
     for (int k0 = 1; k0 <= K; k0 += bt) {
       const int nb = K - k0 + 1 < bt ? K - k0 + 1 : bt;
       TrialPlaneArgs ta{w.u, u_codes, u_scale, f, T, d, Tp, seed, use_w[i], k0, nb, w.tplanes};

@@ -165,6 +165,26 @@ def test_weight_use_se_per_trial(lib):
         compare(out, ref, pols, d=d, n=n)
 
 
+@pytest.mark.parametrize("T,d,n,K", [
+    (70, 64, 72, 33),       # few tiles: 32 trials in a launch over 32 parts, and one more
+    (1100, 1024, 64, 11),   # 288 tiles: 3 parts of uneven trials
+])
+def test_weight_use_se_trial_batches_and_parts(lib, T, d, n, K):
+    X, g, W, dY = synth.rmsnorm_linear_inputs(T, d, n, torch.bfloat16, 2)
+    rng = np.random.default_rng(T)
+    rows = np.sort(rng.choice(d, 6, replace=False))
+    cols = np.sort(rng.choice(d, 8, replace=False))
+    xrows = np.sort(rng.choice(T, 5, replace=False))
+    print(f"[norm_store] dW se per trial T={T} d={d} n={n} K={K}", flush=True)
+    out = lib.rmsnorm_linear(X.cuda(), g.cuda(), W.cuda(), dY.cuda(), policies=("N/N",), K=K, seed=31, want_dw_se=True)
+    torch.cuda.synchronize()
+    ref = norm_store.check(X.float().numpy(), g.numpy(), W.float().numpy(), dY.float().numpy(), eps=1e-5,
+                           fmt=fp8.E4M3, fwd_mode=oq.RNE, policies=("N/N",), K=K, seed=31, dw_rows=rows,
+                           gain_cols=cols, dx_rows=xrows)
+    assert out["dW"]["se"] is not None
+    compare(out, ref, ("N/N",), rows=rows, cols=cols, xrows=xrows, d=d, n=n)
+
+
 def test_forward_only_and_no_tokens(lib):
     """dY NULL: the store and Y only (against the oracle); T = 0 with a non-NULL dY: references
     and estimates are zero, the store reports amax 0 and scale 1."""
