@@ -483,22 +483,26 @@ __global__ __launch_bounds__(256) void val_rows_kernel(const uint8_t* __restrict
 //   q1: (s val(C_u) - gain z) / gain * du          (R: reads deq(C_u) / gain)
 //   q2: (s mean_k val(C_k) - gain z) / gain * du   (N: reads a new rounding; mean over
 //       the K trials = sign (lo + n_up step / K))
-// z = fl32(x r) is recomputed exactly as in the forward. Few columns make few waves: GAIN_RB rows'
-// loads are in flight at once (256 x 64: 16.5 us one row at a time, now 11.8).
-constexpr int GAIN_RB = 8;
-template <typename T>
+// z = fl32(x r) is recomputed exactly as in the forward. Eight rows' loads are in flight at
+// once (256 x 64: 16.5 us one row at a time, 11.8 with eight).
+// RW = 4: a block's four waves share 64 columns' rows (4 of a tile's 16 each, added in wave order), where
+// 256-column blocks are fewer than two per CU (256 x 64: 11.1 us with RW = 1, 5.1).
+template <typename T, int RW>
 __global__ __launch_bounds__(256) void gain_partials_kernel(GainArgs<T> a) {
 #pragma clang fp contract(off)
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  constexpr int GAIN_RB = RW == 4 ? 4 : 8;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t j0 = RW == 4 ? (int64_t)blockIdx.x * 64 + lane : (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t j = j0 < a.d ? j0 : a.d - 1;
   const int64_t rt = blockIdx.y;
-  if (j >= a.d) return;
   const double s = *a.scale;
   const float sf = *a.scale;
   const double rsf = 1.0 / (double)sf;
   const double g = a.gain[j], ig = 1.0 / g;
   double q0 = 0.0, q1 = 0.0, q2 = 0.0;
-  const int64_t tend = (rt + 1) * GAIN_RT < a.T ? (rt + 1) * GAIN_RT : a.T;
-  for (int64_t t0 = rt * GAIN_RT; t0 < tend; t0 += GAIN_RB) {
+  constexpr int RT = GAIN_RT / RW;  // rows of a wave
+  const int64_t tb = rt * GAIN_RT + (RW == 4 ? RT * w : 0), tend = tb + RT < a.T ? tb + RT : a.T;
+  for (int64_t t0 = tb; t0 < tend; t0 += GAIN_RB) {
     float xv[GAIN_RB], rs[GAIN_RB], duv[GAIN_RB], uv[GAIN_RB];
     uint32_t cd[GAIN_RB], cn[GAIN_RB];
 #pragma unroll
@@ -529,6 +533,18 @@ __global__ __launch_bounds__(256) void gain_partials_kernel(GainArgs<T> a) {
       }
     }
   }
+  if constexpr (RW == 4) {
+    __shared__ double red[3][4][64];
+    red[0][w][lane] = q0;
+    red[1][w][lane] = q1;
+    red[2][w][lane] = q2;
+    __syncthreads();
+    if (w != 0) return;
+    q0 = ((red[0][0][lane] + red[0][1][lane]) + red[0][2][lane]) + red[0][3][lane];
+    q1 = ((red[1][0][lane] + red[1][1][lane]) + red[1][2][lane]) + red[1][3][lane];
+    q2 = ((red[2][0][lane] + red[2][1][lane]) + red[2][2][lane]) + red[2][3][lane];
+  }
+  if (j0 >= a.d) return;
   const int64_t nrt = gridDim.y;
   a.part[(0 * nrt + rt) * a.d + j] = q0;
   a.part[(1 * nrt + rt) * a.d + j] = q1;
@@ -856,7 +872,10 @@ bs_status launch_gain_t(const GainArgs<T>& a, float* ref, float* bias_r, float* 
     return BS_OK;
   }
   dim3 grid((unsigned)((a.d + 255) / 256), (unsigned)nrt);
-  gain_partials_kernel<T><<<grid, 256, 0, st>>>(a);
+  if ((int64_t)grid.x * grid.y < 512)
+    gain_partials_kernel<T, 4><<<dim3((unsigned)((a.d + 63) / 64), grid.y), 256, 0, st>>>(a);
+  else
+    gain_partials_kernel<T, 1><<<grid, 256, 0, st>>>(a);
   gain_final_kernel<<<(unsigned)((a.d + 15) / 16), 256, 0, st>>>(a.part, nrt, a.d, ref, bias_r, bias_n, 0, 0);
   BS_CHECK_LAUNCH();
   return BS_OK;
