@@ -132,14 +132,14 @@ def side_measurements(bsp, synth, torch, dev, reps=5):
                                                                 K=cfg4["K"], seed=cfg4["seed"], ws=lws),
                      ("gemm", "gemm_split_sum", "fresh_count", "amax", "quantize"), 3)
     mnk2 = 2.0 * cfg4["M"] * cfg4["k"] * cfg4["n"]
-    segs = 8  # dX_ref, dW_ref, dX bias (2 residual terms), dW bias shared (2), dW bias per use (2)
+    segs = 11  # dX_ref, dW_ref, dX bias (3 residual terms), dW bias shared (3), dW bias per use (3)
     g_s = (t["gemm"] + t["gemm_split_sum"]) / 1e3
     out["linear_bwd_e5m2_16384x2048x8192"] = {
         "policy_trials_per_s": round(len(cfg4["sharings"]) * cfg4["K"] / wall, 1), "call_ms": round(wall * 1e3, 3),
         "gemm_TFLOPs": round(segs * mnk2 / g_s / 1e12, 1),
         "gemm_mfma_frac": round(segs * mnk2 / g_s / 1e12 / BF16_MFMA_PEAK_TFLOPS, 4),
         "kernel_ms": {k: round(v, 4) for k, v in t.items()},
-        "flops": "8 bf16 / fp16 contractions of 2 M k n each (references and residual terms)"}
+        "flops": "11 bf16 contractions of 2 M k n each (references and residual terms)"}
     del Xd, Wd, dy, lws
     torch.cuda.empty_cache()
 

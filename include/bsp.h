@@ -396,7 +396,7 @@ bs_status bs_te_attn_bwd(const void* Q, const void* Kt, const void* V, const flo
  *   dX_ref [M,k], dW_ref [k,n] fp32; estimates dX [n_pol][M*k], dW [n_pol][k*n]. The means
  *   collapse the K trials by linearity; a non-NULL dX.se or dW.se runs the per-trial path (App.
  *   C.4's sample SD over trials / sqrt(K)): trial k's residual fresh_k - dY moves dX and dW by K
- *   per-trial contractions (2 M k n flop each per gradient, two fp16 terms), and its
+ *   per-trial contractions (2 M k n flop each per gradient, three bf16 terms), and its
  *   workspace is bs_linear_bwd_workspace_size(..., want_se = 1).
  *   probeA [M,k], probeB [k,n] fp32 and coupling [n_pol] fp64: all NULL or all set.
  *   dY_scale [1] fp32 out.

@@ -16,15 +16,13 @@ using namespace bsp;
 
 namespace {
 struct LinWs {
-  u16 *xT, *dyT, *e1r[2], *e1c[2], *e2c[2], *x16T, *w16, *wT[3], *pa[3], *pbT[3], *tc[2];
+  u16 *xT, *dyT, *e1r[3], *e1c[3], *e2c[3], *wT[3], *pa[3], *pbT[3], *tc[3];
   float *tdx, *tdw, *d1x, *d1w[2];
   double *S1x, *S2x, *S1w[2], *S2w[2];
   u16 *cnt1, *cnt2;
   float *AW, *XB, *bx[2], *bw[2];
   double *part1, *part2, *fixpart, *fixed;
-  uint32_t* am[2];  // maxima of X and W (slot arrays)
-  float* inv;       // multipliers 2^-e: X, W, the residuals
-  float* gpart;     // split-K partials of the contractions
+  float* gpart;  // split-K partials of the contractions
   int64_t gpart_cap;
 };
 LinWs carve_lin(Carver& c, int64_t M, int64_t k, int64_t n, bool any_shared, bool any_per_use, bool coupling,
@@ -33,16 +31,11 @@ LinWs carve_lin(Carver& c, int64_t M, int64_t k, int64_t n, bool any_shared, boo
   const int64_t Mp = round_up(M > 0 ? M : 1, 64);
   w.xT = c.take<u16>(k * Mp);
   w.dyT = c.take<u16>(n * Mp);
-  w.x16T = c.take<u16>(k * Mp);
-  w.w16 = c.take<u16>(k * n);
-  uint32_t* a = c.take<uint32_t>(2 * AMAX_SLOTS * AMAX_STRIDE);
-  for (int i = 0; i < 2; ++i) w.am[i] = a ? a + i * AMAX_SLOTS * AMAX_STRIDE : nullptr;
-  w.inv = c.take<float>(3);
-  for (int i = 0; i < 2; ++i) w.e1r[i] = c.take<u16>(M * n);
+  for (int i = 0; i < 3; ++i) w.e1r[i] = c.take<u16>(M * n);
   if (any_shared)
-    for (int i = 0; i < 2; ++i) w.e1c[i] = c.take<u16>(n * Mp);
+    for (int i = 0; i < 3; ++i) w.e1c[i] = c.take<u16>(n * Mp);
   if (any_per_use)
-    for (int i = 0; i < 2; ++i) w.e2c[i] = c.take<u16>(n * Mp);
+    for (int i = 0; i < 3; ++i) w.e2c[i] = c.take<u16>(n * Mp);
   if (coupling) {
     w.cnt1 = c.take<u16>(M * n);
     if (any_per_use) w.cnt2 = c.take<u16>(M * n);
@@ -59,7 +52,7 @@ LinWs carve_lin(Carver& c, int64_t M, int64_t k, int64_t n, bool any_shared, boo
     w.XB = c.take<float>(M * n);
   }
   if (want_se) {  // the per-trial path: one trial's residual planes, moves and shifted sums
-    for (int i = 0; i < 2; ++i) w.tc[i] = c.take<u16>(n * Mp);
+    for (int i = 0; i < 3; ++i) w.tc[i] = c.take<u16>(n * Mp);
     w.tdx = c.take<float>(M * k);
     w.tdw = c.take<float>(k * n);
     w.d1x = c.take<float>(M * k);
@@ -137,7 +130,7 @@ bs_status bs_linear_bwd_policy(const void* X, const void* W, const void* dY, bs_
   BS_TRY(launch_store(dY, BS_BF16, M * n, fmt, BS_RNE, seed, 0, base, nullptr, nullptr, dY_scale, diag, st, false));
 
   auto gemm = [&](int Mg, int Ng, int Kg, int64_t lda, int64_t ldb, u16* const* A, int nA, u16* const* B, int nB,
-                  float* C, float alpha, const float* inv_a = nullptr, const float* inv_b = nullptr) -> bs_status {
+                  float* C, float alpha) -> bs_status {
     GemmArgs g{};
     g.M = Mg;
     g.N = Ng;
@@ -149,9 +142,6 @@ bs_status bs_linear_bwd_policy(const void* X, const void* W, const void* dY, bs_
     g.C = C;
     g.part = w.gpart;
     g.part_cap = w.gpart_cap;
-    g.f16 = inv_a != nullptr;  // scaled fp16 operands and their multipliers, else bf16
-    g.alpha_dev = inv_a;
-    g.alpha_dev2 = inv_b;
     if (!gemm_add_products(g, A, nA, B, nB)) return BS_EINVAL;
     return launch_gemm(g, st);
   };
@@ -174,14 +164,6 @@ bs_status bs_linear_bwd_policy(const void* X, const void* W, const void* dY, bs_
     BS_TRY(launch_kappa_fixed((const u16*)dY, dY_scale, fmt, M, n, w.AW, w.XB, w.fixpart, w.fixed, st));
   }
 
-  // the residuals' fp16 partners: X^T and W scaled (by their finite maxima; exact for all but the
-  // smallest values, see launch_scale_f16)
-  BS_TRY(launch_fill2d((float*)w.am[0], 2 * AMAX_SLOTS, 1, AMAX_STRIDE, 0.0f, st));
-  BS_TRY(launch_amax_bf16(Xp, M * k, w.am[0], st, true));
-  BS_TRY(launch_amax_bf16(Wp, k * n, w.am[1], st, true));
-  BS_TRY(launch_scale_f16(w.xT, k * Mp, w.am[0], w.x16T, w.inv + 0, st));
-  BS_TRY(launch_scale_f16(Wp, k * n, w.am[1], w.w16, w.inv + 1, st));
-
   // new roundings of dY: use +1 (dX, and dW when shared), use +2 (dW per use); the coupling
   // statistic draws them with its weights and leaves their counts
   if (coupling_on) {
@@ -195,15 +177,18 @@ bs_status bs_linear_bwd_policy(const void* X, const void* W, const void* dY, bs_
 
   // residual planes E_u = mean of use u's roundings - dY, and the bias contractions
   auto resid = [&](int u, int Kt, int trial0, const u16* counts, u16* const* rows, u16* const* cols) {
-    ResidArgs ra{(const u16*)dY, dY_scale, Kt, f, M, n, {rows ? rows[0] : nullptr, rows ? rows[1] : nullptr},
-                 {cols ? cols[0] : nullptr, cols ? cols[1] : nullptr}, Mp, w.inv + 2, counts, seed, base + 1 + u, trial0};
+    ResidArgs ra{(const u16*)dY, dY_scale, Kt, f, M, n, {}, {}, Mp, counts, seed, base + 1 + u, trial0};
+    for (int i = 0; i < 3; ++i) {
+      ra.rows[i] = rows ? rows[i] : nullptr;
+      ra.cols[i] = cols ? cols[i] : nullptr;
+    }
     return launch_resid_planes(ra, st);
   };
   auto move_dx = [&](u16* const* rows, float* out) {
-    return gemm((int)M, (int)k, (int)n, n, n, rows, 2, &w.w16, 1, out, 1.0f, w.inv + 2, w.inv + 1);
+    return gemm((int)M, (int)k, (int)n, n, n, rows, 3, &Wp, 1, out, 1.0f);
   };
   auto move_dw = [&](u16* const* cols, float* out) {
-    return gemm((int)k, (int)n, (int)Mp, Mp, Mp, &w.x16T, 1, cols, 2, out, 1.0f, w.inv + 2, w.inv + 0);
+    return gemm((int)k, (int)n, (int)Mp, Mp, Mp, &w.xT, 1, cols, 3, out, 1.0f);
   };
   BS_TRY(resid(0, K, 1, w.cnt1, w.e1r, any_shared ? w.e1c : nullptr));
   BS_TRY(move_dx(w.e1r, w.bx[0]));

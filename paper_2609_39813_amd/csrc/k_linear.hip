@@ -19,9 +19,9 @@ __device__ __forceinline__ float resid_value(float g, uint32_t n_up, int K, F8 f
 // The residual planes of one use, the K new roundings drawn in the same pass (DRAW; else their
 // counts are read): a block covers 64 rows x 64 columns, a thread 4 consecutive rows x 4 columns
 // (one Philox call per row and trial). Bound by the draws; the planes' writes run under other
-// blocks' draws. 16384 x 8192, 64 trials, both layouts: 3.0 ms per use; counted by one
-// kernel and formed by another as three bf16 terms, 2.80 + 0.51 ms. HI: the tensor has 2^32 or more groups of
-// four elements (else the high counter word is a constant zero).
+// blocks' draws. 16384 x 8192, 64 trials: 3.1 ms per use (one layout or both); counted by one kernel and
+// formed by another, 2.80 + 0.51 ms. HI: the tensor has 2^32 or more groups of four elements (else the
+// high counter word is a constant zero).
 // The transposed planes pass through an LDS tile per term, a thread's four rows of a column as one
 // 8-byte store; tile rows are 34 words apart, the words of row r rotated by 2 ((r >> 4) & 3), so
 // that store and read passes are free of bank conflicts.
@@ -30,15 +30,12 @@ __device__ __forceinline__ int rp_word(int r, int w) { return r * 34 + ((w + 2 *
 // Four waves per SIMD (128 registers) for the Philox latency.
 template <bool DRAW, bool HI>
 __global__ __launch_bounds__(256, 4) void resid_planes_kernel(ResidArgs a) {
-  __shared__ __attribute__((aligned(16))) uint32_t tile[2][64 * 34];
+  __shared__ __attribute__((aligned(16))) uint32_t tile[3][64 * 34];
   const int cg = threadIdx.x & 15, rg = threadIdx.x >> 4;
   const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
   const int64_t tb = r0 + 4 * rg, cb = c0 + 4 * cg;  // first row, first column (n % 4 == 0)
   const float s = *a.scale;
   const double rs = 1.0 / (double)s;
-  const int e = f16_scale_exp(s * (a.f.mbits == 2 ? 0x1p13f : 0x1p5f));
-  const float scl = ldexpf(1.0f, e);
-  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *a.inv_out = ldexpf(1.0f, -e);
   const bool v8 = ((uintptr_t)a.dY & 7) == 0;
   uint2 g2[4];  // four bf16 per row
   uint32_t cnt[4][4];
@@ -89,28 +86,28 @@ __global__ __launch_bounds__(256, 4) void resid_planes_kernel(ResidArgs a) {
       }
     }
   }
-  u16 hi[4][4], lo[4][4];  // [row][column]
+  u16 o[3][4][4];  // [term][row][column]
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      split2_f16(resid_value(elem(i, q), cnt[i][q], a.K, a.f, s, rs) * scl, hi[i][q], lo[i][q]);
+      split3(resid_value(elem(i, q), cnt[i][q], a.K, a.f, s, rs), o[0][i][q], o[1][i][q], o[2][i][q]);
     if (a.rows[0] && tb + i < a.M && cb < a.n) {
-      const int64_t o = (tb + i) * a.n + cb;
-      *(uint2*)(a.rows[0] + o) = make_uint2((uint32_t)hi[i][0] | ((uint32_t)hi[i][1] << 16),
-                                            (uint32_t)hi[i][2] | ((uint32_t)hi[i][3] << 16));
-      *(uint2*)(a.rows[1] + o) = make_uint2((uint32_t)lo[i][0] | ((uint32_t)lo[i][1] << 16),
-                                            (uint32_t)lo[i][2] | ((uint32_t)lo[i][3] << 16));
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        *(uint2*)(a.rows[p] + (tb + i) * a.n + cb) =
+            make_uint2((uint32_t)o[p][i][0] | ((uint32_t)o[p][i][1] << 16),
+                       (uint32_t)o[p][i][2] | ((uint32_t)o[p][i][3] << 16));
     }
   }
   if (!a.cols[0]) return;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int wd = rp_word(4 * cg + q, 2 * rg);
-    *(uint2*)&tile[0][wd] = make_uint2((uint32_t)hi[0][q] | ((uint32_t)hi[1][q] << 16),
-                                       (uint32_t)hi[2][q] | ((uint32_t)hi[3][q] << 16));
-    *(uint2*)&tile[1][wd] = make_uint2((uint32_t)lo[0][q] | ((uint32_t)lo[1][q] << 16),
-                                       (uint32_t)lo[2][q] | ((uint32_t)lo[3][q] << 16));
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+      *(uint2*)&tile[p][wd] = make_uint2((uint32_t)o[p][0][q] | ((uint32_t)o[p][1][q] << 16),
+                                         (uint32_t)o[p][2][q] | ((uint32_t)o[p][3][q] << 16));
   }
   __syncthreads();
 #pragma unroll
@@ -119,7 +116,7 @@ __global__ __launch_bounds__(256, 4) void resid_planes_kernel(ResidArgs a) {
     if (c0 + cc >= a.n) continue;
     const int w0 = rp_word(cc, 4 * k8), w1 = rp_word(cc, 4 * k8 + 2);
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
+    for (int p = 0; p < 3; ++p) {
       const uint2 x0 = *(const uint2*)&tile[p][w0], x1 = *(const uint2*)&tile[p][w1];
       *(uint4*)(a.cols[p] + (c0 + cc) * a.ldo + r0 + 8 * k8) = make_uint4(x0.x, x0.y, x1.x, x1.y);
     }
@@ -129,7 +126,7 @@ __global__ __launch_bounds__(256, 4) void resid_planes_kernel(ResidArgs a) {
 bs_status launch_resid_planes(const ResidArgs& a, hipStream_t st) {
   if (a.n <= 0) return BS_OK;
   if ((a.n & 3) || (a.ldo & 63) || a.ldo < a.M) return BS_EINVAL;
-  for (int p = 0; p < 2; ++p)
+  for (int p = 0; p < 3; ++p)
     if (((uintptr_t)a.rows[p] & 7) || ((uintptr_t)a.cols[p] & 15)) return BS_EINVAL;
   const int64_t rows = a.cols[0] ? a.ldo : a.M;
   if (rows <= 0) return BS_OK;

@@ -59,7 +59,7 @@ def test_ragged_shared_and_per_use_with_coupling(lib, M, k, n):
 
 @pytest.mark.parametrize("M,k,n,K,fmt,shift", [
     (129, 40, 72, 5, "e5m2", 0),    # one row past two 64-row tiles, a ragged column tile, uneven trial blocks
-    (64, 8, 200, 7, "e4m3", 0),     # E4M3's bound of the residual split
+    (64, 8, 200, 7, "e4m3", 0),     # one full row tile, four column tiles, E4M3's steps
     (70, 24, 136, 4, "e5m2", 1),    # dY 2-byte aligned only
 ])
 def test_residuals_drawn_with_their_planes(lib, M, k, n, K, fmt, shift):
@@ -74,12 +74,41 @@ def test_residuals_drawn_with_their_planes(lib, M, k, n, K, fmt, shift):
     compare(out, ref, ("shared", "per_use"), M, k, n, coupling=False)
 
 
+@pytest.mark.parametrize("along", ["rows", "columns"])
+@pytest.mark.parametrize("coupling", [False, True])
+def test_small_rows_and_columns_keep_their_accuracy(lib, along, coupling):
+    """Rows (columns) of dY spanning 2^-24 of the largest, columns of X and rows of W spanning 2^-40: the
+    scales that an output entry factors into are divided out, and every row and every column of dX (dW) is
+    held to the tolerance by itself. Residuals as three bf16 terms against X and W as given are exact in the
+    products at every magnitude; a split at one scale for a tensor is not."""
+    M, k, n, K = 96, 40, 72, 12
+    X, W, dY, A, B = synth.linear_bwd_inputs(M, k, n, torch.bfloat16, 46)
+    x = 2.0 ** -torch.linspace(0, 40, k).round()      # powers of two: exact in bf16
+    r = 2.0 ** -torch.linspace(0, 24, M).round() if along == "rows" else torch.ones(M)
+    c = 2.0 ** -torch.linspace(0, 24, n).round() if along == "columns" else torch.ones(n)
+    X, W, dY = [t.to(torch.bfloat16) for t in (X.float() * x, W.float() * x[:, None], dY.float() * r[:, None] * c)]
+    print(f"[linear_bwd] small {along} coupling={coupling}", flush=True)
+    out = lib.linear_bwd_policy(X.cuda(), W.cuda(), dY.cuda(), K=K, seed=11, store_id=2, want_se=True,
+                                probeA=A.cuda() if coupling else None, probeB=B.cuda() if coupling else None)
+    torch.cuda.synchronize()
+    ref = linear_bwd.check(X.float().numpy(), W.float().numpy(), dY.float().numpy(), fmt=fp8.E5M2, K=K, seed=11,
+                           store_id=2)
+    scale = {"dX": (r[:, None] * x).double().numpy(), "dW": (x[:, None] * c).double().numpy()}
+    for i, sh in enumerate(("shared", "per_use")):
+        for name, sc in scale.items():
+            for j, what in ((1, "bias"), (2, "se")):
+                a, b = to_np(out[name][what][i]).reshape(sc.shape) / sc, ref[sh][name][j] / sc
+                for ax in (0, 1):
+                    e = np.linalg.norm(a - b, axis=ax) / np.linalg.norm(b, axis=ax)
+                    assert e.max() <= TOL, (sh, name, what, ax, int(e.argmax()), float(e.max()))
+
+
 def test_an_infinity_in_x_stays_in_its_row(lib):
-    """The scaled fp16 copy of X takes its scale from the finite values: an infinite X[t, i] makes row i of
-    dW infinite or NaN and leaves the other rows (and dX) within tolerance."""
+    """An infinite X[t, i] makes row i of dW infinite or NaN and leaves the other rows (and dX) within
+    tolerance."""
     M, k, n, K = 96, 16, 64, 6
     X, W, dY, _, _ = synth.linear_bwd_inputs(M, k, n, torch.bfloat16, 45)
-    X = X * 1000.0                  # beyond fp16's range unscaled
+    X = X * 1000.0
     Xi = X.clone()
     Xi[5, 3] = float("inf")
     out = lib.linear_bwd_policy(Xi.cuda(), W.cuda(), dY.cuda(), K=K, seed=3, store_id=2)
