@@ -248,9 +248,9 @@ def side_measurements(bsp, synth, torch, dev, reps=5):
         "call_ms": round(wall * 1e3, 3), "policy_trials_per_s": round(8 * 256 / wall, 1),
         "kernel_ms": {k: round(v, 4) for k, v in t.items()},
         "fresh_Gelement_trials_per_s": round(et / (t["grid_fresh"] / 1e3) / 1e9, 1),
-        "gemm_TFLOPs": round(9 * 2.0 * 8192 * 1024 * 4096 / ((t["gemm"] + t["gemm_split_sum"]) / 1e3) / 1e12, 1),
-        "work": "8 policies, K = 256 new roundings (one Philox word per element-trial); 9 fp16 contractions of "
-                "2 T d n (Y, du, dW_ref and the U and R+e biases, with two-term operands; N's is their sum)"}
+        "gemm_TFLOPs": round(13 * 2.0 * 8192 * 1024 * 4096 / ((t["gemm"] + t["gemm_split_sum"]) / 1e3) / 1e12, 1),
+        "work": "8 policies, K = 256 new roundings (one Philox word per element-trial); 13 bf16 contractions of "
+                "2 T d n (Y, du, dW_ref and the U and R+e biases, with three-term operands; N's is their sum)"}
     del Xg, gg, Wg, dYg, ws
     torch.cuda.empty_cache()
 

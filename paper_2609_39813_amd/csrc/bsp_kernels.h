@@ -49,13 +49,15 @@ inline double gemm_exec_flops(const GemmArgs& g) { return 2.0 * g.M * g.N * (dou
 // Append the products A_i B_j (i + j <= maxsum) of nA and nB bf16 terms to g's segments: with
 // three-term splits the products of order 2^-24 and above (maxsum 2); with two-term fp16 splits
 // (one exact term against two, or two against two with maxsum 1) those of order 2^-22 and above.
+// small_first: the smallest products first, so that they round in a small accumulator (grid store, 8192 x
+// 1024 x 4096, error against fp64: Y 1.7e-7, 4.4e-7 with the largest first; dW 4.4e-7, 5.3e-7).
 inline bool gemm_add_products(GemmArgs& g, const u16* const* A, int nA, const u16* const* B, int nB,
-                              int maxsum = 2) {
+                              int maxsum = 2, bool small_first = false) {
   if (g.nprod == 0 && g.nseg > 0) g.nprod = g.nseg;  // segments set before: one product each
   ++g.nprod;
-  for (int s = 0; s <= maxsum; ++s)
+  for (int t = 0; t <= maxsum; ++t)
     for (int i = 0; i < nA; ++i) {
-      const int j = s - i;
+      const int s = small_first ? maxsum - t : t, j = s - i;
       if (j < 0 || j >= nB) continue;
       if (g.nseg >= GEMM_MAX_SEG) return false;
       g.A[g.nseg] = A[i];
@@ -122,8 +124,7 @@ bs_status launch_fill_f64(double* p, int64_t n, double v, hipStream_t st);
 // the slot array out (AMAX_SLOTS words AMAX_STRIDE apart, float bits, zeroed by the caller) raised
 // to max |x[i]| over n values
 bs_status launch_amax_f32(const float* x, int64_t n, uint32_t* out, hipStream_t st);
-// finite: over the finite values only
-bs_status launch_amax_bf16(const u16* x, int64_t n, uint32_t* out, hipStream_t st, bool finite = false);
+bs_status launch_amax_bf16(const u16* x, int64_t n, uint32_t* out, hipStream_t st);
 bs_status launch_init_diag(bs_diag* diag, hipStream_t st);
 
 // bf16 operand planes. Row-major: out_p[r*ldo + c], c < C (ldo >= C). Transposed:
@@ -169,9 +170,6 @@ bs_status launch_scale_f16(const u16* in, int64_t n, const uint32_t* slots, u16*
 // [C][ldo], row-major into rows [R][C]
 bs_status launch_planes_both(const float* in, int64_t R, int64_t C, u16* const* outT, int64_t ldo, u16* const* rows,
                              int nterms, hipStream_t st);
-// its transpose: out[c*ldo + r] for r < ldo (zero for r >= R) of a bf16 [R][C]
-bs_status launch_transpose_f16(const u16* in, int64_t R, int64_t C, int64_t ldi, const uint32_t* slots, u16* out,
-                               int64_t ldo, float* inv_out, hipStream_t st);
 
 // Trial statistics over per-trial rows (App. C.4, App. D.4).
 bs_status launch_policy_bias(const float* delta, int K, int64_t m, const float* g_ref, float* mean_err, float* se,

@@ -143,17 +143,6 @@ __global__ __launch_bounds__(fresh_nt(TS)) void grid_fresh_kernel(const float* _
   }
 }
 
-// The bounds of the scaled fp16 splits as slot arrays: |u_q| <= max |u| (slots 0) and |e| <= the
-// largest step, max |u| / M (slots 1), each up to rounding.
-__global__ __launch_bounds__(64) void grid_bounds_kernel(const bs_diag* __restrict__ diag, int bits,
-                                                         uint32_t* __restrict__ su, uint32_t* __restrict__ se) {
-  const int i = threadIdx.x;
-  if (i >= AMAX_SLOTS) return;
-  const float a = diag->amax, m = (float)((1 << (bits - 1)) - 1);
-  su[i * AMAX_STRIDE] = i == 0 ? __float_as_uint(a) : 0u;
-  se[i * AMAX_STRIDE] = i == 0 ? __float_as_uint(a / m) : 0u;
-}
-
 // gain use, fp64 column partials over token chunks of 256: [3][nchunk][d]
 //   ref  sum z du;  R  sum (u/gain - z - eU/gain) du;  N  sum (u/gain - z + eE/gain) du
 // rows per chunk of the gain use's column partial sums: T / 32 chunks (grid x) x d / 256 blocks
@@ -227,10 +216,6 @@ __global__ __launch_bounds__(256) void grid_gain_kernel(const XT* __restrict__ X
 struct GridWs {
   float *u, *rstd, *du, *uq, *eU, *eE, *bias_rg, *bias_ng, *bias_w[2];  // weight biases: U, R+e
   u16 *dyT[3], *aT[3], *uq_rows[3], *wT[3], *dy_rows[3], *w_rows[3];
-  // fp16 operands (bf16 inputs): the maxima of dY, W, u_q and the residuals (slot arrays) and their
-  // multipliers 2^-e (u_q, U, R+e; W; dY)
-  uint32_t* am[4];
-  float* inv;
   double* gpart;
   float* gemm_part;
   int64_t gemm_part_cap;
@@ -255,9 +240,6 @@ GridWs carve_grid(Carver& c, int64_t T, int64_t d, int64_t n, bs_dtype wt, bs_dt
   w.bias_rg = c.take<float>(d);
   w.bias_ng = c.take<float>(d);
   for (int i = 0; i < 2; ++i) w.bias_w[i] = c.take<float>(d * n);
-  uint32_t* a = c.take<uint32_t>(4 * AMAX_SLOTS * AMAX_STRIDE);
-  for (int i = 0; i < 4; ++i) w.am[i] = a ? a + i * AMAX_SLOTS * AMAX_STRIDE : nullptr;
-  w.inv = c.take<float>(5);
   w.gpart = c.take<double>(3 * ((T + GRID_GAIN_RT - 1) / GRID_GAIN_RT + 1) * d);
   w.gemm_part_cap = 4 * d * std::max<int64_t>(std::max<int64_t>(T, n), 64);
   w.gemm_part = c.take<float>(w.gemm_part_cap);
@@ -326,32 +308,12 @@ bs_status grid_run(const GridIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
                                                                w.uq, w.eU, io.diag);
     BS_CHECK_LAUNCH();
   }
-  // bf16 inputs: u_q and the residuals enter the contractions as scaled two-term fp16 splits against
-  // scaled fp16 W and dY (9 term products in all; three bf16 terms each made it 16), their planes
-  // of one read each; fp32 inputs as three bf16 terms
-  const bool h16 = io.dt == BS_BF16;
-  if (h16) {
-    BS_TRY(launch_fill2d((float*)w.am[0], 2 * AMAX_SLOTS, 1, AMAX_STRIDE, 0.0f, st));
-    BS_TRY(launch_amax_bf16((const u16*)io.dY, T * n, w.am[0], st, true));
-    if (io.Y) BS_TRY(launch_amax_bf16((const u16*)io.W, d * n, w.am[1], st, true));
-    grid_bounds_kernel<<<1, 64, 0, st>>>(io.diag, io.bits, w.am[2], w.am[3]);
-    BS_CHECK_LAUNCH();
-  }
-  auto split16 = [&](const float* src, const uint32_t* am, float* inv, u16* const* rows) {
-    MoveSrc ms{};
-    ms.rows = src;
-    ms.ldi = d;
-    return launch_split_move(ms, nullptr, 0, T, d, F16Scale{am, nullptr, inv}, w.aT, nullptr, Tp, rows, d, st);
-  };
-  if (h16) BS_TRY(split16(w.uq, w.am[2], w.inv + 0, io.Y ? w.uq_rows : nullptr));
+  // u_q and the residuals enter the contractions as three bf16 terms: the fp32 values at every
+  // magnitude, against W and dY as given (bf16) or as three terms (fp32)
   // Y = u_q W
   if (io.Y) {
-    if (h16) {
-      BS_TRY(launch_transpose_f16((const u16*)io.W, d, n, n, w.am[1], w.wT[0], d, w.inv + 3, st));
-    } else {
-      BS_TRY(launch_planes(w.uq, BS_F32, T, d, d, false, w.uq_rows, 3, d, 1.0f, st));
-      BS_TRY(launch_planes(io.W, wt, d, n, n, true, w.wT, ntw, d, 1.0f, st));
-    }
+    BS_TRY(launch_planes(w.uq, BS_F32, T, d, d, false, w.uq_rows, 3, d, 1.0f, st));
+    BS_TRY(launch_planes(io.W, wt, d, n, n, true, w.wT, ntw, d, 1.0f, st));
     GemmArgs g{};
     g.M = (int)T;
     g.N = (int)n;
@@ -361,12 +323,7 @@ bs_status grid_run(const GridIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
     g.ldc = n;
     g.alpha = 1.0f;
     g.C = io.Y;
-    if (h16) {
-      g.f16 = 1;
-      g.alpha_dev = w.inv + 0;
-      g.alpha_dev2 = w.inv + 3;
-    }
-    gemm_add_products(g, w.uq_rows, h16 ? 2 : 3, w.wT, ntw);
+    gemm_add_products(g, w.uq_rows, 3, w.wT, ntw, 2, true);
     BS_TRY(launch_gemm(g, st));
   }
   // du = dY W^T
@@ -408,17 +365,11 @@ bs_status grid_run(const GridIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
   }
   // weight use: reference and the U and R+e biases, contractions of [d][Tp] planes with dY^T (the N
   // bias is their sum)
-  if (h16)
-    BS_TRY(launch_transpose_f16((const u16*)io.dY, T, n, n, w.am[0], w.dyT[0], Tp, w.inv + 4, st));
-  else
-    BS_TRY(launch_planes(io.dY, gt, T, n, n, true, w.dyT, nt, Tp, 1.0f, st));
+  BS_TRY(launch_planes(io.dY, gt, T, n, n, true, w.dyT, nt, Tp, 1.0f, st));
   const float* srcs[3] = {w.uq, w.eU, w.eE};
   float* dsts[3] = {io.dW_ref, w.bias_w[0], w.bias_w[1]};
   for (int i = 0; i < 3; ++i) {
-    if (!h16)
-      BS_TRY(launch_planes(srcs[i], BS_F32, T, d, d, true, w.aT, 3, Tp, 1.0f, st));
-    else if (i > 0)
-      BS_TRY(split16(srcs[i], w.am[3], w.inv + i, nullptr));
+    BS_TRY(launch_planes(srcs[i], BS_F32, T, d, d, true, w.aT, 3, Tp, 1.0f, st));
     GemmArgs g{};
     g.M = (int)d;
     g.N = (int)n;
@@ -430,12 +381,7 @@ bs_status grid_run(const GridIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
     g.C = dsts[i];
     g.part = w.gemm_part;
     g.part_cap = w.gemm_part_cap;
-    if (h16) {
-      g.f16 = 1;
-      g.alpha_dev = w.inv + i;
-      g.alpha_dev2 = w.inv + 4;
-    }
-    if (!gemm_add_products(g, w.aT, h16 ? 2 : 3, w.dyT, nt)) return BS_EINVAL;
+    if (!gemm_add_products(g, w.aT, 3, w.dyT, nt, 2, true)) return BS_EINVAL;
     BS_TRY(launch_gemm(g, st));
   }
   // gain use: fp64 column sums

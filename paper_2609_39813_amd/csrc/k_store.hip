@@ -21,33 +21,27 @@ __global__ void init_diag_kernel(bs_diag* diag) {
 // patterns is the float order, and NaN/Inf patterns (>= 0x7F800000) sort above every
 // finite value, so one atomicMax also detects non-finite input. Each thread streams
 // 16-byte vectors (8 bf16 or 4 fp32) in a grid-stride loop; the scalar tail is done once.
-// FIN (bf16): NaN and infinities count as zero.
-template <typename T, bool FIN>
+template <typename T>
 __device__ __forceinline__ uint32_t vec_absmax(uint4 v);
 template <>
-__device__ __forceinline__ uint32_t vec_absmax<float, false>(uint4 v) {
+__device__ __forceinline__ uint32_t vec_absmax<float>(uint4 v) {
   const uint32_t a = v.x & 0x7FFFFFFFu, b = v.y & 0x7FFFFFFFu, c = v.z & 0x7FFFFFFFu, d = v.w & 0x7FFFFFFFu;
   return max(max(a, b), max(c, d));
 }
-template <bool FIN>
-__device__ __forceinline__ uint32_t bf16x8_absmax(uint4 v) {
+template <>
+__device__ __forceinline__ uint32_t vec_absmax<u16>(uint4 v) {
   // bf16 -> fp32 bit patterns are the bf16 bits shifted by 16, order preserved
   const uint32_t w[4] = {v.x, v.y, v.z, v.w};
   uint32_t m = 0;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    uint32_t lo = (w[i] << 16) & 0x7FFFFFFFu, hi = w[i] & 0x7FFF0000u;
-    if (FIN) lo = lo < 0x7F800000u ? lo : 0u, hi = hi < 0x7F800000u ? hi : 0u;
+    const uint32_t lo = (w[i] << 16) & 0x7FFFFFFFu, hi = w[i] & 0x7FFF0000u;
     m = max(m, max(lo, hi));
   }
   return m;
 }
-template <>
-__device__ __forceinline__ uint32_t vec_absmax<u16, false>(uint4 v) { return bf16x8_absmax<false>(v); }
-template <>
-__device__ __forceinline__ uint32_t vec_absmax<u16, true>(uint4 v) { return bf16x8_absmax<true>(v); }
 
-template <typename T, bool FIN = false>
+template <typename T>
 __global__ __launch_bounds__(256) void amax_kernel(const T* __restrict__ x, int64_t n,
                                                    uint32_t* __restrict__ amax_bits, int nslots) {
   constexpr int PER = 16 / sizeof(T);
@@ -71,7 +65,7 @@ __global__ __launch_bounds__(256) void amax_kernel(const T* __restrict__ x, int6
         v[k] = make_uint4(t.x, t.y, t.z, t.w);
       }
 #pragma unroll
-      for (int k = 0; k < U; ++k) m = max(m, vec_absmax<T, FIN>(v[k]));
+      for (int k = 0; k < U; ++k) m = max(m, vec_absmax<T>(v[k]));
     }
     i = per * gridDim.x + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   }
@@ -83,14 +77,11 @@ __global__ __launch_bounds__(256) void amax_kernel(const T* __restrict__ x, int6
       v[k] = make_uint4(t.x, t.y, t.z, t.w);
     }
 #pragma unroll
-    for (int k = 0; k < U; ++k) m = max(m, vec_absmax<T, FIN>(v[k]));
+    for (int k = 0; k < U; ++k) m = max(m, vec_absmax<T>(v[k]));
   }
-  for (; i < nvec; i += stride) m = max(m, vec_absmax<T, FIN>(xv[i]));
+  for (; i < nvec; i += stride) m = max(m, vec_absmax<T>(xv[i]));
   for (int64_t j = nvec * PER + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += stride)
-  {
-    const uint32_t b = __float_as_uint(fabsf(load_f32(x, j)));
-    m = max(m, FIN && b >= 0x7F800000u ? 0u : b);
-  }
+    m = max(m, __float_as_uint(fabsf(load_f32(x, j))));
   m = wave_max_u32(m);
   __shared__ uint32_t red[4];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -544,13 +535,10 @@ bs_status launch_amax_f32(const float* x, int64_t n, uint32_t* out, hipStream_t 
   BS_CHECK_LAUNCH();
   return BS_OK;
 }
-bs_status launch_amax_bf16(const u16* x, int64_t n, uint32_t* out, hipStream_t st, bool finite) {
+bs_status launch_amax_bf16(const u16* x, int64_t n, uint32_t* out, hipStream_t st) {
   if (n < 0 || (n > 0 && (!x || !out))) return BS_EINVAL;
   if (n == 0) return BS_OK;
-  if (finite)
-    amax_kernel<u16, true><<<amax_blocks(n / 8), 256, 0, st>>>(x, n, out, AMAX_SLOTS);
-  else
-    amax_kernel<u16><<<amax_blocks(n / 8), 256, 0, st>>>(x, n, out, AMAX_SLOTS);
+  amax_kernel<u16><<<amax_blocks(n / 8), 256, 0, st>>>(x, n, out, AMAX_SLOTS);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }

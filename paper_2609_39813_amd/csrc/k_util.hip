@@ -96,20 +96,11 @@ __global__ __launch_bounds__(256) void planes_rows4_kernel(const float* __restri
   }
 }
 
-// The scale 2^e of a scaled fp16 copy from the max held in slots; 2^-e to inv_out (nullable).
-__device__ __forceinline__ float f16_scale_of(const uint32_t* slots, float* inv_out) {
-  const int e = f16_scale_exp(amax_of_slots(slots));
-  if (inv_out && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *inv_out = ldexpf(1.0f, -e);
-  return ldexpf(1.0f, e);
-}
-
 // Transposed: out_p[c * ldo + r] for r < ldo (zero for r >= R). Tile 64 x 64 through LDS.
 template <typename T>
 __global__ __launch_bounds__(256) void planes_t_kernel(const T* __restrict__ in, int64_t R, int64_t C, int64_t ldi,
-                                                       PlaneOut out, int nterms, int64_t ldo, float scale,
-                                                       const uint32_t* f16_slots, float* inv_out) {
+                                                       PlaneOut out, int nterms, int64_t ldo, float scale) {
   __shared__ u16 tile[3][64][66];
-  if (f16_slots) scale = f16_scale_of(f16_slots, inv_out);  // one fp16 term
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
 #pragma unroll 4
@@ -119,7 +110,6 @@ __global__ __launch_bounds__(256) void planes_t_kernel(const T* __restrict__ in,
     const float v = (r < R && c < C) ? load_f32(in, r * ldi + c) * scale : 0.0f;
     u16 o[3];
     split_to(v, nterms, o);
-    if (f16_slots) o[0] = f16_bits(v);
     for (int p = 0; p < nterms; ++p) tile[p][rr][tx] = o[p];
   }
   __syncthreads();
@@ -134,29 +124,17 @@ __global__ __launch_bounds__(256) void planes_t_kernel(const T* __restrict__ in,
 
 // The transpose of a bf16 [R, C] matrix (C and ldi multiples of 8, 16-byte aligned rows) into
 // [C][ldo] with zeros in rows R .. ldo - 1 of every output row: one 64 x 64 tile per block,
-// 16-byte loads and stores, the tile held in LDS with rows padded to 144 bytes. F16: the values as
-// scaled fp16 (the scale from slots).
-template <bool F16>
+// 16-byte loads and stores, the tile held in LDS with rows padded to 144 bytes.
 __global__ __launch_bounds__(256) void transpose_bf16_kernel(const u16* __restrict__ in, int64_t R, int64_t C,
-                                                             int64_t ldi, u16* __restrict__ out, int64_t ldo,
-                                                             const uint32_t* slots, float* inv_out) {
+                                                             int64_t ldi, u16* __restrict__ out, int64_t ldo) {
   __shared__ __attribute__((aligned(16))) u16 tile[64][72];
-  const float scl = F16 ? f16_scale_of(slots, inv_out) : 1.0f;
   const int t = threadIdx.x, q = (t & 7) * 8;
   const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass) {
     const int rr = (t >> 3) + 32 * pass;
     const int64_t r = r0 + rr, c = c0 + q;
-    uint4 v = (r < R && c < C) ? *(const uint4*)(in + r * ldi + c) : make_uint4(0, 0, 0, 0);
-    if constexpr (F16) {
-      uint32_t x[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        x[i] = (uint32_t)f16_bits(__uint_as_float(x[i] << 16) * scl) |
-               ((uint32_t)f16_bits(__uint_as_float(x[i] & 0xFFFF0000u) * scl) << 16);
-      v = make_uint4(x[0], x[1], x[2], x[3]);
-    }
+    const uint4 v = (r < R && c < C) ? *(const uint4*)(in + r * ldi + c) : make_uint4(0, 0, 0, 0);
     *(uint4*)&tile[rr][q] = v;
   }
   __syncthreads();
@@ -265,13 +243,13 @@ bs_status launch_planes(const void* in, bs_dtype dt, int64_t R, int64_t C, int64
     bool vecf = dt == BS_F32 && C % 4 == 0 && ldi % 4 == 0 && ldo % 8 == 0 && ((uintptr_t)in & 15) == 0;
     for (int p = 0; p < nterms; ++p) vecf = vecf && ((uintptr_t)outp[p] & 15) == 0;
     if (vec)
-      transpose_bf16_kernel<false><<<grid, 256, 0, st>>>((const u16*)in, R, C, ldi, outp[0], ldo, nullptr, nullptr);
+      transpose_bf16_kernel<<<grid, 256, 0, st>>>((const u16*)in, R, C, ldi, outp[0], ldo);
     else if (vecf)
       transpose_split_f32_kernel<<<grid, 256, 0, st>>>((const float*)in, R, C, ldi, out, nterms, ldo, scale, PlaneOut{});
     else if (dt == BS_F32)
-      planes_t_kernel<float><<<grid, 256, 0, st>>>((const float*)in, R, C, ldi, out, nterms, ldo, scale, nullptr, nullptr);
+      planes_t_kernel<float><<<grid, 256, 0, st>>>((const float*)in, R, C, ldi, out, nterms, ldo, scale);
     else
-      planes_t_kernel<u16><<<grid, 256, 0, st>>>((const u16*)in, R, C, ldi, out, nterms, ldo, scale, nullptr, nullptr);
+      planes_t_kernel<u16><<<grid, 256, 0, st>>>((const u16*)in, R, C, ldi, out, nterms, ldo, scale);
   } else {
     const int64_t n = R * ldo;
     if (n <= 0) return BS_OK;
@@ -313,20 +291,6 @@ bs_status launch_planes_both(const float* in, int64_t R, int64_t C, u16* const* 
   }
   transpose_split_f32_kernel<<<dim3((unsigned)((C + 63) / 64), (unsigned)((ldo + 63) / 64)), 256, 0, st>>>(
       in, R, C, C, t, nterms, ldo, 1.0f, r);
-  BS_CHECK_LAUNCH();
-  return BS_OK;
-}
-
-bs_status launch_transpose_f16(const u16* in, int64_t R, int64_t C, int64_t ldi, const uint32_t* slots, u16* out,
-                               int64_t ldo, float* inv_out, hipStream_t st) {
-  if (!slots || R < 0 || (C > 0 && ldo > 0 && (!in || !out))) return BS_EINVAL;
-  if (C <= 0 || ldo <= 0) return BS_OK;
-  const dim3 grid((unsigned)((C + 63) / 64), (unsigned)((ldo + 63) / 64));
-  if (C % 8 == 0 && ldi % 8 == 0 && ldo % 64 == 0 && ((uintptr_t)in & 15) == 0 && ((uintptr_t)out & 15) == 0)
-    transpose_bf16_kernel<true><<<grid, 256, 0, st>>>(in, R, C, ldi, out, ldo, slots, inv_out);
-  else
-    planes_t_kernel<u16><<<grid, 256, 0, st>>>(in, R, C, ldi, PlaneOut{{out, nullptr, nullptr}}, 1, ldo, 1.0f, slots,
-                                               inv_out);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }

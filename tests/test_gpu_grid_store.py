@@ -74,16 +74,45 @@ def test_grid_widths_and_policy_order(lib, bits):
     (700, 264, 16, 6, 0),    # two groups per thread in 4 trial parts
     (90, 48, 24, 7, 1),      # 2-byte aligned X, W and dY: the element-wise loads and transposes
 ])
-def test_bf16_operands_as_fp16_splits(lib, T, d, n, K, shift):
-    """bf16 inputs enter the contractions as scaled fp16 (u_q and the residuals as two terms) and the N bias
-    is the sum of the U and R+e biases; every split of the trials over a block."""
+def test_bf16_operands_and_trial_parts(lib, T, d, n, K, shift):
+    """bf16 inputs, whose N bias is the sum of the U and R+e biases; every split of the trials over a block."""
     X, g, W, dY = synth.rmsnorm_linear_inputs(T, d, n, torch.bfloat16, 8)
     place = lambda t: torch.cat((torch.zeros(shift, dtype=t.dtype), t.reshape(-1))).cuda()[shift:].view(t.shape)
-    print(f"[grid_store] fp16 T={T} d={d} n={n} K={K} shift={shift}", flush=True)
+    print(f"[grid_store] bf16 T={T} d={d} n={n} K={K} shift={shift}", flush=True)
     out = lib.rmsnorm_linear_grid(place(X), g.cuda(), place(W), place(dY), bits=6, K=K, seed=T, store_id=3)
     torch.cuda.synchronize()
     ref = gs.check(X.float().numpy(), g.numpy(), W.float().numpy(), dY.float().numpy(), bits=6, K=K, seed=T, store_id=3)
     compare(lib, out, ref, gs.POLICIES, d, n)
+
+
+def test_small_tokens_and_columns_keep_their_accuracy(lib):
+    """Tokens spanning 2^-30 (below the normalization's eps), columns of W and dY spanning 2^-44: every row
+    and column of Y and of dW, its means and biases is held to the tolerance by itself, the scales divided
+    out. u_q and the residuals as three bf16 terms against W and dY as given are exact in the products at
+    every magnitude; a split at one scale for a tensor is not."""
+    T, d, n, K = 70, 40, 48, 12
+    X, g, W, dY = synth.rmsnorm_linear_inputs(T, d, n, torch.bfloat16, 9)
+    c = 2.0 ** -torch.linspace(0, 44, n).round()          # powers of two: exact in bf16
+    x = 2.0 ** -torch.linspace(0, 30, T).round()
+    X, W, dY = [t.to(torch.bfloat16) for t in (X.float() * x[:, None], W.float() * c, dY.float() * c)]
+    print("[grid_store] small tokens and columns", flush=True)
+    out = lib.rmsnorm_linear_grid(X.cuda(), g.cuda(), W.cuda(), dY.cuda(), bits=6, K=K, seed=5, store_id=3)
+    torch.cuda.synchronize()
+    ref = gs.check(X.float().numpy(), g.numpy(), W.float().numpy(), dY.float().numpy(), bits=6, K=K, seed=5, store_id=3)
+    cn = c.double().numpy()
+
+    def held(a, b, scale, what):
+        a, b = to_np(a).reshape(b.shape) / scale, b / scale
+        for ax in (0, 1):
+            e = np.linalg.norm(a - b, axis=ax) / np.maximum(np.linalg.norm(b, axis=ax), 1e-300)
+            assert e.max() <= TOL, (what, ax, int(e.argmax()), float(e.max()))
+
+    assert np.array_equal(out["u_codes"].cpu().numpy().astype(np.int32), ref["codes"])
+    held(out["Y"], ref["Y"], ref["step"].astype(np.float64)[:, None] * cn, "Y")
+    held(out["dW_ref"], ref["dW_ref"], cn, "dW_ref")
+    for i, code in enumerate(gs.POLICIES):
+        held(out["dW"]["mean"][i], ref[code]["dW"][0], cn, f"{code} mean")
+        held(out["dW"]["bias"][i], ref[code]["dW"][1], cn, f"{code} bias")
 
 
 @pytest.mark.slow
