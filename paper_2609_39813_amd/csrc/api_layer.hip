@@ -69,9 +69,8 @@ WeightUseWs carve_wu(Carver& c, int64_t T, int64_t k, int64_t n, int K = 1, bool
   w.gpart_cap = 16 * k * n;  // split-K partials: the long-T contraction has few output tiles
   w.gpart = c.take<float>(w.gpart_cap);
   if (se) {
-    const int bt = se_trial_batch(k, n, Tp, K);
-    w.tplanes = c.take<u16>(bt * k * Tp);
-    w.tdelta = c.take<float>(bt * k * n);
+    w.tplanes = c.take<u16>(se_trials_size(k * Tp, K));
+    w.tdelta = c.take<float>(se_trials_size(k * n, K));
     w.td1 = c.take<float>(k * n);
     w.tS1 = c.take<double>(k * n);
     w.tS2 = c.take<double>(k * n);

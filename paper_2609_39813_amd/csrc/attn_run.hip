@@ -26,9 +26,10 @@ struct AttnWs {
 };
 // trials of dK's se side by side in one launch: one alone does not fill the chip at small shapes (16 heads
 // of 250: 22 us for 1, 36 for 8). Past 2^22 elements of dK it does.
+constexpr int64_t DK_TRIALS_CAP = (int64_t)1 << 22;
 int dk_trials_together(int64_t numel, int K) {
   int n = 1;
-  while (n < 16 && n < K && 2 * n * numel <= (int64_t)1 << 22) n *= 2;
+  while (n < 16 && n < K && 2 * n * numel <= DK_TRIALS_CAP) n *= 2;
   return n;
 }
 AttnWs carve_attn(Carver& c, int64_t rows, int64_t numel, bool need_o, bool need_dref, int64_t bh = 0, int64_t Sp = 0,
@@ -36,7 +37,7 @@ AttnWs carve_attn(Carver& c, int64_t rows, int64_t numel, bool need_o, bool need
   AttnWs w{};
   if (K > 0) {
     w.dD_tr = c.take<float>((int64_t)K * rows);
-    w.tdk = c.take<float>(dk_trials_together(numel, K) * numel);
+    w.tdk = c.take<float>(side_by_side_size(numel, 1, dk_trials_together(0, K), DK_TRIALS_CAP));
     for (float** p : {&w.d1, &w.sek}) *p = c.take<float>(numel);
     w.S1 = c.take<double>(numel);
     w.S2 = c.take<double>(numel);

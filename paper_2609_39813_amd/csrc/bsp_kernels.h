@@ -113,6 +113,18 @@ inline int64_t fresh_count_blocks(int64_t T, int64_t d) { return ((d + 255) / 25
 inline int64_t colsum_rows(int64_t T, int64_t d, int K) {
   return K >= 4 && ((d + 63) / 64) * ((T + 31) / 32) < 1024 && (int64_t)K * T * d <= (int64_t)1 << 27 ? 8 : 32;
 }
+// floats that hold them, reserved so that a larger call never needs less (workspace queries grow with every
+// size): the 32-row sums, and what 8-row tiles may add to them (at most 2^24: K T d <= 2^27)
+inline int64_t colsum_size(int64_t T, int64_t d, int K) {
+  const int64_t fine = (int64_t)K * ((T + 7) / 8) * d, coarse = (int64_t)K * ((T + 31) / 32) * d;
+  return fine < coarse + ((int64_t)1 << 24) ? fine : coarse + ((int64_t)1 << 24);
+}
+// elements that hold n equal arrays of x side by side where n is 1 (base) or n x at most cap: they too
+// grow with x, most (the largest n) and cap
+inline int64_t side_by_side_size(int64_t x, int64_t base, int64_t most, int64_t cap) {
+  const int64_t all = most * x < cap ? most * x : cap;
+  return all > base * x ? all : base * x;
+}
 bs_status launch_fresh_count(const float* u, int64_t T, int64_t d, int fmt, const float* scale, uint64_t seed,
                              uint32_t use, int K, u16* counts, const float* w, float* colsum, hipStream_t st);
 

@@ -17,6 +17,8 @@
 // call per group, draw and trial), the trials unrolled inside so that the element's part of the
 // first two rounds is shared and the trial's runs on the scalar unit. A block's four waves share
 // the row. A sum over the wave halves the trials each lane carries at each exchange.
+#include <algorithm>
+
 #include "bsp_kernels.h"
 
 namespace bsp {
@@ -147,6 +149,9 @@ __global__ __launch_bounds__(256) void lsm_trial_kernel(const double* __restrict
 // blocks stay short (the stage is latency: 66 us with 64 trials per block at 512 rows, 64 trials,
 // now 8 us), 64 beyond
 inline int lsm_rt(int K) { return K <= 4096 ? 4 : 64; }
+// blocks of that stage that the workspace has room for: those of the largest smaller K too (a workspace
+// query grows with every size)
+inline int lsm_blocks_max(int K) { return std::max((K + 63) / 64, std::min((K + 3) / 4, 1024)); }
 
 // mean over rows and classes of statistic c in trial k: one wave, rows lane-strided, combined by
 // a fixed xor tree (every lane ends with the total)
@@ -224,7 +229,7 @@ size_t lsm_ws_size(int64_t rows, int C, int K) {
   Carver c;
   for (int i = 0; i < 2; ++i) c.take<double>(rows * C);
   c.take<double>((int64_t)4 * K * rows);
-  c.take<double>((int64_t)8 * ((K + lsm_rt(K) - 1) / lsm_rt(K)));
+  c.take<double>((int64_t)8 * lsm_blocks_max(K));
   c.take<double>(4);
   return c.used();
 }
@@ -251,7 +256,7 @@ bs_status bs_logsoftmax_reuse_check(const double* logits, const int32_t* target,
   double* wm = c.take<double>(rows * C);
   double* part = c.take<double>((int64_t)4 * K * rows);
   const int rt = lsm_rt(K), nb = (K + rt - 1) / rt;
-  double* acc = c.take<double>((int64_t)8 * nb);
+  double* acc = c.take<double>((int64_t)8 * lsm_blocks_max(K));
   double* m0 = c.take<double>(4);
   {
     ProfScope prof("lsm_prep", st);

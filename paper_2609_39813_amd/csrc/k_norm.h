@@ -77,10 +77,15 @@ bs_status launch_dx_t(const DxArgs<T>& a, hipStream_t st);
 // Trials per launch of a weight use's per-trial contractions (planes [d][Tp], moves [d][n] each): 8, and
 // up to 32 while a launch's planes and moves stay within 2^25 elements each. 1111 x 520 x 776, 24
 // trials of two uses: 410 us with 8, 316 with 24 and the planes' trials over more blocks.
+constexpr int64_t SE_TRIALS_CAP = (int64_t)1 << 25;
 inline int se_trial_batch(int64_t d, int64_t n, int64_t Tp, int K) {
   int b = K < 8 ? K : 8;
-  while (b < 32 && b < K && 2 * b * d * (n > Tp ? n : Tp) <= (int64_t)1 << 25) b = 2 * b < K ? 2 * b : K;
+  while (b < 32 && b < K && 2 * b * d * (n > Tp ? n : Tp) <= SE_TRIALS_CAP) b = 2 * b < K ? 2 * b : K;
   return b;
+}
+// elements that hold a launch's planes (x = d Tp) or moves (x = d n)
+inline int64_t se_trials_size(int64_t x, int K) {
+  return side_by_side_size(x, K < 8 ? K : 8, K < 32 ? K : 32, SE_TRIALS_CAP);
 }
 
 // Per-trial weight-use residual planes: for trials k0 .. k0 + nb - 1 (new roundings of u at

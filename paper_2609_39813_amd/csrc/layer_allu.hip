@@ -53,9 +53,10 @@ constexpr int IV_ATT = 8;
 // with its copies in one launch, 1840). Past 2^22 elements of a [T][d] move a trial's launches fill
 // the chip by themselves, and its moves (44 bytes an element) would only leave the caches: 8
 // sequences of 2048 at d = 1024 take one at a time.
+constexpr int64_t TRIALS_CAP = (int64_t)1 << 22;
 int trials_together(int64_t T, int64_t d, int K) {
   int b = 1;
-  while (b < KCH && b < K && 2 * b * T * d <= (int64_t)1 << 22) b *= 2;
+  while (b < KCH && b < K && 2 * b * T * d <= TRIALS_CAP) b *= 2;
   return b;
 }
 
@@ -95,7 +96,11 @@ AlluWs carve_allu(Carver& c, int B, int S, int d, int H, int F, int K) {
   const int64_t kc = std::max(1, std::min(K, KCH));
   const int64_t T = (int64_t)B * S, Td = T * d, Tp = round_up(T > 0 ? T : 1, 64), bh = (int64_t)B * H;
   const int64_t Sp = round_up(S, 64), d3 = 3 * (int64_t)d;
-  const int64_t nt = trials_together(T, d, K);
+  // the arrays of the trials side by side, reserved so that a larger layer never needs less: at most nt
+  // trials, and TRIALS_CAP elements of a move where it is more than one (rounded rows beside them)
+  const int64_t nt = trials_together(0, d, K), moves = side_by_side_size(Td, 1, nt, TRIALS_CAP);
+  const int64_t dot = side_by_side_size(bh * DH * Sp, 1, nt, TRIALS_CAP + nt * 63 * bh * DH);
+  const int64_t rows16 = side_by_side_size((T + 15) / 16 * (int64_t)d, 1, nt, TRIALS_CAP / 16 + nt * d);
   const int64_t nc[NCOMP] = {Td, d, (int64_t)d * d3, (int64_t)d * d};
   w.m = c.take<float>(bh * S);
   w.l = c.take<float>(bh * S);
@@ -105,15 +110,15 @@ AlluWs carve_allu(Carver& c, int B, int S, int d, int H, int F, int K) {
   for (int i = 0; i < 2; ++i) {
     w.pA[i] = c.take<u16>(d * Tp);
     w.tB[i] = c.take<u16>(d3 * Tp);
-    w.rows3[i] = c.take<u16>(nt * T * d3);
-    w.dOp[i] = c.take<u16>(nt * Td);
-    w.dOt[i] = c.take<u16>(nt * bh * DH * Sp);
+    w.rows3[i] = c.take<u16>(3 * moves);
+    w.dOp[i] = c.take<u16>(moves);
+    w.dOt[i] = c.take<u16>(dot);
   }
-  for (float** p : {&w.dh_d, &w.dO_dt, &w.du1_d}) *p = c.take<float>(nt * Td);
-  w.dQ_d = c.take<float>(nt * 3 * Td);  // dQ, dK, dV of the move, one block (one max over the three)
+  for (float** p : {&w.dh_d, &w.dO_dt, &w.du1_d}) *p = c.take<float>(moves);
+  w.dQ_d = c.take<float>(3 * moves);  // dQ, dK, dV of the move, one block (one max over the three)
   w.dK_d = w.dQ_d ? w.dQ_d + Td : nullptr;
   w.dV_d = w.dQ_d ? w.dQ_d + 2 * Td : nullptr;
-  w.dD = c.take<float>(nt * bh * S);
+  w.dD = c.take<float>(moves / DH);
   w.Wo16 = c.take<u16>((int64_t)d * d);
   w.Wqkv16 = c.take<u16>((int64_t)d * d3);
   w.V16 = c.take<u16>(bh * S * DH);
@@ -133,7 +138,7 @@ AlluWs carve_allu(Carver& c, int B, int S, int d, int H, int F, int K) {
   w.tBq = c.take<u16>(kc * 2 * d3 * Tp);
   w.invo = c.take<float>(kc);
   w.invq = c.take<float>(kc);
-  w.gpart = c.take<double>(nt * ((T + 15) / 16) * (int64_t)d);
+  w.gpart = c.take<double>(rows16);
   for (int i = 0; i < NCOMP; ++i) {
     if (i < 2) w.delta[i] = c.take<float>(std::max(1, std::min(K, KCH)) * nc[i]);
     for (int l = 0; l < 3; ++l) w.bias[l][i] = c.take<float>(nc[i]);

@@ -79,14 +79,13 @@ NormWs carve_norm(Carver& c, int64_t T, int64_t d, int64_t n, int K, bs_dtype wt
   if (p.gain_n || p.weight_n[0]) w.counts_g = c.take<u16>(T * d);
   if (p.weight_n[1]) w.counts_w = c.take<u16>(T * d);
   if (p.gain_se) {
-    w.partial = c.take<float>((int64_t)K * ((T + colsum_rows(T, d, K) - 1) / colsum_rows(T, d, K)) * d + 1);
+    w.partial = c.take<float>(colsum_size(T, d, K) + 1);
     w.trial_sums = c.take<double>((int64_t)K * d);
   }
   if (p.want_dxr) w.dx_r = c.take<float>(T * d);
   if (p.weight_se[0] || p.weight_se[1]) {
-    const int bt = se_trial_batch(d, n, Tp, K);
-    w.tplanes = c.take<u16>((int64_t)bt * d * Tp);
-    w.tdelta = c.take<float>((int64_t)bt * d * n);
+    w.tplanes = c.take<u16>(se_trials_size(d * Tp, K));
+    w.tdelta = c.take<float>(se_trials_size(d * n, K));
     w.td1 = c.take<float>(d * n);
     w.tS1 = c.take<double>(d * n);
     w.tS2 = c.take<double>(d * n);
