@@ -31,6 +31,8 @@ def run_all(lib, B, S, d, H, F, K, seed, fmt, mode):
     (1, 72, 64, 1, 136, 4, 32, "e5m2", "sr"),     # F = 136: ragged contraction columns
     (1, 16, 1088, 17, 128, 2, 34, "e4m3", "sr"),  # d > 1024: u1's gain and norm-input uses in two kernels
     (1, 24, 64, 1, 96, 18, 35, "e4m3", "rne"),    # N's trials: a full chunk of 16 side by side, and 2 more
+    (1, 520, 1024, 16, 64, 6, 36, "e4m3", "rne"), # N's trials 4 side by side: launches of 4 and 2 in a chunk
+    (1, 300, 1024, 16, 64, 18, 37, "e4m3", "rne"),# 8 side by side: 8 and 8 in a chunk, 2 in the next
 ])
 def test_every_use_at_once_matches_oracle(lib, B, S, d, H, F, K, seed, fmt, mode):
     out, ref, r = run_all(lib, B, S, d, H, F, K, seed, fmt, mode)
