@@ -89,13 +89,14 @@ __device__ __forceinline__ void sum_trials(V* v, int lane, int L) {
 
 // per (row, trial): the row sums of the four entry errors, [4][K][rows]. SUB: rows of at most 32
 // groups, L lanes (a power of two, at least TK) per trial and 64 / L trials side by side; else
-// L = 64.
-template <int TK, bool SUB>
+// L = 64. MORE: the rows from row0 on (the launches after the first; the loop scheduled around that
+// base takes 927 us for 912 at 512 x 32768).
+template <int TK, bool SUB, bool MORE>
 __global__ __launch_bounds__(256) void lsm_trial_kernel(const double* __restrict__ wp, const double* __restrict__ wm,
                                                         const int32_t* __restrict__ y, int64_t rows, int C, int L,
                                                         double eps, int K, uint64_t seed, uint32_t use_r,
-                                                        uint32_t use_p, double* __restrict__ part) {
-  const int64_t row = blockIdx.x;
+                                                        uint32_t use_p, double* __restrict__ part, int64_t row0) {
+  const int64_t row = MORE ? row0 + blockIdx.x : blockIdx.x;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nsub = SUB ? 64 / L : 1;
   const int k0 = (blockIdx.y * 4 + wave) * TK * nsub;  // trial index (trial k0 + 1) of the wave's first
@@ -224,6 +225,9 @@ __global__ __launch_bounds__(256) void lsm_final_kernel(const double* __restrict
 
 }  // namespace
 
+// rows per launch: a launch holds fewer than 2^32 threads in a grid dimension, and a row takes up to 1024
+constexpr int64_t LSM_ROWS = (int64_t)1 << 21;
+
 size_t lsm_ws_size(int64_t rows, int C, int K) {
   if (rows < 1 || C < 4 || (C & 3) || K < 1) return 0;
   Carver c;
@@ -262,8 +266,11 @@ bs_status bs_logsoftmax_reuse_check(const double* logits, const int32_t* target,
     ProfScope prof("lsm_prep", st);
     // a row's fp64 exponentials bound it: as many waves per row as its length fills
     const int nt = C >= 4096 ? 1024 : (C >= 512 ? 256 : 64);
-    lsm_prep_kernel<<<(unsigned)rows, nt, 0, st>>>(logits, C, eps, calibrate ? cosh(eps) : 1.0, wp, wm);
-    BS_CHECK_LAUNCH();
+    for (int64_t r0 = 0; r0 < rows; r0 += LSM_ROWS) {
+      lsm_prep_kernel<<<(unsigned)std::min(LSM_ROWS, rows - r0), nt, 0, st>>>(
+          logits + r0 * C, C, eps, calibrate ? cosh(eps) : 1.0, wp + r0 * C, wm + r0 * C);
+      BS_CHECK_LAUNCH();
+    }
   }
   const uint32_t base = store_id * 256u;
   {
@@ -275,15 +282,19 @@ bs_status bs_logsoftmax_reuse_check(const double* logits, const int32_t* target,
     const int nsub = 64 / L;
     const bool wide = rows * ((K + 16 * nsub - 1) / (16 * nsub)) >= 2048;
     const int per = 4 * (wide ? 16 : 4) * nsub;
-    const dim3 grid((unsigned)rows, (unsigned)((K + per - 1) / per));
-    auto go = [&](auto kernel) {
-      kernel<<<grid, 256, 0, st>>>(wp, wm, target, rows, C, L, eps, K, seed, base, base + 1, part);
-    };
-    if (L == 64)
-      wide ? go(lsm_trial_kernel<16, false>) : go(lsm_trial_kernel<4, false>);
-    else
-      wide ? go(lsm_trial_kernel<16, true>) : go(lsm_trial_kernel<4, true>);
-    BS_CHECK_LAUNCH();
+    for (int64_t r0 = 0; r0 < rows; r0 += LSM_ROWS) {
+      const dim3 grid((unsigned)std::min(LSM_ROWS, rows - r0), (unsigned)((K + per - 1) / per));
+      auto go = [&](auto kernel) {
+        kernel<<<grid, 256, 0, st>>>(wp, wm, target, rows, C, L, eps, K, seed, base, base + 1, part, r0);
+      };
+      if (r0 > 0)  // then wide
+        L == 64 ? go(lsm_trial_kernel<16, false, true>) : go(lsm_trial_kernel<16, true, true>);
+      else if (L == 64)
+        wide ? go(lsm_trial_kernel<16, false, false>) : go(lsm_trial_kernel<4, false, false>);
+      else
+        wide ? go(lsm_trial_kernel<16, true, false>) : go(lsm_trial_kernel<4, true, false>);
+      BS_CHECK_LAUNCH();
+    }
   }
   {
     ProfScope prof("lsm_reduce", st);

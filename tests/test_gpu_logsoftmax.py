@@ -10,6 +10,7 @@ import pytest
 import torch
 
 from oracle import logsoftmax as ls
+from oracle import philox
 
 pytestmark = pytest.mark.gpu
 
@@ -54,6 +55,25 @@ def test_lane_and_trial_splits_match_oracle(lib, rows, C, K):
     """The edges of the trial kernel's lane groups, its two trial counts and both reductions; the
     tolerance is that of test_statistics_match_oracle (fp64 sums in different orders)."""
     test_statistics_match_oracle(lib, rows, C, K, 0.1, False)
+
+
+@pytest.mark.slow
+def test_rows_past_one_launch(lib):
+    """2^24 + 5 rows of one Philox group: more blocks than a launch's grid dimension holds threads for."""
+    rows, C, eps, seed = (1 << 24) + 5, 4, 0.1, 9
+    z, y, got = run(lib, rows, C, 1, eps, seed)
+    total = dict.fromkeys(ls.STATS, 0.0)
+    for r0 in range(0, rows, 1 << 20):
+        zc, yc = z[r0:r0 + (1 << 20)].numpy(), y[r0:r0 + (1 << 20)].numpy()
+        row = np.arange(r0, r0 + len(yc), dtype=np.uint64)
+        draw = [np.stack(philox.philox4x32_10(row, np.uint64(0), np.uint64(1), np.uint64(256 + use), np.uint64(seed),
+                                              np.uint64(0)), axis=1) for use in (0, 1)]
+        r, rp = [np.where(w >= np.uint64(1 << 31), eps, -eps) for w in draw]
+        for name, e in ls.entry_errors(ls.log_softmax(zc), yc, r, rp).items():
+            total[name] += e.sum()
+    for i, name in enumerate(ls.STATS):
+        m = total[name] / (rows * C)
+        assert abs(got[i, 0] - m) <= 1e-9 * abs(m) and got[i, 1] == 0, (name, got[i], m)
 
 
 def test_targets_outside_the_classes_match_none(lib):
