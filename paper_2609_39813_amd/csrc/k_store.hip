@@ -180,6 +180,7 @@ __global__ __launch_bounds__(256) void quantize_kernel(const T* __restrict__ x, 
   bool bad;
   const double rs = 1.0 / (double)store_scale(diag, scale_in, scale_out, fmax, blockIdx.x == 0 && threadIdx.x == 0, bad);
   if (bad) return;
+  const bool nans = !__builtin_isfinite(rs);  // a caller's scale of 0 or NaN: quotients may be NaN, which a maximum skips
   const int64_t ngroups = (n + 7) / 8, stride = (int64_t)gridDim.x * blockDim.x;
   uint32_t nsat = 0;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < ngroups; t += stride) {
@@ -219,9 +220,9 @@ __global__ __launch_bounds__(256) void quantize_kernel(const T* __restrict__ x, 
       y[q] = div_scale(xv[q], rs);
       big = fmaxf(big, fabsf(y[q]));
     }
-    // clamped to [-FMAX, FMAX] (sign of zero kept) and counted (a ballot and a scalar popcount: the
-    // count is wave-uniform) only where one of the wave's values needs it; padding zeros never do
-    if (__any(!(big <= fmax))) {
+    // clamped to [-FMAX, FMAX] (sign of zero kept; a NaN to -FMAX) and counted (a ballot and a scalar popcount:
+    // the count is wave-uniform) only where one of the wave's values needs it; padding zeros never do
+    if (nans || __any(!(big <= fmax))) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
         nsat += (uint32_t)__popcll(__ballot(fabsf(y[q]) > fmax));

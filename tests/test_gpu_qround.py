@@ -50,6 +50,23 @@ def test_given_scale_clamps_and_coarse(lib, fmt, mode, factor):
 
 @pytest.mark.parametrize("fmt", ["e4m3", "e5m2"])
 @pytest.mark.parametrize("mode", ["rne", "sr"])
+@pytest.mark.parametrize("scale", [0.0, float("nan")])
+def test_a_scale_without_quotients_clamps(lib, fmt, mode, scale):
+    """A caller's scale of 0 (a delayed scale before its first amax) or NaN: infinite quotients clamp and are
+    counted, quotients that are NaN (0 / 0, x / NaN) clamp to -FMAX uncounted, whatever their neighbours."""
+    x = torch.zeros(4099)
+    x[:600] = torch.linspace(-2, 2, 600)      # no zero among them; a wave of zeros after them
+    codes, s, dg = run(lib, x, fmt, mode, seed=3, trial=1, use=1, scale=torch.tensor([scale]))
+    top = 0x7E if fmt == "e4m3" else 0x7B     # the code of FMAX
+    want = np.full(4099, top | 0x80, np.uint8)
+    if scale == 0.0:
+        want[300:600] = top
+    assert np.array_equal(codes, want)
+    assert dg["n_saturated"] == (600 if scale == 0.0 else 0)
+
+
+@pytest.mark.parametrize("fmt", ["e4m3", "e5m2"])
+@pytest.mark.parametrize("mode", ["rne", "sr"])
 def test_codec_edge_values_unit_scale(lib, fmt, mode):
     f = FMT[fmt]
     grid = np.unique(np.abs(fp8.decode(np.arange(256, dtype=np.uint8), f)))
