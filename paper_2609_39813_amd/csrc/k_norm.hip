@@ -62,9 +62,11 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const T* __restrict__ 
 // squares pass through LDS, and lane l adds the entries l, l + 64, ... of the chunk, chunks in
 // order, so partial l still takes j = l, l + 64, ... ascending. A wave takes RMS_RPW rows (the
 // same trip count in every wave, so the block barriers are uniform); one amax atomic per block.
-// Below RMS_T4 rows a wave takes one (four leave CUs idle, each a chain of loads and barriers: 256 x
-// 64 8.7 us, now 4.2; 1111 x 520 13.6, now 7.6), above four (a quarter of the atomics).
-constexpr int64_t RMS_T4 = 8192;
+// One row per wave shortens its chain of loads and barriers, four take a quarter of the atomics on the one
+// amax word (about 3 us per 1024 rows of one). us with one, with four: 64 columns, 1024 rows 8.3, 10.3;
+// 2048 11.1, 10.8; 4096 17.1, 12.5. 1024 columns, 3072 rows 17.9, 18.7; 4096 20.9, 19.8. 2048 columns, 5120
+// rows 29.1, 30.9; 6144 32.9, 32.3. 8192 columns, 8184 rows 136, 145, the difference 6 less per 1024 rows.
+inline bool rms_one_row(int64_t T, int64_t d) { return T <= std::min<int64_t>(1024 + 2 * d, 8192); }
 
 template <typename T>
 __device__ __forceinline__ void load8_f32(const T* p, float (&x)[8]);
@@ -778,9 +780,9 @@ bs_status launch_rmsnorm_fwd(const void* X, bs_dtype dt, const float* gain, int6
     using One = std::integral_constant<int, 1>;
     using Four = std::integral_constant<int, 4>;
     if (vec && dt == BS_F32)
-      T < RMS_T4 ? fwd8(float{}, One{}) : fwd8(float{}, Four{});
+      rms_one_row(T, d) ? fwd8(float{}, One{}) : fwd8(float{}, Four{});
     else if (vec)
-      T < RMS_T4 ? fwd8(u16{}, One{}) : fwd8(u16{}, Four{});
+      rms_one_row(T, d) ? fwd8(u16{}, One{}) : fwd8(u16{}, Four{});
     else if (dt == BS_F32)
       rmsnorm_fwd_kernel<float><<<blocks, 256, 0, st>>>((const float*)X, gain, T, d, eps, u, rstd,
                                                         (uint32_t*)&diag->amax);

@@ -93,6 +93,14 @@ def test_trial_parts_of_the_new_rounding_counters(lib, T, d, K):
     compare(out, ref, pols, rows=rows, cols=cols, xrows=xrows, d=d, n=n)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("T,d", [(1152, 64), (1153, 64), (1165, 64), (1041, 8), (3073, 1024)])
+def test_rows_per_wave_of_the_forward(lib, dtype, T, d):
+    """One row per wave up to 1024 + 2 d rows, four beyond (a ragged last block of 16): codes bit for bit."""
+    out, ref = run_both(lib, T, d, 8, dtype, 1, ("U/R",), seed=T)
+    compare(out, ref, ("U/R",), d=d, n=8)
+
+
 def test_operands_off_16_bytes_take_the_same_values(lib):
     """fp32 W and dY one element past a 16-byte boundary: planes of each layout by a launch of their
     own, the same terms."""
