@@ -15,8 +15,8 @@
 //
 // A wave takes one row and TK trials; a lane takes groups of 4 consecutive classes (one Philox
 // call per group, draw and trial), the trials unrolled inside so that the element's part of the
-// first two rounds is shared and the trial's runs on the scalar unit. A block's four waves share
-// the row. A sum over the wave halves the trials each lane carries at each exchange.
+// first two rounds is shared and the trial's runs on the scalar unit. A block's up to four waves
+// share the row. A sum over the wave halves the trials each lane carries at each exchange.
 #include <algorithm>
 
 #include "bsp_kernels.h"
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(256) void lsm_trial_kernel(const double* __restrict
   const int64_t row = MORE ? row0 + blockIdx.x : blockIdx.x;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nsub = SUB ? 64 / L : 1;
-  const int k0 = (blockIdx.y * 4 + wave) * TK * nsub;  // trial index (trial k0 + 1) of the wave's first
+  const int k0 = (blockIdx.y * (blockDim.x >> 6) + wave) * TK * nsub;  // trial index (trial k0 + 1) of the wave's first
   if (k0 >= K) return;                                 // wave-uniform; no barrier below
   const int sub = SUB ? lane / L : 0, gl = SUB ? lane % L : lane;
   const int ngroups = C / 4;
@@ -275,24 +275,35 @@ bs_status bs_logsoftmax_reuse_check(const double* logits, const int32_t* target,
   const uint32_t base = store_id * 256u;
   {
     ProfScope prof("lsm_trial", st);
-    // L lanes per trial (short rows put several trials side by side); 16 trials per lane group
-    // where that still gives every SIMD two waves, else 4 (shorter serial chains on an idle chip)
+    // L lanes per trial (short rows put several trials side by side). Trials per lane group: as many as
+    // leave two waves of a row work (trials past K cost what others do: 4096 x 1000, one trial, 72 us
+    // with 1, 78 with 4, 112 with 16; 64 trials 325, 277, 268) and give every SIMD two waves (512 x
+    // 32768, 16 trials: 350 us with 2, 378 with 4, 613 with 16). As many waves per block as have trials.
     int L = 64;
     while (L > 16 && C / 4 <= L / 2) L /= 2;
     const int nsub = 64 / L;
-    const bool wide = rows * ((K + 16 * nsub - 1) / (16 * nsub)) >= 2048;
-    const int per = 4 * (wide ? 16 : 4) * nsub;
+    int tk = 1;
+    while (tk < 16 && 4 * tk * nsub <= K && rows * ((K + 2 * tk * nsub - 1) / (2 * tk * nsub)) >= 2048) tk *= 2;
+    const int nw = std::min(4, (K + tk * nsub - 1) / (tk * nsub)), per = nw * tk * nsub;
     for (int64_t r0 = 0; r0 < rows; r0 += LSM_ROWS) {
       const dim3 grid((unsigned)std::min(LSM_ROWS, rows - r0), (unsigned)((K + per - 1) / per));
-      auto go = [&](auto kernel) {
-        kernel<<<grid, 256, 0, st>>>(wp, wm, target, rows, C, L, eps, K, seed, base, base + 1, part, r0);
+      auto go = [&](auto n) {
+        constexpr int TK = decltype(n)::value;
+        auto run = [&](auto kernel) {
+          kernel<<<grid, 64 * nw, 0, st>>>(wp, wm, target, rows, C, L, eps, K, seed, base, base + 1, part, r0);
+        };
+        if (r0 == 0)
+          L == 64 ? run(lsm_trial_kernel<TK, false, false>) : run(lsm_trial_kernel<TK, true, false>);
+        else
+          L == 64 ? run(lsm_trial_kernel<TK, false, true>) : run(lsm_trial_kernel<TK, true, true>);
       };
-      if (r0 > 0)  // then wide
-        L == 64 ? go(lsm_trial_kernel<16, false, true>) : go(lsm_trial_kernel<16, true, true>);
-      else if (L == 64)
-        wide ? go(lsm_trial_kernel<16, false, false>) : go(lsm_trial_kernel<4, false, false>);
-      else
-        wide ? go(lsm_trial_kernel<16, true, false>) : go(lsm_trial_kernel<4, true, false>);
+      switch (tk) {
+        case 1: go(std::integral_constant<int, 1>{}); break;
+        case 2: go(std::integral_constant<int, 2>{}); break;
+        case 4: go(std::integral_constant<int, 4>{}); break;
+        case 8: go(std::integral_constant<int, 8>{}); break;
+        default: go(std::integral_constant<int, 16>{});
+      }
       BS_CHECK_LAUNCH();
     }
   }

@@ -44,10 +44,15 @@ def test_statistics_match_oracle(lib, rows, C, K, eps, calibrate):
 
 
 @pytest.mark.parametrize("rows,C,K", [
-    (2100, 16, 20),     # 16 lanes per trial, 16 trials per lane, a ragged last chunk of trials
-    (1030, 68, 70),     # 17 groups on 32 lanes, two trials side by side
-    (2050, 200, 17),    # 50 groups on 64 lanes, 16 trials per wave and one more
-    (3, 516, 9),        # 256 threads per row in the preparation, 4 trials per wave
+    (2100, 16, 20),     # 16 lanes per trial, 2 trials per lane, a ragged last chunk of trials
+    (1030, 68, 70),     # 17 groups on 32 lanes, two trials side by side, 16 per lane
+    (2050, 200, 17),    # 50 groups on 64 lanes, 8 trials per wave and one more
+    (3, 516, 9),        # 256 threads per row in the preparation, one trial per wave
+    (2100, 16, 140),    # 16 lanes per trial, 16 trials per lane, three waves
+    (2050, 200, 41),    # 64 lanes, 16 trials per wave, three waves
+    (2100, 132, 9),     # 4 trials per wave, the last wave with one
+    (2100, 16, 3),      # fewer trials than lie side by side in a wave
+    (2100, 516, 1),     # one trial: blocks of one wave
     (2, 4100, 5),       # 1024 threads per row, the lanes' last group ragged
     (1, 8, 4100),       # more than 4096 trials: 64 per block of the reduction
 ])
