@@ -536,7 +536,7 @@ static bs_status launch_gemm_wave(const GemmArgs& g, hipStream_t st) {
 // round over those the CUs hold):
 //   256 x 256   13 + 2 f (later 12.5) + n (0.98 + 0.38 f^4)   4096^2 x 1024: 37 measured, 37 estimated
 //   128 x 128   7.7 + 3 f (later 3 + 3 f) + n (0.4 + 0.44 f)  8192 x 1024^2: 24 and 24; 3000^2 x 512: 25 and 24
-//   32 x 32     2.4 + r (1.4, from 8 chunks 0.45 + 1.75 n/8)  512^2 x 1536: 8.7 and 8.1 (its 8 waves share the chunks)
+//   32 x 32     2.4 + r (1.4, from 8 chunks 0.45 + 1.75 n/8)  768^2 x 2048: 24 and 25 (its 8 waves share the chunks)
 //   split sum   4 + s M N 1e-6 (the partials out and in, and the launch)
 // (By output size alone, 256 x 256 from M N = 2^20, these took 33.3, 19.3 with 128 x 128, at 4160 x
 // 776 x 1152; 28.6, now 14.4, at 4096 x 512 x 1024; 16.3, now 8.7, at 512^2 x 1536. With rounds counted
@@ -547,7 +547,7 @@ struct GemmPlan {
 };
 // kind's time for `blocks` blocks of n chunks each
 static double gemm_estimate(int kind, double blocks, int n) {
-  if (kind == 2) return 2.4 + (n < 8 ? 1.4 : 0.45 + 1.75 * ((n + 7) / 8)) * std::max(1.0, blocks / 256);
+  if (kind == 2) return 2.4 + (n < 8 ? 1.4 : 0.45 + 1.75 * ((n + 7) / 8)) * std::ceil(blocks / 256);
   const double cap = kind == 0 ? 256 : 512, full = std::floor(blocks / cap);
   auto round = [&](double f, bool first) {
     return kind == 0 ? (first ? 13.0 + 2.0 * f : 12.5) + n * (0.98 + 0.38 * f * f * f * f)
