@@ -530,33 +530,34 @@ static bs_status launch_gemm_wave(const GemmArgs& g, hipStream_t st) {
 
 // Which kernel, and how many splits of K: the least estimated time of the pipelined kernel's 256 x 256
 // and 128 x 128 tiles (one and two blocks per CU) and the small-output kernel's 32 x 32 tiles.
-// The times (us) are fitted to launches of 60 shapes from 64 x 64 x 64 to 8192 x 8192 x 2048: rounds of
-// at most 256 (512) blocks, each with a fixed part (the first larger) and per 64-deep chunk of a block a
-// part that grows as more blocks load and multiply at once (n chunks per block, f the blocks of the
-// round over those the CUs hold):
-//   256 x 256   13 + 2 f (later 12.5) + n (0.98 + 0.38 f^4)   4096^2 x 1024: 37 measured, 37 estimated
-//   128 x 128   7.7 + 3 f (later 3 + 3 f) + n (0.4 + 0.44 f)  8192 x 1024^2: 24 and 24; 3000^2 x 512: 25 and 24
-//   32 x 32     2.4 + r (1.4, from 8 chunks 0.45 + 1.75 n/8)  768^2 x 2048: 24 and 25 (its 8 waves share the chunks)
+// The times (us) are fitted to launches of 141 shapes from 64 x 64 x 64 to 8192 x 8192 x 2048: a fixed
+// part, and per 64-deep chunk of a block a part that grows as more blocks load and multiply at once (n
+// chunks per block, f the share of the blocks the CUs hold, r rounds of them):
+//   256 x 256   13 + n (0.95 + 0.6 f)     4096^2 x 1024: 38 measured, 38 estimated
+//     rounds    each 12.5 + n (0.98 + 0.38 f^4), the first 2.5 more   8192 x 4096 x 1024: 72 and 71
+//   128 x 128   6.5 + n (0.42 + 0.6 f)    2048 x 4096 x 1024: 24 and 23; 640^2 x 2816: 25 and 26
+//     rounds    each 3 + 3 f + n (0.4 + 0.44 f), the first 4.7 more   16384 x 1024 x 512: 30 and 30
+//   32 x 32     2.4 + 1.9 n/8 r           512^2 x 1536: 8.7 and 8.1 (its 8 waves share the chunks; the rounds
+//               of a few chunks overlap, of more count whole: 768^2 x 2048 24 and 25)
 //   split sum   4 + s M N 1e-6 (the partials out and in, and the launch)
 // (By output size alone, 256 x 256 from M N = 2^20, these took 33.3, 19.3 with 128 x 128, at 4160 x
-// 776 x 1152; 28.6, now 14.4, at 4096 x 512 x 1024; 16.3, now 8.7, at 512^2 x 1536. With rounds counted
-// in fractions 16384 x 1024 x 512 took 28.5 with 128 x 128, 25.1 with 256 x 256.)
+// 776 x 1152; 28.6, now 14.4, at 4096 x 512 x 1024; 16.3, now 8.7, at 512^2 x 1536. With every round
+// counted by its fraction and no fixed part 16384 x 1024 x 512 took 28.5 with 128 x 128, 25.1 with 256 x
+// 256, and 768^2 x 2048 24.0 with 32 x 32, 20.1 with 128 x 128.)
 struct GemmPlan {
   int kind = 0;  // 0: 256 x 256, 1: 128 x 128, 2: 32 x 32
   int splits = 1;
 };
 // kind's time for `blocks` blocks of n chunks each
 static double gemm_estimate(int kind, double blocks, int n) {
-  if (kind == 2) return 2.4 + (n < 8 ? 1.4 : 0.45 + 1.75 * ((n + 7) / 8)) * std::ceil(blocks / 256);
-  const double cap = kind == 0 ? 256 : 512, full = std::floor(blocks / cap);
-  auto round = [&](double f, bool first) {
-    return kind == 0 ? (first ? 13.0 + 2.0 * f : 12.5) + n * (0.98 + 0.38 * f * f * f * f)
-                     : (first ? 7.7 : 3.0) + 3.0 * f + n * (0.4 + 0.44 * f);
+  const double cap = kind == 1 ? 512 : 256, r = blocks / cap;
+  if (kind == 2) return 2.4 + 1.9 * ((n + 7) / 8) * std::max(1.0, n < 24 ? r : std::ceil(r));
+  if (r <= 1.0) return (kind == 0 ? 13.0 : 6.5) + n * ((kind == 0 ? 0.95 : 0.42) + 0.6 * r);
+  auto round = [&](double f) {
+    return kind == 0 ? 12.5 + n * (0.98 + 0.38 * f * f * f * f) : 3.0 + 3.0 * f + n * (0.4 + 0.44 * f);
   };
-  const double f = blocks / cap - full;
-  double t = full > 0 ? round(1.0, true) + (full - 1) * round(1.0, false) : 0.0;
-  if (f > 0) t += round(f, full == 0);
-  return t;
+  const double full = std::floor(r);
+  return (kind == 0 ? 2.5 : 4.7) + full * round(1.0) + (r > full ? round(r - full) : 0.0);
 }
 static GemmPlan plan_gemm(const GemmArgs& g) {
   const int total = (int)std::min<int64_t>((int64_t)((g.K + LBK - 1) / LBK) * g.nseg, 1 << 30);
@@ -567,6 +568,7 @@ static GemmPlan plan_gemm(const GemmArgs& g) {
     const int bt = kind == 0 ? 256 : (kind == 1 ? 128 : 32);
     const double tiles = (double)((g.M + bt - 1) / bt) * ((g.N + bt - 1) / bt) * g.batch;
     for (int s = 1; s <= (kind == 2 ? 1 : std::max(1, top)); ++s) {
+      if (s > 1 && tiles * s > (kind == 0 ? 256 : 512)) break;  // more blocks than the CUs hold gain nothing
       double t = gemm_estimate(kind, tiles * s, (total + s - 1) / s);
       if (s > 1) t += 4.0 + s * (double)g.M * g.N * 1e-6;
       if (t < tb) tb = t, best.kind = kind, best.splits = s;
