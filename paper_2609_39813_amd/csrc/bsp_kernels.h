@@ -22,10 +22,10 @@ struct GemmArgs {
   int f16 = 0;              // 1: every operand holds fp16 values (the 2-term fp16 split), else bf16
   const float* alpha_dev2 = nullptr;  // nullable: a second device multiplier of alpha
   uint32_t* amax = nullptr;  // nullable: slots (AMAX_SLOTS) raised to max |C| of the values written
-                             // (C's new values, accumulate = 0 only; the pipelined kernel only)
+                             // (C's new values, accumulate = 0 only; 16-byte aligned operands only)
   // batch > 1: that many independent contractions, z = 0 .. batch - 1, each with every segment's
   // A and B offset by z sA, z sB elements, C by z sC and alpha_dev2 by z s_alpha2 (no split-K;
-  // the pipelined kernel only)
+  // 16-byte aligned operands only)
   int batch = 1;
   int64_t sA = 0, sB = 0, sC = 0, s_alpha2 = 0;
   int64_t s_amax = 0;  // stride of amax over the members
@@ -132,7 +132,6 @@ bs_status launch_combine(const float* ref, const float* bias, const float* se, i
                          float* bias_out, float* se_out, hipStream_t st);
 
 bs_status launch_fill2d(float* p, int64_t rows, int64_t cols, int64_t ld, float v, hipStream_t st);
-bs_status launch_fill_f64(double* p, int64_t n, double v, hipStream_t st);
 // the slot array out (AMAX_SLOTS words AMAX_STRIDE apart, float bits, zeroed by the caller) raised
 // to max |x[i]| over n values
 bs_status launch_amax_f32(const float* x, int64_t n, uint32_t* out, hipStream_t st);

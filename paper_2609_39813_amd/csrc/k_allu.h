@@ -99,8 +99,6 @@ bs_status launch_allu_d(const AlluDArgs& a, hipStream_t st);
 
 // mean of K trials from shifted sums: out = d1 + S1 / K
 bs_status launch_trial_mean(const float* d1, const double* S1, int K, int64_t m, float* out, hipStream_t st);
-// out[i] = v for n floats (any v, NaN included)
-bs_status launch_fill(float* out, int64_t n, float v, hipStream_t st);
 // Copies (src) and fills (src null: the value v) of whole arrays, every job in one launch.
 constexpr int COPY_MAX = 48;
 struct CopyJob {

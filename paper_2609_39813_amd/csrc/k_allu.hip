@@ -269,11 +269,6 @@ __global__ __launch_bounds__(256) void trial_mean_kernel(const float* __restrict
     out[i] = (float)((double)d1[i] + S1[i] / (double)K);
 }
 
-__global__ __launch_bounds__(256) void fill_kernel(float* __restrict__ out, int64_t n, float v) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    out[i] = v;
-}
-
 // job j's 4096-element pieces are blocks first[j] .. first[j + 1] - 1. Bound by memory; one launch
 // for the 48 arrays of the small layer check (22 us; its copies and fills one by one took about 195).
 __global__ __launch_bounds__(256) void copy_batch_kernel(CopyBatch b) {
@@ -381,13 +376,6 @@ bs_status launch_copy_batch(CopyBatch& b, hipStream_t st) {
     if (blocks > 0x7FFFFFFF) return BS_ESHAPE;
   }
   if (blocks > 0) copy_batch_kernel<<<(unsigned)blocks, 256, 0, st>>>(b);
-  BS_CHECK_LAUNCH();
-  return BS_OK;
-}
-
-bs_status launch_fill(float* out, int64_t n, float v, hipStream_t st) {
-  if (n <= 0) return BS_OK;
-  fill_kernel<<<blocks1d(n), 256, 0, st>>>(out, n, v);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }

@@ -120,7 +120,4 @@ bs_status launch_trial_se(const double* S1, const double* S2, int K, int64_t m, 
 bs_status launch_gain_final(const double* part, int64_t nrt, int64_t d, float* ref, float* bias_r, float* bias_n,
                             hipStream_t st, int nz = 1, int64_t s_part = 0, int64_t s_ref = 0);
 
-bs_status launch_combine_alt(const float* ref, const float* alt, int64_t n, float* mean_out, float* bias_out,
-                             float* se_out, hipStream_t st);
-
 }  // namespace bsp

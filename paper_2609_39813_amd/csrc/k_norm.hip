@@ -747,16 +747,6 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ 
 }
 
 // mean = alt, bias = alt - ref (a use whose reading is computed in full).
-__global__ __launch_bounds__(256) void combine_alt_kernel(const float* __restrict__ ref, const float* __restrict__ alt,
-                                                          int64_t n, float* __restrict__ mean_out,
-                                                          float* __restrict__ bias_out, float* __restrict__ se_out) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    if (mean_out) mean_out[i] = alt[i];
-    if (bias_out) bias_out[i] = alt[i] - ref[i];
-    if (se_out) se_out[i] = 0.0f;
-  }
-}
-
 // ------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------
@@ -1007,14 +997,6 @@ bs_status launch_combine(const float* ref, const float* bias, const float* se, i
                          float* bias_out, float* se_out, hipStream_t st) {
   if (n <= 0 || (!mean_out && !bias_out && !se_out)) return BS_OK;
   combine_kernel<<<grid1d((n + 3) / 4, 4096), 256, 0, st>>>(ref, bias, se, n, mean_out, bias_out, se_out);
-  BS_CHECK_LAUNCH();
-  return BS_OK;
-}
-
-bs_status launch_combine_alt(const float* ref, const float* alt, int64_t n, float* mean_out, float* bias_out,
-                             float* se_out, hipStream_t st) {
-  if (n <= 0 || (!mean_out && !bias_out && !se_out)) return BS_OK;
-  combine_alt_kernel<<<grid1d(n), 256, 0, st>>>(ref, alt, n, mean_out, bias_out, se_out);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }

@@ -24,22 +24,12 @@ __global__ void fill2d_kernel(float* p, int64_t rows, int64_t cols, int64_t ld, 
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
     p[(i / cols) * ld + (i % cols)] = v;
 }
-__global__ void fill_f64_kernel(double* p, int64_t n, double v) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
-}
 
 bs_status launch_fill2d(float* p, int64_t rows, int64_t cols, int64_t ld, float v, hipStream_t st) {
   const int64_t n = rows * cols;
   if (n <= 0) return BS_OK;
   const int64_t want = (n + 255) / 256;
   fill2d_kernel<<<(unsigned)(want < 4096 ? want : 4096), 256, 0, st>>>(p, rows, cols, ld, v);
-  BS_CHECK_LAUNCH();
-  return BS_OK;
-}
-bs_status launch_fill_f64(double* p, int64_t n, double v, hipStream_t st) {
-  if (n <= 0) return BS_OK;
-  const int64_t want = (n + 255) / 256;
-  fill_f64_kernel<<<(unsigned)(want < 4096 ? want : 4096), 256, 0, st>>>(p, n, v);
   BS_CHECK_LAUNCH();
   return BS_OK;
 }

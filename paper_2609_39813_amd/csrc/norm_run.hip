@@ -234,7 +234,7 @@ bs_status norm_run(const NormIO& io, void* ws, size_t ws_bytes, hipStream_t st) 
   }
   if (fwd_only) return BS_OK;
 
-  const bool du16 = h16 && n % 64 == 0;  // du's fp16 contraction runs on the pipelined kernel (K % 64)
+  const bool du16 = h16 && n % 64 == 0;  // du in fp16; of other n its operands stay three exact bf16 terms
   const int ntd = h16 ? 2 : nt;  // terms of the incoming gradient's planes
   if (h16) {
     // dY's scaled two-term fp16 split in both layouts from one read, W as scaled fp16
