@@ -10,8 +10,8 @@
 // fp64, from the logits); a trial adds the one its sign picks. Per element and trial that leaves
 // two Philox words (8.5 VALU each), a compare, a 64-bit select and an fp64 add per copy: 26 VALU,
 // the bound. (Forming g and g* anew per trial took a third word for 1^T h and four fp64 quotients:
-// 7.0 ms at 512 x 32768, 64 trials; now 0.78 ms, 1.38 T element-trials/s against 1.46 at the VALU
-// ceiling.)
+// 7.0 ms at 512 x 32768, 64 trials; now 0.78 ms of 0.93 for the call, 1.38 T element-trials/s against 1.46
+// at the VALU ceiling; 0.90 ms in a trace of six calls, at the clock of an idle chip.)
 //
 // A wave takes one row and TK trials; a lane takes groups of 4 consecutive classes (one Philox
 // call per group, draw and trial), the trials unrolled inside so that the element's part of the
