@@ -179,7 +179,10 @@ def test_attention_reference_matches_autograd():
     for name, t in (("dQ", Qr), ("dK", Kr), ("dV", Vr)):
         ref = t.grad[0].numpy()
         assert np.abs(out[name + "_ref"] - ref).max() <= 1e-6 * max(1.0, np.abs(ref).max()), name
-    np.testing.assert_allclose(out["O"], (pq @ V).numpy(), rtol=0, atol=0)
+    # the same fp64 products summed in the order of either library's kernel (which depends on the host):
+    # at most S roundings of 2^-53 each on both sides
+    bound = 2 * S * 2.0 ** -53 * (pq.abs() @ V.abs()).numpy()
+    assert (np.abs(out["O"] - (pq @ V).numpy()) <= bound).all()
 
 
 def test_attention_policy_zeros_and_draw_counts():
