@@ -402,7 +402,7 @@ __global__ __launch_bounds__(256, 2) void pstore_rows_kernel(PstoreArgs a) {
 // bias fields and dQ: per element the sums over trials, then the fields of every read; the
 // fields go to memory for the key-major pass and into dQ = c sum_k field K (three bf16 terms).
 // Bound by the VALU work (445 instructions an element with every field, 256 of them the trial
-// sums of K = 32) at one wave per SIMD (six fields' accumulators): 730 us at 64 heads of 1024.
+// sums of K = 32) at one wave per SIMD (six fields' accumulators): 695 us at 64 heads of 1024.
 // ------------------------------------------------------------------------------------
 // ALL: every field is needed; AB: the trial sums of b too (J2 is)
 template <int FMT, bool ALL, bool AB>
@@ -628,8 +628,8 @@ __global__ __launch_bounds__(256) void pstore_dq_kernel(PstoreArgs a) {
 // key-major, the needed fields: dK = c sum_q field Q (three bf16 terms per field) for the fields
 // id[0..NF-1] (the reference first); DV: dV = s sum_q val(C) dO (one term) and its biases
 // sum_q field dO. Lane (g, c16) of wave w owns key k0 + 16 w + c16.
-// Bound by the fields' bytes, read back at 2.6 TB/s (64 heads of 1024, all eight fields: 1.14 GB,
-// 435 us; half the registers at twice the waves, or other orders of a tile, read no faster). A half
+// Bound by the fields' bytes, read back at 2.9 TB/s (64 heads of 1024, all eight fields: 1.14 GB,
+// 400 us; half the registers at twice the waves, or other orders of a tile, read no faster). A half
 // tile's fields are loaded while the half before is multiplied, and no load is under a condition:
 // behind one the compiler waits for every load before it, and an array filled there goes through
 // scratch. Fields no policy reads are neither stored nor read: J(p_q), J(a), K(a) and a mean of a
